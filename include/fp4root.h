@@ -341,15 +341,13 @@ const char* fp4root_status_string(int status);
 int fp4root_version(void);
 
 /* ---- product tiling (tests and tuning) --------------------------------------
- * The NVFP4 products cover each 128 x 128 output tile with four waves of 64 x 64
- * outputs ("wide") or eight waves of 32 x 64 ("narrow").  By default (mode 0) the
- * Gram of qX and the update product take the wide form for a launch that fills
- * whole rounds of resident workgroups (two per CU) or at least four rounds, the
- * narrow form otherwise; the Gram with the B epilogue always takes the narrow one.
- * Mode 1 forces the narrow form everywhere, mode 2 the wide form for the Gram of
- * qX and the update product.  Every product is exact, so outputs are bit for bit
- * the same in every mode; only the time changes.  The setting is process-wide and
- * applies to launches issued after the call (calls on other threads race with it).
+ * The NVFP4 products run with workgroup tiles of 128 x 128 outputs, 64 x 64 per wave
+ * ("wide"), or 64 x 64 outputs, 32 x 32 per wave ("narrow").  By default (mode 0) a
+ * launch takes the wide form when it has at least one round of wide workgroups (two
+ * per CU), the narrow form otherwise.  Mode 1 forces the narrow form everywhere, mode
+ * 2 the wide form.  Every product is exact, so outputs are bit for bit the same in
+ * every mode; only the time changes.  The setting is process-wide and applies to
+ * launches issued after the call (calls on other threads race with it).
  * Returns the previous mode, or FP4ROOT_ERR_INVALID_ARG for a mode outside 0..2. */
 int fp4root_set_product_tiling(int mode);
 

@@ -143,18 +143,28 @@ struct StepWs {
   uint8_t *qx_c = nullptr, *qx_s = nullptr, *qxt_c = nullptr, *qxt_s = nullptr;
   float* A = nullptr;
   uint8_t *qa_c = nullptr, *qa_s = nullptr;
-  // chain bound records (per 64-element stage and 16 rows) of qX, qXt and qA / qB,
-  // when m and n are multiples of 64 (else null: the products fold every block)
-  float *rho_x = nullptr, *rho_xt = nullptr, *rho_a = nullptr;
+  // chain bounds of qX, qXt and qA / qB: row words and levels (ChainOp), or the
+  // encoders' own records alone (see use_levels)
+  uint32_t *words_x = nullptr, *words_xt = nullptr, *words_a = nullptr;
+  float *rec_x = nullptr, *rec_xt = nullptr, *rec_a = nullptr;
   // BF16 path
   uint16_t *xb = nullptr, *a16 = nullptr, *b16 = nullptr;
   char* blaslt_ws = nullptr;   // scratch of the library GEMM (update product)
 };
 
+// Chain bounds over runs of up to four stages take one more launch per encoder; with
+// few stages the encoders' own one-stage records do.
+constexpr int64_t kLevelsMinK = 1024;
+bool use_levels(int64_t K) { return K >= kLevelsMinK; }
+int64_t words_stride(int64_t rows, int64_t K) { return (K + 63) / 64 * rows; }
+int64_t rec_stride(int64_t rows, int64_t K) {
+  return use_levels(K) ? chain_level_count(rows, K) : rows / 16 * ((K + 63) / 64);
+}
+
 void carve_step(Carver& cv, int64_t batch, int64_t m, int64_t n, bool bf16, StepWs& w) {
   w.sc = cv.take<MatScalars>((size_t)batch);
   if (!bf16) {
-    // the products' operands, stage-major (see QOut::tiled)
+    // the products' operands, stage-major (see OperandOut)
     w.qx_c = cv.take<uint8_t>((size_t)(batch * tiled_code_bytes(m, n)));
     w.qx_s = cv.take<uint8_t>((size_t)(batch * tiled_scale_bytes(m, n)));
     w.qxt_c = cv.take<uint8_t>((size_t)(batch * tiled_code_bytes(n, m)));
@@ -162,10 +172,13 @@ void carve_step(Carver& cv, int64_t batch, int64_t m, int64_t n, bool bf16, Step
     w.A = cv.take<float>((size_t)(batch * m * m));
     w.qa_c = cv.take<uint8_t>((size_t)(batch * tiled_code_bytes(m, m)));
     w.qa_s = cv.take<uint8_t>((size_t)(batch * tiled_scale_bytes(m, m)));
-    if (m % 64 == 0 && n % 64 == 0) {
-      w.rho_x = cv.take<float>((size_t)(batch * m * n / 1024));
-      w.rho_xt = cv.take<float>((size_t)(batch * m * n / 1024));
-      w.rho_a = cv.take<float>((size_t)(batch * m * m / 1024));
+    w.rec_x = cv.take<float>((size_t)(batch * rec_stride(m, n)));
+    w.rec_xt = cv.take<float>((size_t)(batch * rec_stride(n, m)));
+    w.rec_a = cv.take<float>((size_t)(batch * rec_stride(m, m)));
+    if (use_levels(n)) w.words_x = cv.take<uint32_t>((size_t)(batch * words_stride(m, n)));
+    if (use_levels(m)) {
+      w.words_xt = cv.take<uint32_t>((size_t)(batch * words_stride(n, m)));
+      w.words_a = cv.take<uint32_t>((size_t)(batch * words_stride(m, m)));
     }
   } else {
     w.xb = cv.take<uint16_t>((size_t)(batch * m * n));
@@ -190,14 +203,49 @@ hipError_t export_operand(uint8_t* codes, uint8_t* scales, const uint8_t* tc, co
 }
 
 // Operand views of the stage-major buffers of one step.
-QOut tiled_out(uint8_t* c, uint8_t* s, int64_t rows, int64_t K, float* rho) {
-  QOut q{c, s, tiled_code_bytes(rows, K), tiled_scale_bytes(rows, K), rho, rows * K / 1024};
-  q.tiled = 1;
+OperandOut operand_out(uint8_t* c, uint8_t* s, int64_t rows, int64_t K, uint32_t* words, float* rec) {
+  OperandOut q{c, s, tiled_code_bytes(rows, K), tiled_scale_bytes(rows, K)};
+  if (!rec) return q;   // binary32 accumulation: no chain bounds
+  if (words) {
+    q.words = words;
+    q.words_bstride = words_stride(rows, K);
+  } else {
+    q.rec = rec;
+    q.rec_bstride = rec_stride(rows, K);
+  }
   return q;
 }
-Fp4Operand tiled_operand(const uint8_t* c, const uint8_t* s, int64_t rows, int64_t K, const float* rho) {
-  return Fp4Operand{c, s, tiled_code_bytes(rows, K), tiled_scale_bytes(rows, K), rho, rows * K / 1024};
+Fp4Operand tiled_operand(const uint8_t* c, const uint8_t* s, int64_t rows, int64_t K, const float* rec) {
+  Fp4Operand o{c, s, tiled_code_bytes(rows, K), tiled_scale_bytes(rows, K)};
+  if (!rec) return o;
+  o.rec = rec;
+  o.rec_bstride = rec_stride(rows, K);
+  o.levels = use_levels(K) ? 3 : 1;
+  return o;
 }
+// The chain levels of an operand's row words.
+ChainOp chain_op(const uint32_t* words, float* rec, int64_t batch, int64_t rows, int64_t K) {
+  return ChainOp{words, rec, words_stride(rows, K), rec_stride(rows, K), rows, (int32_t)((K + 63) / 64),
+                 (int32_t)batch};
+}
+// Collects operands whose words await reduction; launches when full or flushed.
+struct ChainQueue {
+  ChainOp op[kMaxChainOps];
+  int count = 0;
+  hipStream_t st;
+  explicit ChainQueue(hipStream_t s) : st(s) {}
+  hipError_t add(const OperandOut& q, float* rec, int64_t batch, int64_t rows, int64_t K) {
+    if (!q.words) return hipSuccess;
+    op[count++] = chain_op(q.words, rec, batch, rows, K);
+    return count == kMaxChainOps ? flush() : hipSuccess;
+  }
+  hipError_t flush() {
+    if (count == 0) return hipSuccess;
+    const hipError_t e = launch_chain_levels(op, count, st);
+    count = 0;
+    return e;
+  }
+};
 
 // One shape group in one NVFP4 NS step: a batch of m x n matrices at x (matrix
 // stride bstride), its step workspace, its coefficients, and (last step of a
@@ -256,6 +304,7 @@ int run_step_fp4(const StepGroup* gs, int count, uint32_t flags, uint64_t seed, 
   auto rec = [acc32](float* r) { return acc32 ? nullptr : r; };
   const uint32_t mask = sign_mask(seed, step), next_mask = sign_mask(seed, step + 1);
   const int xn = xs, xm = xs + 1, nxn = xs ^ 2, nxm = (xs ^ 2) + 1;
+  ChainQueue chains(st);
   // qX and qXt; the amax slots recorded later in the step are cleared by the encoder
   // of X (or before the amax passes of X when those run first)
   for (int i = 0; i < count; ++i) {
@@ -269,15 +318,18 @@ int run_step_fp4(const StepGroup* gs, int count, uint32_t flags, uint64_t seed, 
       FP4R_TRY(launch_amax(bx, 1, mask, rot, false, w.sc, xn, status, st));
       FP4R_TRY(launch_amax(bx, 0, mask, rot, false, w.sc, xm, status, st));
     }
-    const QOut qx = tiled_out(w.qx_c, w.qx_s, sg.m, sg.n, rec(w.rho_x));
-    const QOut qxt = tiled_out(w.qxt_c, w.qxt_s, sg.n, sg.m, rec(w.rho_xt));
+    const OperandOut qx = operand_out(w.qx_c, w.qx_s, sg.m, sg.n, w.words_x, rec(w.rec_x));
+    const OperandOut qxt = operand_out(w.qxt_c, w.qxt_s, sg.n, sg.m, w.words_xt, rec(w.rec_xt));
     FP4R_TRY(launch_encode_x2(sg.x, sg.batch, sg.m, sg.n, sg.bstride, mask, rot, ad, w.sc, xn, xm, qx, qxt, st,
                               reset));
+    FP4R_TRY(chains.add(qx, w.rec_x, sg.batch, sg.m, sg.n));
+    FP4R_TRY(chains.add(qxt, w.rec_xt, sg.batch, sg.n, sg.m));
   }
+  FP4R_TRY(chains.flush());
   // A = qX qX^T, recording amax(A H)
   FP4R_TRY(launch_products(kModeGramA, 0, gs, count, [&](const StepGroup& sg) {
     GemmFp4Args g = product_args(sg, mask, rot, acc32);
-    g.a = tiled_operand(sg.w->qx_c, sg.w->qx_s, sg.m, sg.n, rec(sg.w->rho_x));
+    g.a = tiled_operand(sg.w->qx_c, sg.w->qx_s, sg.m, sg.n, rec(sg.w->rec_x));
     g.b = g.a;
     g.M = sg.m; g.N = sg.m; g.K = sg.n;
     g.slot_a = g.slot_b = xn;
@@ -289,10 +341,12 @@ int run_step_fp4(const StepGroup* gs, int count, uint32_t flags, uint64_t seed, 
   // qA
   for (int i = 0; i < count; ++i) {
     const StepGroup& sg = gs[i];
-    const Batch ba{sg.w->A, sg.batch, sg.m, sg.m, sg.m, sg.m * sg.m};
-    const QOut qa = tiled_out(sg.w->qa_c, sg.w->qa_s, sg.m, sg.m, rec(sg.w->rho_a));
-    FP4R_TRY(launch_encode(ba, 1, mask, rot, false, ad, sg.w->sc, kSlotA, qa, nullptr, st));
+    const StepWs& w = *sg.w;
+    const OperandOut qa = operand_out(w.qa_c, w.qa_s, sg.m, sg.m, w.words_a, rec(w.rec_a));
+    FP4R_TRY(launch_encode_operand(w.A, sg.batch, sg.m, sg.m, sg.m * sg.m, mask, rot, ad, w.sc, kSlotA, qa, st));
+    FP4R_TRY(chains.add(qa, w.rec_a, sg.batch, sg.m, sg.m));
   }
+  FP4R_TRY(chains.flush());
   if (tr) {
     const StepGroup& sg = gs[0];
     FP4R_TRY(export_operand(tr->qa_codes, tr->qa_scales, sg.w->qa_c, sg.w->qa_s, sg.batch, sg.m, sg.m, st));
@@ -301,7 +355,7 @@ int run_step_fp4(const StepGroup* gs, int count, uint32_t flags, uint64_t seed, 
   // B = b A + c qA qA^T, written over A, recording amax(B H)
   FP4R_TRY(launch_products(kModeGramB, 1, gs, count, [&](const StepGroup& sg) {
     GemmFp4Args g = product_args(sg, mask, rot, acc32);
-    g.a = tiled_operand(sg.w->qa_c, sg.w->qa_s, sg.m, sg.m, rec(sg.w->rho_a));
+    g.a = tiled_operand(sg.w->qa_c, sg.w->qa_s, sg.m, sg.m, rec(sg.w->rec_a));
     g.b = g.a;
     g.M = sg.m; g.N = sg.m; g.K = sg.m;
     g.slot_a = g.slot_b = kSlotA;
@@ -317,9 +371,10 @@ int run_step_fp4(const StepGroup* gs, int count, uint32_t flags, uint64_t seed, 
   for (int i = 0; i < count; ++i) {
     const StepGroup& sg = gs[i];
     const StepWs& w = *sg.w;
-    const Batch ba{w.A, sg.batch, sg.m, sg.m, sg.m, sg.m * sg.m};
-    const QOut qb = tiled_out(w.qa_c, w.qa_s, sg.m, sg.m, rec(w.rho_a));
-    FP4R_TRY(launch_encode(ba, 1, mask, rot, false, ad, w.sc, kSlotB, qb, nullptr, st));
+    const OperandOut qb = operand_out(w.qa_c, w.qa_s, sg.m, sg.m, w.words_a, rec(w.rec_a));
+    FP4R_TRY(launch_encode_operand(w.A, sg.batch, sg.m, sg.m, sg.m * sg.m, mask, rot, ad, w.sc, kSlotB, qb, st));
+    FP4R_TRY(chains.add(qb, w.rec_a, sg.batch, sg.m, sg.m));
+    FP4R_TRY(chains.flush());
     // last step: X_{k+1} goes straight to the callers' matrices
     GemmFin fin;
     if (sg.fin) {
@@ -340,8 +395,8 @@ int run_step_fp4(const StepGroup* gs, int count, uint32_t flags, uint64_t seed, 
     }
     FP4R_TRY(launch_products(kModeUpdateX, 2, gs + i, 1, [&](const StepGroup& u) {
       GemmFp4Args g = product_args(u, next_mask, rot, acc32);
-      g.a = tiled_operand(u.w->qa_c, u.w->qa_s, u.m, u.m, rec(u.w->rho_a));
-      g.b = tiled_operand(u.w->qxt_c, u.w->qxt_s, u.n, u.m, rec(u.w->rho_xt));
+      g.a = tiled_operand(u.w->qa_c, u.w->qa_s, u.m, u.m, rec(u.w->rec_a));
+      g.b = tiled_operand(u.w->qxt_c, u.w->qxt_s, u.n, u.m, rec(u.w->rec_xt));
       g.M = u.m; g.N = u.n; g.K = u.m;
       g.slot_a = kSlotB; g.slot_b = xm;
       g.out = u.x; g.out_bstride = u.bstride; g.aux = u.x;

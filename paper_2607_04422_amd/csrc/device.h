@@ -467,20 +467,27 @@ FP4R_DEV void mom_block(const float (&x)[16], const uint8_t* codes, const uint8_
   for (int i = 0; i < 16; ++i) mv[i] = (float)__builtin_fma((double)b1, (double)mh[i], (double)b2 * (double)x[i]);
 }
 
-// Chain bound of one 4-block stage of a row (the NVFP4 products accumulate a
-// stage in binary32 when rho sigma < 2^48, see gemm_fp4.hip):
-//   rho = sum_b n2_b 4^(e_b - e_min),  e = max(exponent field, 1) over blocks with
-// a non-zero scale (a zero block adds nothing and does not lower e_min).
-FP4R_DEV uint32_t block_exp(uint32_t scale) {
-  return (scale & 0x7Fu) ? max((scale >> 3) & 15u, 1u) : 15u;
+// Chain bound (the NVFP4 products accumulate a group of blocks in binary32 when
+// rho sigma < 2^48, see gemm_fp4.hip).  A block's elements are multiples of
+// 2^(e - 11), e = the exponent field (at least 1) plus the number of trailing zero
+// bits of the scale's integer significand M, and the sum of their squares is
+// n2 4^(E - 11), E the exponent field alone.  A row's bound over a group of blocks is
+//   rho = T 4^(-e_min),  T = sum_b n2_b 4^(E_b),  e_min = min e_b over blocks with a
+// non-zero scale (a zero block adds nothing and does not lower e_min).
+FP4R_DEV uint32_t scale_exp(uint32_t scale) { return max((scale >> 3) & 15u, 1u); }
+FP4R_DEV uint32_t block_unit(uint32_t scale) {   // e, at most 15 (a smaller unit is a valid one)
+  if ((scale & 0x7Fu) == 0u) return 15u;
+  const uint32_t mant = (scale >> 3) ? 8u + (scale & 7u) : (scale & 7u);
+  return min(scale_exp(scale) + (uint32_t)__builtin_ctz(mant), 15u);
 }
-FP4R_DEV float stage_rho(const uint32_t (&n2)[4], const uint32_t (&e)[4]) {
-  const uint32_t emin = min(min(e[0], e[1]), min(e[2], e[3]));
-  double r = 0.0;
-#pragma unroll
-  for (int b = 0; b < 4; ++b) r += ldexp((double)n2[b], 2 * (int)(e[b] - emin));
-  return ru32(r);   // the sum is exact in binary64 (terms n2 < 2^19 times 4^k, k <= 14)
+FP4R_DEV float block_square(uint32_t n2, uint32_t scale) {   // n2 4^E (exact: n2 < 2^19)
+  return ldexpf((float)n2, 2 * (int)scale_exp(scale));
 }
+// A stage of one row as a word: T rounded up to 28 bits of its pattern (past the two
+// roundings of the sum of four), e_min in the low four bits.
+FP4R_DEV uint32_t row_word(float t, uint32_t e) { return ((__float_as_uint(t) + 31u) & ~15u) | e; }
+FP4R_DEV float word_square(uint32_t w) { return __uint_as_float(w & ~15u); }
+FP4R_DEV float word_rho(uint32_t w) { return ldexpf(word_square(w), -2 * (int)(w & 15u)); }   // exact
 
 // Lane moves within a row of 16 lanes (DPP; every source lane of the patterns used
 // exists, and all lanes of the wave must be active): quad_perm broadcasts of lane k
@@ -491,12 +498,16 @@ FP4R_DEV uint32_t dpp_u(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xF, 0xF, true);
 }
 
-// The stage bound of the row whose four blocks sit in lanes 4i .. 4i + 3.  All
-// lanes of the wave must be active.
-FP4R_DEV float quad_stage_rho(uint32_t n2, uint32_t e) {
-  const uint32_t qn[4] = {dpp_u<0x00>(n2), dpp_u<0x55>(n2), dpp_u<0xAA>(n2), dpp_u<0xFF>(n2)};
-  const uint32_t qe[4] = {dpp_u<0x00>(e), dpp_u<0x55>(e), dpp_u<0xAA>(e), dpp_u<0xFF>(e)};
-  return stage_rho(qn, qe);
+// The stage word of the row whose four blocks sit in lanes 4i .. 4i + 3 (every lane of
+// the quad gets it).  All lanes of the wave must be active.
+FP4R_DEV uint32_t quad_row_word(uint32_t n2, uint32_t scale) {
+  float t = block_square(n2, scale);
+  t = t + __uint_as_float(dpp_u<0xB1>(__float_as_uint(t)));
+  t = t + __uint_as_float(dpp_u<0x4E>(__float_as_uint(t)));
+  uint32_t e = block_unit(scale);
+  e = min(e, dpp_u<0xB1>(e));
+  e = min(e, dpp_u<0x4E>(e));
+  return row_word(t, e);
 }
 
 // Maximum of non-negative values over each 16 lanes / over the wave (compared as

@@ -6,53 +6,56 @@
 //   B = b A + c qA qA^T (K = m, symmetric; epilogue reads A, may overwrite it)
 //   X <- a X + qB qXt^T (K = m; epilogue reads X_k and writes X_{k+1} in place)
 //
-// NVFP4 operands (exact bridge): codes and E4M3 scales are decoded to f16
-// while staging into LDS (q * s needs at most 6 significant bits and lies in
-// [2^-10, 2688], so it is exact in f16).  One MFMA 32x32x16 covers exactly one
-// 16-element block: all its products are integer multiples of s_a s_b / 4 with
-// |sum| < 2^19 of those units, so the MFMA result (accumulator input 0) is the
-// exact block sum.  Block sums are accumulated in binary64 and the epilogue
-// forms the output in binary64 and rounds once to binary32, so every product
-// equals the binary32 rounding of its exact value whenever the binary64 running
-// sums are exact (every partial sum within 53 bits of the smallest product unit,
-// which holds unless the block exponents of a row span more than about 20 binades).
+// NVFP4 operands (exact bridge): codes and E4M3 scales are decoded to f16 in
+// registers (q * s needs at most 6 significant bits and lies in [2^-10, 2688], so it
+// is exact in f16).  One MFMA 32x32x16 covers exactly one 16-element block: all its
+// products are integer multiples of s_a s_b / 4 with |sum| < 2^19 of those units, so
+// the MFMA result (accumulator input 0) is the exact block sum.  Block sums are
+// accumulated in binary64 and the epilogue forms the output in binary64 and rounds
+// once to binary32, so every product equals the binary32 rounding of its exact value
+// whenever the binary64 running sums are exact (every partial sum within 53 bits of
+// the smallest product unit, which holds unless the block exponents of a row span
+// more than about 20 binades).
 //
 // Chained blocks.  Element values are q s with q = k/2 (|k| <= 12) and
-// s = M 2^(e-10) (E4M3: M <= 15, e >= 1; subnormal scales as M = m, e = 1), so
-// every product of a row i of the first operand and a row j of the second over
-// a group G of blocks is a multiple of u = 2^(ea_min(i) + eb_min(j) - 22), the
-// minima over G.  Any partial sum of those products, in any order, is at most
-// their sum of magnitudes, and by Cauchy-Schwarz at most sqrt(T_a(i) T_b(j)),
-// T being the sum of squared values over G.  With rho_i = T_a(i) 2^(22 - 2 ea_min(i))
-// = sum_b n2_b 4^(e_b - ea_min(i)) (n2 = sum (2q)^2 M^2 per block; sigma_j alike)
-// the bound is below 2^24 u whenever rho_i sigma_j < 2^48; then every partial
-// sum is exactly representable in binary32, and the MFMAs of the group may
-// accumulate into one binary32 register, folded into binary64 once.  The encoders
-// store rho per 16 rows for every 64-element stage (four blocks), rounded up to
-// binary32.  Each compute wave tests the maxima over its own rows (diagonal tiles
-// of symmetric products test tile-wide maxima, so that (i, j) and (j, i) add the
-// same binary32 values in the same order and the product stays exactly symmetric)
-// and runs every stage either as one group or as one group per block.
+// s = M 2^(E-10) (E4M3: M <= 15, E >= 1; subnormal scales as M = m, E = 1).  With
+// e = E + (trailing zero bits of M), every product of a row i of the first operand and
+// a row j of the second over a group G of blocks is a multiple of
+// u = 2^(ea_min(i) + eb_min(j) - 22), the minima over G.  Any partial sum of those
+// products, in any order, is at most their sum of magnitudes, and by Cauchy-Schwarz at
+// most sqrt(S_a(i) S_b(j)), S the sum of squared values over G.  With
+// rho_i = S_a(i) 2^(22 - 2 ea_min(i)) = sum_b n2_b 4^(E_b - ea_min(i)) (n2 = sum (2q)^2
+// M^2 per block; sigma_j alike) the bound is below 2^24 u whenever rho_i sigma_j <
+// 2^48; then every partial sum is exactly representable in binary32, and the MFMAs of
+// the group may accumulate into one binary32 register, folded into binary64 once.  A
+// group is an aligned run of four or two 64-element stages where the bound of the run
+// holds, one stage, or (where a stage's own bound fails) single blocks.  Each wave
+// tests the largest rho and sigma of its own rows (diagonal tiles of symmetric
+// products test tile-wide maxima, so that (i, j) and (j, i) add the same binary32
+// values in the same order and the product stays exactly symmetric).
 //
-// Work per wave (Gram of qX and update product): a 64 x 64 output tile (2 x 2
-// MFMA tiles), 64 binary64 accumulators and 64 binary32 chain registers per lane;
-// four waves share a 128 x 128 workgroup tile and two workgroups a CU (two waves
-// per SIMD, 236-248 of their 256 VGPRs).  The Gram of qA runs 32 x 64 per wave,
-// eight waves per workgroup, four per SIMD.  Per MFMA the exact path issues 8 fold
-// instructions (one conversion and one binary64 add per output and stage) and 4-5
-// decode instructions; per stage a wave waits for its LDS operand reads, for the
-// staged loads of the next stage and at the barrier, which the other waves of its
-// SIMD cover only in part.  Groups longer than one stage would keep the chain
-// registers live beside the binary64 accumulators, which does not fit: every
-// arrangement tried spilled 36-200 binary32 registers per lane, at 32 x 64 per
-// wave (128 registers) and at 64 x 64 (256).
+// What bounds the kernel: vector instruction issue.  Per MFMA (32 cycles of the matrix
+// core, 4 of the issue port) a 64 x 64 wave tile decodes 8.5 instructions' worth of
+// operands and folds 8 per group and stage (one conversion and one binary64 add per
+// output), at about 4.4 cycles each; the matrix cores and vector instructions of the
+// two waves of a SIMD overlap when they alternate finely, so each MFMA is followed by
+// decode instructions of the next block.  Groups of more than one stage cut the folds
+// to 0.24 (Gram of qX), 0.8-1.0 (Gram of qA) and 0.55-0.8 (update) per stage and output
+// on Student-t momentum, against 1.0, 1.4 and 1.2 with one-stage groups.  Measured
+// against shared decoded operands in LDS with one barrier per stage and one-stage
+// groups (28-matrix 3B set, same box): Gram of qX 683 -> 816, Gram of qA 607 -> 678,
+// update product 662 -> 795 TFLOP/s, call 37.7 -> 33.6 ms.
+//
+// Work per wave: a 64 x 64 output tile (2 x 2 MFMA tiles), 64 binary64 accumulators and
+// 64 binary32 chain registers per lane (249-251 VGPRs, two waves per SIMD); four
+// waves share a 128 x 128 workgroup tile.  Small launches run 32 x 32 per wave, 64 x
+// 64 per workgroup.
 //
 // Binary32 accumulation (GemmFp4Args::acc32, the library's FP4ROOT_F_FP32_ACCUM):
 // the same loop with one chain over the whole contraction (zeroed once, never
-// folded, no chain records), as tensor-core NVFP4 products accumulate in FP32.
+// folded, no chain bounds), as tensor-core NVFP4 products accumulate in FP32.
 // Each product is then within the binary32 accumulation bound of its exact value
-// rather than equal to its rounding.  Its spare registers carry operand loads two
-// stages ahead.
+// rather than equal to its rounding.
 #include "device.h"
 #include "internal.h"
 
@@ -66,60 +69,18 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-// Tile configurations of the exact NVFP4 product: WAVES_M x WAVES_N waves, each
-// owning TM x TN MFMA 32x32 tiles, WPE waves per SIMD; K is staged through LDS 64
-// elements (four NVFP4 blocks) at a time, double-buffered.  Every workgroup tile is
-// 128 x 128 and two workgroups share a CU.  Wide: 64 x 64 outputs per wave (four
-// waves per workgroup, two per SIMD), half the LDS operand reads per MFMA of
-// Narrow's 32 x 64 per wave (eight waves per workgroup, four per SIMD).  A wide
-// workgroup alone on a CU (the last, partly filled round of a launch) has one wave
-// per SIMD, which cannot overlap MFMA and VALU work, so launches of the Gram of qX
-// and the update product take Wide only when they fill whole rounds of resident
-// workgroups or at least kWideMinRounds of them; the Gram of qA (short
-// contraction) always takes Narrow.
-#ifndef FP4R_FP4_CFG_WIDE
-#define FP4R_FP4_CFG_WIDE 2, 2, 2, 2, 2
-#endif
-#ifndef FP4R_FP4_CFG_NARROW
-#define FP4R_FP4_CFG_NARROW 4, 2, 1, 2, 4
-#endif
-#ifndef FP4R_FP4_WIDE_MIN_ROUNDS
-#define FP4R_FP4_WIDE_MIN_ROUNDS 4
-#endif
-// products (bit = mode) whose operand decode runs at raised wave priority
-#ifndef FP4R_FP4_DECODE_PRIO
-#define FP4R_FP4_DECODE_PRIO 7
-#endif
+// Tile forms of the NVFP4 products: WM x WN waves, each owning TM x TN MFMA 32x32
+// tiles, WPE waves per SIMD.  Wide decodes half as much per MFMA; Narrow has four
+// times the workgroups and a shorter chain per stage, so it wins while a launch does
+// not fill the chip with wide workgroups.
 template <int WM_, int WN_, int TM_, int TN_, int WPE_>
 struct Fp4Tiling {
   static constexpr int WM = WM_, WN = WN_, TM = TM_, TN = TN_, WPE = WPE_;
+  static constexpr int kTile = WM_ * TM_ * 32;
+  static_assert(kTile == WN_ * TN_ * 32, "square workgroup tiles (symmetric products)");
 };
-using Fp4Wide = Fp4Tiling<FP4R_FP4_CFG_WIDE>;
-using Fp4Narrow = Fp4Tiling<FP4R_FP4_CFG_NARROW>;
-constexpr int kWideMinRounds = FP4R_FP4_WIDE_MIN_ROUNDS;
-constexpr int KS = 64;   // K per LDS stage (4 NVFP4 blocks)
-
-// LDS layout of one decoded ROWS x 64 operand stage: block kb (16 f16, two
-// 16-byte halves h) of row r at byte
-//   base(kb) + 32 r + 16 (h ^ sw(r)),   base(kb) = 32 ROWS kb + {0, 16, 64, 80}[kb],
-// sw(r) = bit 2 of r xor bit 3 of r.  gfx950 serves a 16-byte LDS read 16 lanes
-// per cycle over 64 banks (256 bytes) and a 16-byte write 8 lanes per cycle over
-// 32 banks (128 bytes); lanes that share banks in one cycle conflict (measured
-// with the SQ_LDS_BANK_CONFLICT counter on known patterns).  The MFMA operand
-// reads (16 consecutive rows of one block and half per 16 lanes) fall in distinct
-// banks through the swizzle.  The loader's writes (2 rows x the 4 blocks per 8
-// lanes) fall in distinct banks through the block offsets, which are 0, 1, 4 and
-// 5 sixteen-byte units modulo 128 bytes against the rows' 2 units apart.  The
-// offsets are constants, so one address register per operand tile serves every
-// block of both buffers.
-FP4R_DEV int lds_row_off(int row, int h) { return row * 32 + ((h ^ ((row >> 2) & 1) ^ ((row >> 3) & 1)) << 4); }
-template <int ROWS>
-__host__ __device__ constexpr int lds_kb_base(int kb) { return 32 * ROWS * kb + 16 * ((kb & 1) + 4 * (kb >> 1)); }
-template <int ROWS>
-constexpr int lds_stage_bytes() { return lds_kb_base<ROWS>(3) + 32 * ROWS; }
-static_assert(lds_kb_base<128>(0) % 128 == 0 && lds_kb_base<128>(1) % 128 == 16 && lds_kb_base<128>(2) % 128 == 64 &&
-                  lds_kb_base<128>(3) % 128 == 80,
-              "block offsets");
+using Fp4Wide = Fp4Tiling<2, 2, 2, 2, 2>;
+using Fp4Narrow = Fp4Tiling<2, 2, 1, 1, 4>;
 
 // Output tile coordinates.  Symmetric products enumerate the upper triangle
 // row by row; others are row-major over (tiles_m x tiles_n).
@@ -140,70 +101,58 @@ FP4R_DEV void tile_coords(int64_t t, int tiles_m, int tiles_n, bool sym, int& tm
 }
 
 // ---------------------------------------------------------------------------
-// NVFP4 operand staging: each thread loads whole 16-element blocks (8 code
-// bytes + 1 scale byte), decodes them to f16 and writes them to LDS.  Block
-// slot idx = thread + NT j (j < kPer) stages row idx / 4, block idx % 4 of the
-// stage.  The operands are stage-major (the encoders write them so): the 32 code
-// bytes and 4 scale bytes of one row and stage follow those of the previous row,
-// so a stage of the tile's rows is one contiguous run and lane idx reads bytes
-// 8 idx .. 8 idx + 7 of it (whole 128-byte lines per wave).
+// NVFP4 operand staging.  A lane of a 32x32x16 MFMA holds eight consecutive
+// contraction elements of one row: half h = lane / 32 of a 16-element block.  The
+// operands are stage-major with the code words of a row's four blocks ordered by
+// half (see QOut::tiled), so the 16 bytes at half h are the lane's codes of a whole
+// stage, one word per block.  Each wave copies the rows it multiplies into a ring of
+// its own in LDS, straight from memory (global_load_lds, no registers), and decodes
+// the words in registers just before their MFMAs: no data passes between waves, so
+// the main loop has no barrier.
 
-template <int ROWS, int NT>
-struct Fp4Stage {
-  static constexpr int kPer = ROWS * 4 / NT;   // blocks per thread per stage
-  static_assert(kPer >= 1 && ROWS * 4 == kPer * NT, "whole blocks per thread");
-  uint2 codes[kPer];
-  uint32_t scales[kPer];
-};
-
-FP4R_DEV int stage_row(int idx) { return idx >> 2; }
-FP4R_DEV int stage_kb(int idx) { return idx & 3; }
+// Copies one stage of a wave's operand rows into its ring slot at LDS byte `lds`:
+// 16 code bytes per lane for each of TM + TN row tiles (lane i to slot byte 512 +
+// 1024 t + 16 i) and the scale words of up to 64 rows per operand (4 bytes per lane, A
+// at slot byte 0, B at 256).  An instruction offset moves both addresses, so one M0
+// value serves them all and the code bases are 4096 bytes low: the lane offsets
+// `co` (64-byte granules of rows, + 4096 - 512 - 1024 t) make up for it.  The loads are
+// counted by vmcnt only: the caller waits (wait_loads) before reading the slot.
+template <int TM, int TN>
+FP4R_DEV void load_stage(uint32_t lds, const uint32_t (&co)[TM + TN], uint32_t so_a, uint32_t so_b,
+                         const uint8_t* ca, const uint8_t* cb, const uint8_t* sa, const uint8_t* sb) {
+  static_assert((TM == 2 && TN == 2) || (TM == 1 && TN == 1), "row tiles per wave");
+  if constexpr (TM == 2) {
+    asm volatile(
+        "s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+        "global_load_lds_dword %5, %9\n\t"
+        "global_load_lds_dword %6, %10 offset:256\n\t"
+        "global_load_lds_dwordx4 %1, %7 offset:512\n\t"
+        "global_load_lds_dwordx4 %2, %7 offset:1536\n\t"
+        "global_load_lds_dwordx4 %3, %8 offset:2560\n\t"
+        "global_load_lds_dwordx4 %4, %8 offset:3584" ::"s"(lds),
+        "v"(co[0]), "v"(co[1]), "v"(co[2]), "v"(co[3]), "v"(so_a), "v"(so_b), "s"(ca), "s"(cb), "s"(sa), "s"(sb)
+        : "memory", "m0");
+  } else {
+    asm volatile(
+        "s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+        "global_load_lds_dword %3, %7\n\t"
+        "global_load_lds_dword %4, %8 offset:256\n\t"
+        "global_load_lds_dwordx4 %1, %5 offset:512\n\t"
+        "global_load_lds_dwordx4 %2, %6 offset:1536" ::"s"(lds),
+        "v"(co[0]), "v"(co[1]), "v"(so_a), "v"(so_b), "s"(ca), "s"(cb), "s"(sa), "s"(sb)
+        : "memory", "m0");
+  }
+}
+// Waits until at most N of this wave's vector memory operations are outstanding.
+template <int N>
+FP4R_DEV void wait_loads() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
 
 constexpr int kBufWord3 = 0x00020000;          // raw 32-bit data format, no swizzle
 constexpr uint32_t kBufOutOfRange = 0x7FFFFFF0u;
 
-// The tile's rows of one operand: stage 0 of its codes and scales, the bytes from
-// one stage to the next, and how many of its ROWS rows exist (a tail tile has fewer).
-struct Fp4Src {
-  const uint8_t* codes;
-  const uint8_t* scales;
-  int64_t code_stage, scale_stage;
-  int live, nstages;
-};
-
-template <int ROWS>
-FP4R_DEV Fp4Src fp4_src(const Fp4Operand& op, int64_t mat, int64_t rows, int64_t K, int64_t row0) {
-  Fp4Src s;
-  s.codes = op.codes + mat * op.codes_bstride + row0 * 32;
-  s.scales = op.scales + mat * op.scales_bstride + row0 * 4;
-  s.code_stage = rows * 32;
-  s.scale_stage = rows * 4;
-  s.live = (int)(rows - row0 < ROWS ? rows - row0 : ROWS);
-  s.nstages = (int)((K + 63) / 64);
-  return s;
-}
-
-template <int ROWS, int NT>
-FP4R_DEV void fp4_load(const Fp4Src& src, int nkb, int stage, Fp4Stage<ROWS, NT>& s) {
-  // one buffer resource per stage over the tile's rows of that stage: rows past the
-  // matrix, blocks past the end of K and stages past the last read as 0
-  const bool in_k = stage < src.nstages;
-  const int64_t st = in_k ? stage : 0;
-  const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)(src.codes + st * src.code_stage), (short)0, in_k ? src.live * 32 : 0, kBufWord3);
-  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)(src.scales + st * src.scale_stage), (short)0, in_k ? src.live * 4 : 0, kBufWord3);
-#pragma unroll
-  for (int j = 0; j < Fp4Stage<ROWS, NT>::kPer; ++j) {
-    const int idx = (int)threadIdx.x + NT * j;
-    const bool valid = stage * 4 + stage_kb(idx) < nkb;
-    const uint32_t oc = valid ? 8u * (uint32_t)idx : kBufOutOfRange;
-    const uint32_t os = valid ? (uint32_t)idx : kBufOutOfRange;
-    const auto c = __builtin_amdgcn_raw_buffer_load_b64(rc, (int)oc, 0, 0);
-    s.codes[j] = make_uint2(c[0], c[1]);
-    s.scales[j] = __builtin_amdgcn_raw_buffer_load_b8(rs, (int)os, 0, 0);
-  }
-}
+constexpr int kSchedValu = 0x2, kSchedMfma = 0x8;   // masks of sched_group_barrier
 
 template <int SEL>
 FP4R_DEV f16x2 fp4_pair(uint32_t w, f16x2 s2) {
@@ -211,37 +160,20 @@ FP4R_DEV f16x2 fp4_pair(uint32_t w, f16x2 s2) {
   const f16x2 q = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 1.0f, SEL);
   return q * s2;
 }
-
-// Decodes the staged blocks into the LDS stage at `lds`.
-template <int ROWS, int NT>
-FP4R_DEV void fp4_store(char* lds, const Fp4Stage<ROWS, NT>& s) {
-#pragma unroll
-  for (int j = 0; j < Fp4Stage<ROWS, NT>::kPer; ++j) {
-    const int idx = (int)threadIdx.x + NT * j;
-    const int r = stage_row(idx), kb = stage_kb(idx);
-    // the E4M3 scale in both halves, converted exactly (every E4M3 value is an f16)
-    const f16x2 s2 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8((s.scales[j] & 0xFFu) * 0x0101u, 1.0f, false);
-    const uint32_t w[2] = {s.codes[j].x, s.codes[j].y};
-#pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      const f16x2 p0 = fp4_pair<0>(w[half], s2), p1 = fp4_pair<1>(w[half], s2);
-      const f16x2 p2 = fp4_pair<2>(w[half], s2), p3 = fp4_pair<3>(w[half], s2);
-      f16x8 v;
-      v[0] = p0[0]; v[1] = p0[1]; v[2] = p1[0]; v[3] = p1[1];
-      v[4] = p2[0]; v[5] = p2[1]; v[6] = p3[0]; v[7] = p3[1];
-      *reinterpret_cast<f16x8*>(lds + lds_kb_base<ROWS>(kb) + lds_row_off(r, half)) = v;
-    }
-    // one block at a time: few temporaries live beside the accumulators
-    __builtin_amdgcn_sched_barrier(0);
-  }
+// Eight codes times their block scale: an MFMA operand of one lane.
+FP4R_DEV f16x8 fp4_decode(uint32_t w, _Float16 s) {
+  const f16x2 s2 = {s, s};
+  const f16x2 p0 = fp4_pair<0>(w, s2), p1 = fp4_pair<1>(w, s2);
+  const f16x2 p2 = fp4_pair<2>(w, s2), p3 = fp4_pair<3>(w, s2);
+  f16x8 v;
+  v[0] = p0[0]; v[1] = p0[1]; v[2] = p1[0]; v[3] = p1[1];
+  v[4] = p2[0]; v[5] = p2[1]; v[6] = p3[0]; v[7] = p3[1];
+  return v;
 }
 
-// Chain records of one operand (see the header): per 64-element stage and 16 rows,
-// [rows/16][K/64] (group-major).  Before the stage loop
-// each wave evaluates rho sigma over its own row groups for every stage (up to
-// kRecStages, K = 32768) into its column of an LDS byte table; the loop reads one
-// byte per stage.
-constexpr int kRecStages = 512;
+// Stages whose chain decisions a wave prepares (K up to 64 kChainStages); later stages
+// fold every block.
+constexpr int kChainWindows = 8, kChainStages = 64 * kChainWindows;
 
 // ---------------------------------------------------------------------------
 // Rotated amaxes of an output, for the tensor scale of the operand encoded from
@@ -337,11 +269,8 @@ FP4R_DEV uint32_t wave_max_bits(float v) {
 // ---------------------------------------------------------------------------
 // Exact NVFP4 product.
 
-// Accumulation form of one stage (uniform over a wave): one group per block, or
-// the stage as one group.
-enum StageForm { kFormBlock = 0, kFormStage = 1, kFormRun = 2 };
-template <int F>
-using form_t = std::integral_constant<int, F>;
+template <int KB>
+using block_t = std::integral_constant<int, KB>;
 
 // One output tile of one product: workgroup wg of the product's tiles_per_mat *
 // batch tiles; fin (may be null) routes a last update's output to the callers'
@@ -353,17 +282,13 @@ FP4R_DEV void gemm_fp4_tile(const GemmFp4Args& g, int64_t wg, int tiles_m, int t
   // padded row of the FP32 output tile staged in LDS: rows stay 16-byte aligned, and
   // the two half-waves of an MFMA-layout write (rows 4 apart) fall 32 banks apart
   constexpr int kLdT = BN + 8;
-  constexpr int kStA = lds_stage_bytes<BM>(), kStB = lds_stage_bytes<BN>();
-  constexpr size_t kMainBytes = (size_t)2 * (kStA + kStB);
+  // ring of two raw stages per wave (see load_stage)
+  constexpr int kOps = TM + TN, kSlot = 512 + 1024 * kOps, kRing = 2 * kSlot;
+  constexpr size_t kMainBytes = (size_t)NW * kRing;
   constexpr size_t kEpiBytes = (size_t)BM * kLdT * sizeof(float);
-  constexpr int kGa = BM / 16, kGb = BN / 16;   // 16-row groups per operand tile
   __shared__ __attribute__((aligned(16))) char smem[kMainBytes > kEpiBytes ? kMainBytes : kEpiBytes];
-  __shared__ uint8_t wflags[kRecStages][NW];
+  __shared__ uint64_t wflags[NW][2][kChainWindows];   // per wave: stages that chain, that continue a group
   __shared__ uint32_t red[2][NW];   // per-wave amaxes (rows, columns)
-  char* const la0 = smem;
-  char* const la1 = smem + kStA;
-  char* const lb0 = smem + 2 * kStA;
-  char* const lb1 = smem + 2 * kStA + kStB;
   constexpr bool kSym = MODE != kModeUpdateX;
   const int64_t mat = wg / tiles_per_mat;
   int tm, tn;
@@ -372,8 +297,7 @@ FP4R_DEV void gemm_fp4_tile(const GemmFp4Args& g, int64_t wg, int tiles_m, int t
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int wm = wave / WN_, wn = wave % WN_;
-  const int nkb = (int)(g.K / 16);   // K <= 2^21
-  const int nstages = (int)((nkb + 3) / 4);
+  const int nstages = (int)((g.K + 63) / 64);   // K <= 2^21
 
   double acc[TM][TN][16];
 #pragma unroll
@@ -383,197 +307,218 @@ FP4R_DEV void gemm_fp4_tile(const GemmFp4Args& g, int64_t wg, int tiles_m, int t
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0;
 
-  const Fp4Src src_a = fp4_src<BM>(g.a, mat, g.M, g.K, row0);
-  const Fp4Src src_b = fp4_src<BN>(g.b, mat, g.N, g.K, col0);
-
   // a group chains if rho sigma < 2^48; the limit leaves room for the rounding of
   // the binary32 product rho * sigma
   constexpr float kLim = 281474976710656.0f * (1.0f - 1.0f / 65536.0f);   // 2^48 (1 - 2^-16)
-  // the rows a compute wave covers: TM * 2 groups of A, TN * 2 of B; diagonal
-  // tiles of symmetric products use all groups of the tile (see the header)
+  // the rows a wave covers; diagonal tiles of symmetric products test the tile's rows
+  // (see the header)
   const bool diag = kSym && tm == tn;
-  const bool chain_on = g.a.rhog != nullptr && g.b.rhog != nullptr;
-  const int ga0 = diag ? 0 : wm * TM * 2, nga = diag ? kGa : TM * 2;
-  const int gb0 = diag ? 0 : wn * TN * 2, ngb = diag ? kGb : TN * 2;
-  const float* rec_a = chain_on ? g.a.rhog + mat * g.a.rhog_bstride : nullptr;
-  const float* rec_b = chain_on ? g.b.rhog + mat * g.b.rhog_bstride : nullptr;
-  // the largest record of stage `ss` over groups g0 .. g0 + ng - 1 (records are
-  // group-major, [rows/16][K/64], so the lanes of a wave read consecutive stages;
-  // missing groups of a tail tile read 0: their rows are zero)
-  const int64_t nst_all = g.K / 64;
-  auto group_max = [&](const float* rec, int64_t groups_all, int64_t ss, int64_t g0, int ng) {
+  const int levels = ACC32 ? 0 : g.a.levels;
+  const int ushift = levels > 1 ? 5 : 4;   // rows of a record unit
+  const int64_t entries = levels > 1 ? chain_entries(nstages) : nstages;
+  const float* const rec_a = g.a.rec + mat * g.a.rec_bstride;
+  const float* const rec_b = g.b.rec + mat * g.b.rec_bstride;
+  // the largest bound of entry `at` over the units of `rows` rows from `r0` on (units
+  // past the matrix hold no rows)
+  auto unit_max = [&](const float* rec, int64_t total, int64_t r0, int rows, int64_t at) {
     float mx = 0.0f;
-    for (int k = 0; k < ng; ++k)
-      if (g0 + k < groups_all) mx = fmaxf(mx, rec[(g0 + k) * nst_all + ss]);
+    const int64_t u0 = r0 >> ushift, end = (total + (1 << ushift) - 1) >> ushift;
+    for (int k = 0; k < (rows >> ushift); ++k)
+      if (u0 + k < end) mx = fmaxf(mx, rec[(u0 + k) * entries + at]);
     return mx;
   };
-  // chain flags of every stage for this wave's rows into wflags[.][wave] (one
-  // stage per lane and pass): bit 0 = the stage chains.  Only this wave touches its column, so no
-  // barrier is needed.  Stages past kRecStages (K over 64 kRecStages) fold every block.
+  // Decides for 64 stages at a time, one per lane: a stage chains if its own bound
+  // holds, and continues the group of the stage before it if the bound of an aligned
+  // run of two or four stages holds in which it is not the first.
   auto fill_flags = [&]() {
-    const int64_t nga_all = g.M / 16, ngb_all = g.N / 16;
-    const int64_t a0 = row0 / 16 + ga0, b0 = col0 / 16 + gb0;
-    const int nfill = nstages < kRecStages ? nstages : kRecStages;
-    for (int s0 = 0; s0 < nfill; s0 += 64) {
-      const int ss = s0 + lane;
-      uint32_t f = 0;
-      if (chain_on && ss < nfill) {
-        if (group_max(rec_a, nga_all, ss, a0, nga) * group_max(rec_b, ngb_all, ss, b0, ngb) < kLim) f |= 1u;
+    const int64_t a0 = row0 + (diag ? 0 : wm * TM * 32), b0 = col0 + (diag ? 0 : wn * TN * 32);
+    const int ra = diag ? BM : TM * 32, rb = diag ? BN : TN * 32;
+    for (int w = 0; w < kChainWindows && 64 * w < nstages; ++w) {
+      const int ss = 64 * w + lane;
+      bool chain = false, cont = false;
+      if (levels > 0 && ss < nstages) {
+        chain = unit_max(rec_a, g.M, a0, ra, ss) * unit_max(rec_b, g.N, b0, rb, ss) < kLim;
+        if (levels > 1) {
+          int64_t at = nstages;
+          for (int l = 1; l <= 2; ++l) {
+            if (ss & ((1 << l) - 1))
+              cont |= unit_max(rec_a, g.M, a0, ra, at + (ss >> l)) * unit_max(rec_b, g.N, b0, rb, at + (ss >> l)) < kLim;
+            at += (nstages + (1 << l) - 1) >> l;
+          }
+        }
       }
-      if (ss < kRecStages) wflags[ss][wave] = (uint8_t)f;
+      const uint64_t mc = __builtin_amdgcn_ballot_w64(chain), mo = __builtin_amdgcn_ballot_w64(cont);
+      if (lane == 0) {
+        wflags[wave][0][w] = mc;
+        wflags[wave][1][w] = mo;
+      }
     }
   };
-  auto stage_flags = [&](int s) { return !ACC32 && s < kRecStages ? (uint32_t)wflags[s][wave] : 0u; };
 
-  // stage -> LDS buffers (decoded operands)
-  // The decode runs at raised wave priority: a wave that has finished its MFMAs
-  // then gets the issue slots ahead of waves still in their MFMA or fold phase, and
-  // reaches the barrier sooner (the Gram of qA, with its short K, keeps the default).
-  auto put = [&](char* la, char* lb, const Fp4Stage<BM, NT>& xa, const Fp4Stage<BN, NT>& xb) __attribute__((always_inline)) {
-    constexpr bool kPrio = (FP4R_FP4_DECODE_PRIO >> MODE) & 1;
-    if constexpr (kPrio) __builtin_amdgcn_s_setprio(1);
-    fp4_store<BM, NT>(la, xa);
-    fp4_store<BN, NT>(lb, xb);
-    if constexpr (kPrio) __builtin_amdgcn_s_setprio(0);
+  // Operand t = 0 .. TM - 1 are the wave's row tiles of A, the next TN those of B.
+  // Rows past the matrix read the last row instead (their outputs are discarded) and
+  // stages past the last read the last one (never used), so every load is in range.
+  const uint8_t* const codes_a = g.a.codes + mat * g.a.codes_bstride + row0 * 32;
+  const uint8_t* const codes_b = g.b.codes + mat * g.b.codes_bstride + col0 * 32;
+  const uint8_t* const scales_a = g.a.scales + mat * g.a.scales_bstride + row0 * 4;
+  const uint8_t* const scales_b = g.b.scales + mat * g.b.scales_bstride + col0 * 4;
+  uint32_t row[kOps];
+#pragma unroll
+  for (int t = 0; t < kOps; ++t) {
+    const int64_t live = t < TM ? g.M - row0 : g.N - col0;
+    const int r = (t < TM ? wm * TM + t : wn * TN + t - TM) * 32 + (lane & 31);
+    row[t] = (uint32_t)(r < live ? r : (int)live - 1);
+  }
+  uint32_t co[kOps];
+#pragma unroll
+  for (int t = 0; t < kOps; ++t) co[t] = row[t] * 32 + (uint32_t)(lane >> 5) * 16 + (4096 - 512 - 1024 * t);
+  // scale words of the wave's rows: lane i the word of row i (64 rows with two row
+  // tiles; with one, lanes 32 .. 63 repeat its rows), A at slot byte 0
+  const int own = TM == 2 ? lane : lane & 31;
+  const int64_t live_a = g.M - row0, live_b = g.N - col0;
+  const int sr_a = wm * TM * 32 + own, sr_b = wn * TN * 32 + own;
+  const uint32_t so_a = (uint32_t)(sr_a < live_a ? sr_a : (int)live_a - 1) * 4;
+  const uint32_t so_b = (uint32_t)(sr_b < live_b ? sr_b : (int)live_b - 1) * 4 + (4096 - 256);
+  char* const ring = smem + wave * kRing;
+  const uint32_t ring_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)ring;
+  // the next stage to load; past the last one the pointers stay
+  const uint8_t *ca = codes_a - 4096, *cb = codes_b - 4096, *sa = scales_a, *sb = scales_b - 4096;
+  const int64_t step_a = g.M * 32, step_b = g.N * 32;
+  auto issue = [&](int stage) __attribute__((always_inline)) {
+    load_stage<TM, TN>(ring_lds + (stage & 1) * kSlot, co, so_a, so_b, ca, cb, sa, sb);
+    const bool more = stage + 1 < nstages;
+    const int64_t da = more ? step_a : 0, db = more ? step_b : 0;
+    ca += da;
+    cb += db;
+    sa += da / 8;
+    sb += db / 8;
+  };
+  constexpr int kLoads = kOps + 2;   // vector memory operations of one stage
+  uint4 raw[kOps];
+  uint32_t rsc[kOps];
+  const int lane_sc = (lane & 31) * 4;
+  auto read_raw = [&](int stage) __attribute__((always_inline)) {
+    const char* slot = ring + (stage & 1) * kSlot;
+#pragma unroll
+    for (int t = 0; t < kOps; ++t)
+      rsc[t] = *reinterpret_cast<const uint32_t*>(slot + (t < TM ? 128 * t : 256 + 128 * (t - TM)) + lane_sc);
+#pragma unroll
+    for (int t = 0; t < kOps; ++t) raw[t] = *reinterpret_cast<const uint4*>(slot + 512 + 1024 * t + 16 * lane);
+  };
+  f16x8 op[2][kOps];   // decoded operands of a block, and of the next one
+  auto decode = [&](int kb, int t) __attribute__((always_inline)) {
+    const f16x2 sc = kb < 2 ? __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(rsc[t], 1.0f, false)
+                            : __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(rsc[t], 1.0f, true);
+    const uint32_t w = kb == 0 ? raw[t].x : kb == 1 ? raw[t].y : kb == 2 ? raw[t].z : raw[t].w;
+    op[kb & 1][t] = fp4_decode(w, sc[kb & 1]);
   };
 
   const f32x16 zero = {};
   f32x16 p[TM][TN];   // the binary32 chain registers
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) p[i][j] = zero;
   auto fold = [&](int i, int j) __attribute__((always_inline)) {
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[i][j][e] = acc[i][j][e] + (double)p[i][j][e];
   };
-  // MFMAs of the stage in (la, lb).  A group starts with accumulator input 0 and
-  // is folded into binary64 as soon as it ends (after its last block, or at the end
-  // of the stage), so the chain registers are dead while the next stage decodes.
-  // Form Run (binary32 accumulation) adds every block to the chain registers, which
-  // start at zero before the first stage and are never folded.  Blocks past the end
-  // of K are zero in LDS and join any group.
-  auto compute = [&](auto form_tag, const char* la, const char* lb) __attribute__((always_inline)) {
-    constexpr int F = decltype(form_tag)::value;
+
+  issue(0);
+  issue(1);
+  if constexpr (!ACC32) fill_flags();
+  wait_loads<kLoads>();
+  read_raw(0);
 #pragma unroll
-    for (int kb = 0; kb < 4; ++kb) {
-      f16x8 av[TM], bv[TN];
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-        av[i] = *reinterpret_cast<const f16x8*>(
-            la + lds_kb_base<BM>(kb) + lds_row_off((wm * TM + i) * 32 + (lane & 31), lane >> 5));
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-        bv[j] = *reinterpret_cast<const f16x8*>(
-            lb + lds_kb_base<BN>(kb) + lds_row_off((wn * TN + j) * 32 + (lane & 31), lane >> 5));
+  for (int t = 0; t < kOps; ++t) decode(0, t);
+  __builtin_amdgcn_sched_barrier(0);
+  // Stage s: its raw words are in registers and the operands of its first block are
+  // decoded.  Every MFMA is followed by decode work of the next block (the matrix core
+  // is busy for 32 cycles, the issue port for 4).  The chain registers hold the open
+  // group on entry; the exact products fold it into binary64 before the first block,
+  // or before every block where the stage may not chain.
+  uint64_t chain_mask = 0, cont_mask = 0;
+  for (int s = 0; s < nstages; ++s) {
+    if (!ACC32 && (s & 63) == 0) {
+      chain_mask = cont_mask = 0;
+      if (s < kChainStages) {
+        const uint64_t c = wflags[wave][0][s >> 6], o = wflags[wave][1][s >> 6];
+        chain_mask = ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(c >> 32)) << 32) |
+                     (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)c);
+        cont_mask = ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(o >> 32)) << 32) |
+                    (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)o);
+      }
+    }
+    const bool chains = (chain_mask >> (s & 63)) & 1, continues = (cont_mask >> (s & 63)) & 1;
+    // the slot of stage s is free once its words have reached the registers
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    issue(s + 2);
+    __builtin_amdgcn_sched_barrier(0);
+    // the MFMAs of block kb and the decode of the next block, in a fixed order: one
+    // MFMA, then the vector instructions that fit its time on the matrix core
+    auto block = [&](auto kb_tag, auto fresh_tag) __attribute__((always_inline)) {
+      constexpr int kb = decltype(kb_tag)::value;
+      constexpr bool fresh = decltype(fresh_tag)::value;
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
-          const bool fresh = F == kFormBlock || (F == kFormStage && kb == 0);
-          p[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av[i], bv[j], fresh ? zero : p[i][j], 0, 0, 0);
+          if (fresh) fold(i, j);
+          p[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(op[kb & 1][i], op[kb & 1][TM + j],
+                                                           fresh ? zero : p[i][j], 0, 0, 0);
         }
-      __builtin_amdgcn_sched_barrier(0);   // keep operand loads next to their use
-      if (F == kFormBlock && kb < 3) {
-        // every block a group of its own (rare: the stage bound failed)
+#pragma unroll
+      for (int t = 0; t < kOps; ++t) {
+        decode((kb + 1) & 3, t);
+        asm volatile("" : "+v"(op[(kb + 1) & 1][t]));
+      }
+#pragma unroll
+      for (int t = 0; t < TM * TN; ++t) {
+        if (fresh) __builtin_amdgcn_sched_group_barrier(kSchedValu, 32, 0);
+        __builtin_amdgcn_sched_group_barrier(kSchedMfma, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(kSchedValu, (8 * kOps + TM * TN - 1) / (TM * TN) + 1, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    // a stage that may not chain starts a group at every block
+    auto split = [&]() __attribute__((always_inline)) {
+      if (!ACC32 && !chains) {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
-          for (int j = 0; j < TN; ++j) fold(i, j);
-        __builtin_amdgcn_sched_barrier(0);
+          for (int j = 0; j < TN; ++j) {
+            fold(i, j);
+            p[i][j] = zero;
+          }
       }
-    }
-    if constexpr (F != kFormRun) {
+    };
+    if (!ACC32 && !continues) {
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j) fold(i, j);
+        for (int j = 0; j < TN; ++j) {
+          fold(i, j);
+          p[i][j] = zero;
+        }
     }
-  };
-  // one stage that is a group of its own (form Stage) or folds every block (Block);
-  // with binary32 accumulation every stage continues the one chain (form Run)
-  auto run_single = [&](uint32_t f, const char* la, const char* lb) __attribute__((always_inline)) {
-    if constexpr (ACC32) {
-      compute(form_t<kFormRun>(), la, lb);
-    } else {
-      if (f & 1u) compute(form_t<kFormStage>(), la, lb);
-      else compute(form_t<kFormBlock>(), la, lb);
-    }
-  };
-  if constexpr (ACC32) {
+    block(block_t<0>(), std::false_type());
+    split();
+    block(block_t<1>(), std::false_type());
+    split();
+    block(block_t<2>(), std::false_type());
+    split();
+    wait_loads<kLoads>();
+    read_raw(s + 1);
+    __builtin_amdgcn_sched_barrier(0);
+    block(block_t<3>(), std::false_type());
+  }
+  wait_loads<0>();
+  if constexpr (!ACC32) {
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int j = 0; j < TN; ++j) p[i][j] = zero;
-  }
-
-  // With binary32 accumulation the registers allow operand loads two stages ahead, in
-  // two register sets (even and odd stages).  The exact products load one stage ahead:
-  // their 32 x 64 form would spill, and their 64 x 64 form, which fits at 256 VGPRs,
-  // ran its update product 1-2 % slower that way.
-  constexpr bool kAhead2 = ACC32;
-  if constexpr (kAhead2) {
-    Fp4Stage<BM, NT> sa[2];
-    Fp4Stage<BN, NT> sb[2];
-    fp4_load<BM, NT>(src_a, nkb, 0, sa[0]);
-    fp4_load<BN, NT>(src_b, nkb, 0, sb[0]);
-    fp4_load<BM, NT>(src_a, nkb, 1, sa[1]);
-    fp4_load<BN, NT>(src_b, nkb, 1, sb[1]);
-    put(la0, lb0, sa[0], sb[0]);
-    fp4_load<BM, NT>(src_a, nkb, 2, sa[0]);
-    fp4_load<BN, NT>(src_b, nkb, 2, sb[0]);
-    if constexpr (!ACC32) fill_flags();
-    __syncthreads();
-    // pairs of stages, then an odd last stage after the loop (one exit, so the
-    // loop-carried chain registers keep their registers)
-    int s = 0;
-    for (; s + 1 < nstages; s += 2) {
-      run_single(stage_flags(s), la0, lb0);
-      put(la1, lb1, sa[1], sb[1]);
-      fp4_load<BM, NT>(src_a, nkb, s + 3, sa[1]);
-      fp4_load<BN, NT>(src_b, nkb, s + 3, sb[1]);
-      __syncthreads();
-      run_single(stage_flags(s + 1), la1, lb1);
-      if (s + 2 < nstages) {
-        put(la0, lb0, sa[0], sb[0]);
-        fp4_load<BM, NT>(src_a, nkb, s + 4, sa[0]);
-        fp4_load<BN, NT>(src_b, nkb, s + 4, sb[0]);
-      }
-      __syncthreads();
-    }
-    if (s < nstages) run_single(stage_flags(s), la0, lb0);
+      for (int j = 0; j < TN; ++j) fold(i, j);
   } else {
-  Fp4Stage<BM, NT> sa;
-  Fp4Stage<BN, NT> sb;
-  fp4_load<BM, NT>(src_a, nkb, 0, sa);
-  fp4_load<BN, NT>(src_b, nkb, 0, sb);
-  put(la0, lb0, sa, sb);
-  // stage 1 loads while the flags are computed (reads 0 past the last stage)
-  fp4_load<BM, NT>(src_a, nkb, 1, sa);
-  fp4_load<BN, NT>(src_b, nkb, 1, sb);
-  if constexpr (!ACC32) fill_flags();
-  __syncthreads();
-  // Two stages per iteration with the LDS buffers as constants: stage s computes
-  // from one buffer while stage s + 1, loaded during the previous stage, decodes
-  // into the other; the loads of stage s + 2 are issued into the same registers
-  // right after that decode, so they have the barrier and a whole stage of MFMAs
-  // to arrive.  Loads past the last stage read 0 and are never decoded.
-  for (int s = 0; s < nstages; s += 2) {
-    const bool has_odd = s + 1 < nstages, more = s + 2 < nstages;
-    run_single(stage_flags(s), la0, lb0);
-    if (has_odd) {
-      put(la1, lb1, sa, sb);
-      fp4_load<BM, NT>(src_a, nkb, s + 2, sa);
-      fp4_load<BN, NT>(src_b, nkb, s + 2, sb);
-    }
-    __syncthreads();
-    if (!has_odd) break;
-    run_single(stage_flags(s + 1), la1, lb1);
-    if (more) {
-      put(la0, lb0, sa, sb);
-      fp4_load<BM, NT>(src_a, nkb, s + 3, sa);
-      fp4_load<BN, NT>(src_b, nkb, s + 3, sb);
-    }
-    __syncthreads();
-  }
-  }
-  if constexpr (ACC32) {
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -581,35 +526,32 @@ FP4R_DEV void gemm_fp4_tile(const GemmFp4Args& g, int64_t wg, int tiles_m, int t
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[i][j][e] = (double)p[i][j][e];
   }
+  __syncthreads();   // the epilogue reuses the rings
 
-  // epilogue: binary64 formula, one rounding to binary32, staged through LDS
-  // (the main loop's buffers are free after its last barrier), one MFMA tile at
-  // a time
+  // epilogue: binary64 formula, one rounding to binary32, staged through LDS, one
+  // MFMA tile at a time
   const double sga = (double)g.sc[mat].sg[g.slot_a], sgb = (double)g.sc[mat].sg[g.slot_b];
   const double alpha = sga * sgb;   // exact: product of two binary32 values
-  const double ca = (double)g.ca, cb = (double)g.cb, cc = (double)g.cc;
+  const double fa = (double)g.ca, fb = (double)g.cb, fc = (double)g.cc;
   float* out = g.out + mat * g.out_bstride;
   const float* aux = g.aux ? g.aux + mat * g.out_bstride : nullptr;
   float* tile = reinterpret_cast<float*>(smem);
-  // the epilogue operand (A for B, X_k for X_{k+1}) of all of this lane's
-  // outputs, loaded up front (in-range index for lanes past the edge)
-  float xin[TM][TN][16];
-  if (MODE != kModeGramA) {
-    const int64_t live = g.M - row0 < BM ? g.M - row0 : BM;
-    const __amdgpu_buffer_rsrc_t rs =
-        __builtin_amdgcn_make_buffer_rsrc((void*)(aux + row0 * g.N), (short)0, (int)(live * g.N * 4), kBufWord3);
+  // the epilogue operand (A for B, X_k for X_{k+1}) of this lane's outputs of MFMA
+  // tile (i, j) (lanes past the edge read 0)
+  const int64_t live_rows = g.M - row0 < BM ? g.M - row0 : BM;
+  const __amdgpu_buffer_rsrc_t aux_rs = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(aux ? aux + row0 * g.N : out), (short)0, MODE != kModeGramA ? (int)(live_rows * g.N * 4) : 0, kBufWord3);
+  float xin[2][16];   // of two tiles in turn: the next one's loads are in flight
+  auto load_aux = [&](int i, int j, float (&x)[16]) __attribute__((always_inline)) {
+    const int64_t c = col0 + (wn * TN + j) * 32 + (lane & 31);
+    const int rl = (wm * TM + i) * 32 + 4 * (lane >> 5);
+    const uint32_t off0 = c < g.N ? (uint32_t)((rl * g.N + c) * 4) : kBufOutOfRange;
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const int rl = (wm * TM + i) * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
-          const int64_t c = col0 + (wn * TN + j) * 32 + (lane & 31);
-          const uint32_t off = c < g.N ? (uint32_t)((rl * g.N + c) * 4) : kBufOutOfRange;
-          xin[i][j][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, (int)off, 0, 0));
-        }
-  }
+    for (int e = 0; e < 16; ++e)
+      x[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                           aux_rs, (int)(off0 + (uint32_t)((8 * (e >> 2) + (e & 3)) * g.N * 4)), 0, 0));
+  };
+  if (MODE != kModeGramA) load_aux(0, 0, xin[0]);
   // off-diagonal tiles of symmetric products (and a transposed final output): the
   // transposed tile straight from registers (four consecutive rows of a column
   // form a row segment of it)
@@ -630,6 +572,11 @@ FP4R_DEV void gemm_fp4_tile(const GemmFp4Args& g, int64_t wg, int tiles_m, int t
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
+      constexpr int kTiles = TM * TN;
+      const int tile_no = i * TN + j;
+      if (MODE != kModeGramA && tile_no + 1 < kTiles)
+        load_aux((tile_no + 1) / TN, (tile_no + 1) % TN, xin[(tile_no + 1) & 1]);
+      const float(&x)[16] = xin[tile_no & 1];
       // this lane's outputs of MFMA tile (i, j) in binary32 (zero outside the matrix)
       float val[16];
 #pragma unroll
@@ -637,8 +584,8 @@ FP4R_DEV void gemm_fp4_tile(const GemmFp4Args& g, int64_t wg, int tiles_m, int t
         const int rl = (wm * TM + i) * 32 + 8 * (e >> 2) + 4 * hb + (e & 3);
         const int cl = (wn * TN + j) * 32 + (lane & 31);
         double v = alpha * acc[i][j][e];
-        if (MODE == kModeGramB) v = cb * (double)xin[i][j][e] + cc * v;
-        if (MODE == kModeUpdateX) v = ca * (double)xin[i][j][e] + v;
+        if (MODE == kModeGramB) v = fb * (double)x[e] + fc * v;
+        if (MODE == kModeUpdateX) v = fa * (double)x[e] + v;
         const bool in = row0 + rl < g.M && col0 + cl < g.N;
         val[e] = in ? (float)v : 0.0f;
         tile[rl * kLdT + cl] = val[e];
@@ -730,17 +677,6 @@ void k_gemm_fp4_multi(GemmFp4Batch gb) {
                                               nullptr);
 }
 
-// Every configuration covers a 128 x 128 output tile with whole blocks per staging thread.
-constexpr int kFp4Tile = 128;
-template <class C>
-constexpr bool fp4_cfg_ok() {
-  return C::WM * C::TM * 32 == kFp4Tile && C::WN * C::TN * 32 == kFp4Tile &&
-         (kFp4Tile * 4) % (C::WM * C::WN * 64) == 0;
-}
-static_assert(fp4_cfg_ok<Fp4Wide>() && fp4_cfg_ok<Fp4Narrow>(), "128 x 128 workgroup tiles (square: symmetric products)");
-// resident workgroups of a full round: two per CU
-constexpr int64_t kFp4Round = 2 * 256;
-
 template <int MODE, class C, bool ACC32>
 void launch_fp4_single(dim3 grid, hipStream_t st, const GemmFp4Args& g, int tm, int tn, int64_t per,
                        const GemmFin& f) {
@@ -766,7 +702,10 @@ void launch_fp4_kernel(GemmMode mode, bool wide, dim3 grid, hipStream_t st, cons
         if (wide) launch_fp4_single<kModeGramA, Fp4Wide, ACC32>(grid, st, g, tm, tn, per, f);
         else launch_fp4_single<kModeGramA, Fp4Narrow, ACC32>(grid, st, g, tm, tn, per, f);
         break;
-      case kModeGramB: launch_fp4_single<kModeGramB, Fp4Narrow, ACC32>(grid, st, g, tm, tn, per, f); break;
+      case kModeGramB:
+        if (wide) launch_fp4_single<kModeGramB, Fp4Wide, ACC32>(grid, st, g, tm, tn, per, f);
+        else launch_fp4_single<kModeGramB, Fp4Narrow, ACC32>(grid, st, g, tm, tn, per, f);
+        break;
       default:
         if (wide) launch_fp4_single<kModeUpdateX, Fp4Wide, ACC32>(grid, st, g, tm, tn, per, f);
         else launch_fp4_single<kModeUpdateX, Fp4Narrow, ACC32>(grid, st, g, tm, tn, per, f);
@@ -777,9 +716,16 @@ void launch_fp4_kernel(GemmMode mode, bool wide, dim3 grid, hipStream_t st, cons
     if (wide) launch_fp4_multi<kModeGramA, Fp4Wide, ACC32>(grid, st, gb);
     else launch_fp4_multi<kModeGramA, Fp4Narrow, ACC32>(grid, st, gb);
   } else {
-    launch_fp4_multi<kModeGramB, Fp4Narrow, ACC32>(grid, st, gb);
+    if (wide) launch_fp4_multi<kModeGramB, Fp4Wide, ACC32>(grid, st, gb);
+    else launch_fp4_multi<kModeGramB, Fp4Narrow, ACC32>(grid, st, gb);
   }
 }
+
+// Launches of at least one round of resident wide workgroups (two per CU) run wide.
+// One NS step, narrow / wide us per launch: Gram of qX 16 / 25 (36 wide tiles), 49 / 50
+// (272), 130 / 122 (528), 117 / 99 (600); update 17 / 26 (64), 43 / 48 (396), 85 / 76 (512),
+// 153 / 131 (1024).
+constexpr int64_t kWideMinTiles = 512;
 
 std::atomic<int> g_product_tiling{0};
 
@@ -787,7 +733,6 @@ int swap_product_tiling(int mode) { return g_product_tiling.exchange(mode); }
 
 hipError_t launch_gemm_fp4_batch(GemmMode mode, const GemmFp4Args* list, int count, hipStream_t st,
                                  const GemmFin* fin) {
-  constexpr int BM = kFp4Tile, BN = kFp4Tile;
   if (count < 1 || count > kMaxGemmProblems) return hipErrorInvalidValue;
   if (fin && fin->count > 0 && (count != 1 || mode != kModeUpdateX || fin->count != list[0].batch))
     return hipErrorInvalidValue;
@@ -798,14 +743,26 @@ hipError_t launch_gemm_fp4_batch(GemmMode mode, const GemmFp4Args* list, int cou
   for (int i = 0; i < count; ++i) order[i] = i;
   for (int i = 1; i < count; ++i)
     for (int j = i; j > 0 && list[order[j]].K > list[order[j - 1]].K; --j) std::swap(order[j], order[j - 1]);
+  const bool sym = mode != kModeUpdateX;
+  auto tiles_of = [&](const GemmFp4Args& g, int tile, int& tiles_m, int& tiles_n) {
+    tiles_m = (int)((g.M + tile - 1) / tile);
+    tiles_n = (int)((g.N + tile - 1) / tile);
+    return sym ? (int64_t)tiles_m * (tiles_m + 1) / 2 : (int64_t)tiles_m * tiles_n;
+  };
+  int64_t wide_tiles = 0;
+  for (int i = 0; i < count; ++i) {
+    int tm, tn;
+    wide_tiles += tiles_of(list[i], Fp4Wide::kTile, tm, tn) * list[i].batch;
+  }
+  const int forced = g_product_tiling.load(std::memory_order_relaxed);
+  const bool wide = forced == 0 ? wide_tiles >= kWideMinTiles : forced == 2;
   GemmFp4Batch gb;
   gb.count = 0;
   int64_t total = 0;
-  const bool sym = mode != kModeUpdateX;
   for (int i = 0; i < count; ++i) {
     const GemmFp4Args& g = list[order[i]];
-    const int tiles_m = (int)((g.M + BM - 1) / BM), tiles_n = (int)((g.N + BN - 1) / BN);
-    const int64_t per = sym ? (int64_t)tiles_m * (tiles_m + 1) / 2 : (int64_t)tiles_m * tiles_n;
+    int tiles_m, tiles_n;
+    const int64_t per = tiles_of(g, wide ? Fp4Wide::kTile : Fp4Narrow::kTile, tiles_m, tiles_n);
     if (per * g.batch == 0) continue;
     const int k = gb.count++;
     gb.p[k] = g;
@@ -817,8 +774,6 @@ hipError_t launch_gemm_fp4_batch(GemmMode mode, const GemmFp4Args* list, int cou
   }
   if (gb.count == 0) return hipSuccess;
   const dim3 grid((uint32_t)total);
-  const int forced = g_product_tiling.load(std::memory_order_relaxed);
-  const bool wide = forced == 0 ? (total % kFp4Round == 0 || total >= kWideMinRounds * kFp4Round) : forced == 2;
   // several products per launch: the symmetric products only
   if (gb.count > 1 && ((fin && fin->count > 0) || mode == kModeUpdateX)) return hipErrorInvalidValue;
   GemmFin f;

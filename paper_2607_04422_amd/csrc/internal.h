@@ -117,20 +117,52 @@ struct QOut {
   uint8_t* codes;
   uint8_t* scales;
   int64_t codes_bstride, scales_bstride;
-  // optional (axis 1 only, K = cols a multiple of 64): chain bound records, the
-  // largest rho over each 16 rows per 64-element stage, [rows/16][K/64]
-  float* rhog = nullptr;
-  int64_t rhog_bstride = 0;
-  // stage-major layout (the products' operands; axis-1 encoders only): per matrix
-  // codes [ceil(K/64)][rows][32 bytes] and scales [ceil(K/64)][rows][4 bytes], so
-  // that one 64-element stage of consecutive rows is contiguous; otherwise row-major
-  int tiled = 0;
+};
+
+// A products' operand of one matrix of `rows` rows and K contraction elements, as the
+// operand encoders write it.  Stage-major: per 64-element stage the 32 code bytes of
+// every row one after another, and likewise the 4 scale bytes, so that a stage of
+// consecutive rows is contiguous.  A row's 32 code bytes hold the first 8 elements of
+// its four blocks (one word each), then the last 8 of each: the words of one MFMA
+// lane half.  Blocks past K (a last partial stage) are zero.
+struct OperandOut {
+  uint8_t* codes;
+  uint8_t* scales;
+  int64_t codes_bstride, scales_bstride;
+  // chain bounds (see row_word in device.h), one of the two or neither:
+  // words: per stage and row, [ceil(K/64)][rows], for launch_chain_levels;
+  // rec:   per 16 rows and stage, the largest rho, [rows/16][ceil(K/64)]
+  uint32_t* words = nullptr;
+  int64_t words_bstride = 0;
+  float* rec = nullptr;
+  int64_t rec_bstride = 0;
 };
 
 // Bytes of one matrix's codes / scales in the stage-major layout (rows rows, K
 // contraction elements; a last partial stage is padded).
 __host__ __device__ inline int64_t tiled_code_bytes(int64_t rows, int64_t K) { return (K + 63) / 64 * rows * 32; }
 __host__ __device__ inline int64_t tiled_scale_bytes(int64_t rows, int64_t K) { return (K + 63) / 64 * rows * 4; }
+
+// Chain bounds over aligned runs of 1, 2 and 4 stages, per unit of 32 rows:
+// [ceil(rows/32)][n1 + n2 + n4], n_g = ceil(stages / g) entries of each run length
+// (the largest rho of the unit's rows over the run).
+__host__ __device__ inline int64_t chain_entries(int64_t nst) { return nst + (nst + 1) / 2 + (nst + 3) / 4; }
+inline int64_t chain_level_count(int64_t rows, int64_t K) { return (rows + 31) / 32 * chain_entries((K + 63) / 64); }
+constexpr int kMaxChainOps = 8;
+struct ChainOp {
+  const uint32_t* words;
+  float* rec;
+  int64_t words_bstride, rec_bstride, rows;
+  int32_t nst;
+  int32_t batch;
+};
+struct ChainList {
+  ChainOp op[kMaxChainOps];
+  int64_t wg_end[kMaxChainOps];
+  int32_t count;
+};
+// Reduces the row words of up to kMaxChainOps operands to their chain levels.
+hipError_t launch_chain_levels(const ChainOp* ops, int count, hipStream_t st);
 
 // Copy of stage-major codes and scales (batch matrices of rows x K) into the
 // row-major layout (codes rows x K/2, scales rows x K/16 per matrix); a null
@@ -149,7 +181,13 @@ hipError_t launch_encode(const Batch& in, int axis, uint32_t sign_mask, bool rot
                          bool adaptive46, MatScalars* sc, int slot, const QOut& out,
                          float* tensor_scale, hipStream_t st);
 
-// launch_encode along rows (axis 1, no clipping, no chain records) with the element
+// The operand Q1x16 of a batch of contiguous rows x K matrices (row blocks), with the
+// tensor scale from amax slot `slot`; writes sc[b].sg[slot].
+hipError_t launch_encode_operand(const float* x, int64_t batch, int64_t rows, int64_t K, int64_t bstride,
+                                 uint32_t sign_mask, bool rotate, bool adaptive46, MatScalars* sc, int slot,
+                                 const OperandOut& out, hipStream_t st);
+
+// launch_encode along rows (axis 1, no clipping) with the element
 // magnitudes rounded stochastically (fp4root_momentum_update); draws from `sr_key`.
 hipError_t launch_encode_sr(const Batch& in, uint32_t sign_mask, bool rotate, bool adaptive46,
                             MatScalars* sc, int slot, const QOut& out, float* tensor_scale,
@@ -206,7 +244,7 @@ hipError_t launch_qadamw(const QAdamWLaunch& p, hipStream_t st);
 // products that run after it; never slot_n or slot_m), as launch_reset_scalars does.
 hipError_t launch_encode_x2(const float* x, int64_t batch, int64_t m, int64_t n, int64_t x_bstride,
                             uint32_t sign_mask, bool rotate, bool adaptive46, MatScalars* sc,
-                            int slot_n, int slot_m, const QOut& qx, const QOut& qxt, hipStream_t st,
+                            int slot_n, int slot_m, const OperandOut& qx, const OperandOut& qxt, hipStream_t st,
                             uint32_t reset_mask = 0);
 
 // ---------------------------------------------------------------------------
@@ -215,11 +253,14 @@ hipError_t launch_encode_x2(const float* x, int64_t batch, int64_t m, int64_t n,
 enum GemmMode { kModeGramA = 0, kModeGramB = 1, kModeUpdateX = 2 };
 
 struct Fp4Operand {
-  const uint8_t* codes;   // stage-major: [ceil(K/64)][rows][32 bytes] (QOut::tiled)
-  const uint8_t* scales;  // stage-major: [ceil(K/64)][rows][4 bytes]
+  const uint8_t* codes;   // stage-major (OperandOut)
+  const uint8_t* scales;
   int64_t codes_bstride, scales_bstride;
-  const float* rhog = nullptr;  // [rows/16][K/64] chain bound records; null: no chaining
-  int64_t rhog_bstride = 0;
+  // chain bounds: levels = 0 none; 1 per 16 rows (OperandOut::rec); 3 per 32 rows over
+  // runs of 1, 2 and 4 stages (launch_chain_levels)
+  const float* rec = nullptr;
+  int64_t rec_bstride = 0;
+  int levels = 0;
 };
 
 struct GemmFp4Args {

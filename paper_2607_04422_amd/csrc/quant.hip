@@ -656,24 +656,9 @@ __global__ __launch_bounds__(256) void k_encode(Batch in, uint32_t mask, int rot
     sc[b].sg[slot] = sg;
     if (tensor_scale) tensor_scale[b] = sg;
   }
-  // With chain records (axis 1, cols a multiple of 64) each wave takes 16 rows x
-  // one 64-column stage: lane 4i + k holds block k of row i, so the stage bound
-  // of a row and the record over the 16 rows reduce within the wave.
-  const bool want_rho = AXIS == 1 && out.rhog != nullptr;
-  if (g >= nblk) return;   // nblk is a multiple of 64 when records are requested: whole waves leave
+  if (g >= nblk) return;
   int64_t r = 0, c = 0;
-  if (want_rho) {
-    // the wave index is uniform (waves never straddle a 256-thread group), so the
-    // division by the stage count is scalar work
-    const uint32_t nst = (uint32_t)(in.cols / 64);
-    const uint32_t wv = __builtin_amdgcn_readfirstlane((uint32_t)(g >> 6));
-    const uint32_t rg = wv / nst, st = wv - rg * nst;
-    const int lane = (int)(threadIdx.x & 63);
-    r = (int64_t)rg * 16 + (lane >> 2);
-    c = ((int64_t)st * 4 + (lane & 3)) * 16;
-  } else {
-    block_pos<AXIS>(in, g, r, c);
-  }
+  block_pos<AXIS>(in, g, r, c);
   {
     float u[16];
     load_block_at<AXIS>(in, b, r, c, u);
@@ -686,19 +671,11 @@ __global__ __launch_bounds__(256) void k_encode(Batch in, uint32_t mask, int rot
     uint32_t scale;
     uint64_t codes;
     uint32_t n2;
-    quant_block(u, sg, adaptive != 0, scale, codes, n2, want_rho, kf);
+    quant_block(u, sg, adaptive != 0, scale, codes, n2, false, kf);
     if constexpr (SR)
       codes = sr_block_codes(u, kf, scale, sg, codes, sr_key, (uint64_t)((b * in.rows + r) * in.cols + c));
-    if (want_rho) {
-      const float rho = wave_max_pos(quad_stage_rho(n2, block_exp(scale)));
-      if ((threadIdx.x & 63) == 0)
-        out.rhog[b * out.rhog_bstride + (r / 16) * (in.cols / 64) + c / 64] = rho;
-    }
     int64_t code_off, scale_off;
-    if (AXIS == 1 && out.tiled) {   // stage-major: [cols/64][rows][32 B], [cols/64][rows][4 B]
-      code_off = ((c / 64) * in.rows + r) * 32 + (c % 64) / 2;
-      scale_off = ((c / 64) * in.rows + r) * 4 + (c % 64) / 16;
-    } else if (AXIS == 1) {   // [rows][cols/2], [rows][cols/16]
+    if (AXIS == 1) {   // [rows][cols/2], [rows][cols/16]
       code_off = r * (in.cols / 2) + c / 2;
       scale_off = r * (in.cols / 16) + c / 16;
     } else {           // transposed: [cols][rows/2], [cols][rows/16]
@@ -711,6 +688,71 @@ __global__ __launch_bounds__(256) void k_encode(Batch in, uint32_t mask, int rot
   }
 }
 
+// The words that lane q of a quad stores (8 bytes at 8 q of the row's 32 bytes of a
+// stage-major stage): first halves of blocks 0 .. 3, then their second halves.  Lane q
+// holds block q's codes; all lanes of the wave must be active.
+FP4R_DEV uint2 quad_stage_words(uint64_t codes, int q) {
+  const uint32_t lo = (uint32_t)codes, hi = (uint32_t)(codes >> 32);
+  const uint32_t l0 = dpp_u<0x88>(lo), l1 = dpp_u<0xDD>(lo);   // lanes 0, 2, 0, 2 and 1, 3, 1, 3
+  const uint32_t h0 = dpp_u<0x88>(hi), h1 = dpp_u<0xDD>(hi);
+  return q < 2 ? make_uint2(l0, l1) : make_uint2(h0, h1);
+}
+
+// A products' operand from row blocks: each wave takes 16 rows x one 64-element stage,
+// lane 4i + k block k of row i (consecutive waves take consecutive stages of a row
+// group, so a workgroup reads whole 256-byte row segments).
+__global__ __launch_bounds__(256) void k_encode_operand(const float* x, int64_t rows, int64_t K, int64_t bstride,
+                                                        uint32_t mask, int rotate, int adaptive, MatScalars* sc,
+                                                        int slot, OperandOut out) {
+  const int64_t b = blockIdx.y;
+  const uint32_t nst = (uint32_t)((K + 63) / 64);
+  // uniform over the wave, so the division by the stage count is scalar work
+  const uint32_t wv = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const float sg = tensor_scale_from_amax(amax_read(sc[b], slot));
+  if (blockIdx.x == 0 && threadIdx.x == 0) sc[b].sg[slot] = sg;
+  const uint32_t rg = wv / nst, st = wv - rg * nst;
+  if ((int64_t)rg * 16 >= rows) return;   // rows is a multiple of 16: whole waves leave
+  const int lane = (int)(threadIdx.x & 63), q = lane & 3;
+  const int64_t r = (int64_t)rg * 16 + (lane >> 2), c = ((int64_t)st * 4 + q) * 16;
+  uint32_t scale = 0, n2 = 0;
+  uint64_t codes = 0;
+  const bool want = out.words != nullptr || out.rec != nullptr;
+  if (c < K) {
+    float u[16];
+    const float4* p = reinterpret_cast<const float4*>(x + b * bstride + r * K + c);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const float4 v = p[k];
+      u[4 * k] = v.x; u[4 * k + 1] = v.y; u[4 * k + 2] = v.z; u[4 * k + 3] = v.w;
+    }
+    const float kf = rotate_for_quant(u, mask, rotate, sg);
+    quant_block(u, sg, adaptive != 0, scale, codes, n2, want, kf);
+  }
+  const int64_t row = (int64_t)st * rows + r;
+  *reinterpret_cast<uint2*>(out.codes + b * out.codes_bstride + row * 32 + 8 * q) = quad_stage_words(codes, q);
+  out.scales[b * out.scales_bstride + row * 4 + q] = (uint8_t)scale;
+  if (want) {
+    const uint32_t w = quad_row_word(n2, scale);
+    if (out.words) {
+      if (q == 0) out.words[b * out.words_bstride + row] = w;
+    } else {
+      const float rho = wave_max_pos(word_rho(w));
+      if (lane == 0) out.rec[b * out.rec_bstride + (int64_t)rg * nst + st] = rho;
+    }
+  }
+}
+
+hipError_t launch_encode_operand(const float* x, int64_t batch, int64_t rows, int64_t K, int64_t bstride,
+                                 uint32_t sign_mask, bool rotate, bool adaptive46, MatScalars* sc, int slot,
+                                 const OperandOut& out, hipStream_t st) {
+  if (rows % 16 != 0 || K % 16 != 0) return hipErrorInvalidValue;
+  const int64_t waves = rows / 16 * ((K + 63) / 64);
+  const dim3 grid((uint32_t)((waves + 3) / 4), (uint32_t)batch);
+  hipLaunchKernelGGL(k_encode_operand, grid, dim3(256), 0, st, x, rows, K, bstride, sign_mask, (int)rotate,
+                     (int)adaptive46, sc, slot, out);
+  return hipGetLastError();
+}
+
 // Both quantisations of X from one read: a 64 x 64 tile is staged in LDS; each
 // thread encodes one 16-column block (qX, along n) and one 16-row block (qXt,
 // along m, written transposed).
@@ -719,7 +761,7 @@ __global__ __launch_bounds__(256) void k_encode(Batch in, uint32_t mask, int rot
 // memory waits (about 2.5 % less time per launch).
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k_encode_x2(const float* x, int64_t m, int64_t n, int64_t x_bstride,
                                                    uint32_t mask, int rotate, int adaptive, MatScalars* sc,
-                                                   int slot_n, int slot_m, QOut qx, QOut qxt, uint32_t reset_mask) {
+                                                   int slot_n, int slot_m, OperandOut qx, OperandOut qxt, uint32_t reset_mask) {
   // rows padded to 68 floats: 16-byte row slices for the row blocks.  gfx950 serves
   // a 128-bit LDS read 16 lanes per cycle over 64 banks and a 128-bit write 8 lanes
   // per cycle over 32 banks: the 16 lanes of one read (4 rows x 4 slices) and 64
@@ -757,10 +799,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k
     }
   }
   __syncthreads();
+  const bool want = qx.words != nullptr || qx.rec != nullptr;
   {
     const int i = threadIdx.x >> 2, q = threadIdx.x & 3;
     const int64_t r = r0 + i, c = c0 + 16 * q;
-    uint32_t n2 = 0, e = 15;
+    uint32_t n2 = 0, scale = 0;
+    uint64_t codes = 0;
     if (r < m && c < n) {
       float u[16];
       const float4* t = reinterpret_cast<const float4*>(&tile[i][16 * q]);
@@ -770,63 +814,144 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k
         u[4 * k] = v.x; u[4 * k + 1] = v.y; u[4 * k + 2] = v.z; u[4 * k + 3] = v.w;
       }
       const float kf = rotate_for_quant(u, mask, rotate, sgn);
-      uint32_t scale;
-      uint64_t codes;
-      quant_block(u, sgn, adaptive != 0, scale, codes, n2, qx.rhog != nullptr, kf);
-      e = block_exp(scale);
-      const int64_t oc = qx.tiled ? ((c0 / 64) * m + r) * 32 + 8 * q : r * (n / 2) + c / 2;
-      const int64_t os = qx.tiled ? ((c0 / 64) * m + r) * 4 + q : r * (n / 16) + c / 16;
-      *reinterpret_cast<uint2*>(qx.codes + b * qx.codes_bstride + oc) = make_uint2((uint32_t)codes, (uint32_t)(codes >> 32));
-      qx.scales[b * qx.scales_bstride + os] = (uint8_t)scale;
+      quant_block(u, sgn, adaptive != 0, scale, codes, n2, want, kf);
     }
-    // chain record of this wave's 16 rows for the tile's 64-column stage: lanes
-    // 4i .. 4i + 3 hold row i's four blocks (blocks past the edge count as zero)
-    if (qx.rhog) {
-      const float rho = wave_max_pos(quad_stage_rho(n2, e));
-      if ((threadIdx.x & 63) == 0 && r0 + 16 * (threadIdx.x >> 6) < m)
-        qx.rhog[b * qx.rhog_bstride + ((r0 / 16) + (threadIdx.x >> 6)) * (n / 64) + c0 / 64] = rho;
+    const int64_t row = (c0 / 64) * m + r;
+    const uint2 w = quad_stage_words(codes, q);
+    if (r < m) {
+      *reinterpret_cast<uint2*>(qx.codes + b * qx.codes_bstride + row * 32 + 8 * q) = w;
+      qx.scales[b * qx.scales_bstride + row * 4 + q] = (uint8_t)scale;
+    }
+    // chain bound of row i's stage (lanes 4i .. 4i + 3 hold its four blocks; blocks past
+    // the edge count as zero), or the largest over this wave's 16 rows
+    if (want) {
+      const uint32_t rw = quad_row_word(n2, scale);
+      if (qx.words) {
+        if (q == 0 && r < m) qx.words[b * qx.words_bstride + row] = rw;
+      } else {
+        const float rho = wave_max_pos(word_rho(rw));
+        if ((threadIdx.x & 63) == 0 && r0 + 16 * (threadIdx.x >> 6) < m)
+          qx.rec[b * qx.rec_bstride + ((r0 / 16) + (threadIdx.x >> 6)) * cdiv(n, 64) + c0 / 64] = rho;
+      }
     }
   }
   {
     const int j = threadIdx.x & 63, q = threadIdx.x >> 6;   // column j, 16 rows at 16 q
     const int64_t c = c0 + j, r = r0 + 16 * q;
-    uint32_t n2 = 0, e = 15;
+    uint32_t n2 = 0, scale = 0;
+    uint64_t codes = 0;
     if (r < m && c < n) {
       float u[16];
 #pragma unroll
       for (int k = 0; k < 16; ++k) u[k] = tile[16 * q + k][j];
       const float kf = rotate_for_quant(u, mask, rotate, sgm);
-      uint32_t scale;
-      uint64_t codes;
-      quant_block(u, sgm, adaptive != 0, scale, codes, n2, qxt.rhog != nullptr, kf);
-      e = block_exp(scale);
-      const int64_t oc = qxt.tiled ? ((r0 / 64) * n + c) * 32 + 8 * q : c * (m / 2) + r / 2;
-      const int64_t os = qxt.tiled ? ((r0 / 64) * n + c) * 4 + q : c * (m / 16) + r / 16;
-      *reinterpret_cast<uint2*>(qxt.codes + b * qxt.codes_bstride + oc) = make_uint2((uint32_t)codes, (uint32_t)(codes >> 32));
-      qxt.scales[b * qxt.scales_bstride + os] = (uint8_t)scale;
+      quant_block(u, sgm, adaptive != 0, scale, codes, n2, want, kf);
     }
-    if (qxt.rhog) {
-      // the stage's four blocks of column j sit in the four waves: exchange in LDS
-      // (the tile is no longer read once every thread has passed the barrier),
-      // then wave 0 reduces each 16 columns (16 rows of qXt) to a record
-      __syncthreads();
-      uint32_t* xn = reinterpret_cast<uint32_t*>(&tile[0][0]);
-      xn[q * 64 + j] = n2;
-      xn[256 + q * 64 + j] = e;
-      __syncthreads();
-      if (q == 0) {
-        uint32_t qn[4], qe[4];
+    // the four blocks of column j (one row of qXt's stage) sit in the four waves:
+    // exchange in LDS (the tile is no longer read once every thread has passed the
+    // barrier); thread 4 j' + q' then stores 8 bytes of row j'
+    __syncthreads();
+    uint32_t* const xc = reinterpret_cast<uint32_t*>(&tile[0][0]);   // [8][64] code words (half, block), rows
+    float* const xt = reinterpret_cast<float*>(xc + 512);            // [4][64] n2 4^E
+    uint32_t* const xs = xc + 768;                                   // [4][64] scale | e << 8
+    xc[q * 64 + j] = (uint32_t)codes;
+    xc[(4 + q) * 64 + j] = (uint32_t)(codes >> 32);
+    xs[q * 64 + j] = scale | (block_unit(scale) << 8);
+    if (want) xt[q * 64 + j] = block_square(n2, scale);
+    __syncthreads();
+    const int j2 = threadIdx.x >> 2, q2 = threadIdx.x & 3;
+    const int64_t row = (r0 / 64) * n + c0 + j2;
+    uint32_t sw[4];
+    float t = 0.0f;
+    if (q2 == 0) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          qn[k] = xn[k * 64 + j];
-          qe[k] = xn[256 + k * 64 + j];
-        }
-        const float rho = row16_max_pos(stage_rho(qn, qe));
-        if ((j & 15) == 0 && c < n)
-          qxt.rhog[b * qxt.rhog_bstride + (c / 16) * (m / 64) + r0 / 64] = rho;
+      for (int k = 0; k < 4; ++k) sw[k] = xs[k * 64 + j2];
+    }
+    if (c0 + j2 < n) {
+      *reinterpret_cast<uint2*>(qxt.codes + b * qxt.codes_bstride + row * 32 + 8 * q2) =
+          make_uint2(xc[(2 * q2) * 64 + j2], xc[(2 * q2 + 1) * 64 + j2]);
+      if (q2 == 0)
+        *reinterpret_cast<uint32_t*>(qxt.scales + b * qxt.scales_bstride + row * 4) =
+            (sw[0] & 0xFFu) | ((sw[1] & 0xFFu) << 8) | ((sw[2] & 0xFFu) << 16) | ((sw[3] & 0xFFu) << 24);
+    }
+    if (want) {
+      uint32_t rw = 0;
+      if (q2 == 0) {
+        t = (xt[j2] + xt[64 + j2]) + (xt[128 + j2] + xt[192 + j2]);
+        rw = row_word(t, min(min(sw[0] >> 8, sw[1] >> 8), min(sw[2] >> 8, sw[3] >> 8)));
+      }
+      if (qxt.words) {
+        if (q2 == 0 && c0 + j2 < n) qxt.words[b * qxt.words_bstride + row] = rw;
+      } else {
+        const float rho = wave_max_pos(word_rho(rw));   // the wave's 16 rows (0 in the other lanes)
+        if ((threadIdx.x & 63) == 0 && c0 + j2 < n)
+          qxt.rec[b * qxt.rec_bstride + ((c0 + j2) / 16) * cdiv(m, 64) + r0 / 64] = rho;
       }
     }
   }
+}
+
+// Chain levels (see chain_entries): each wave takes two units of 32 rows (one per half
+// wave, a row per lane) x four stages.
+__global__ __launch_bounds__(256) void k_chain_levels(ChainList list) {
+  int oi = 0;
+  while (oi + 1 < list.count && (int64_t)blockIdx.x >= list.wg_end[oi]) ++oi;
+  const ChainOp& op = list.op[oi];
+  const int64_t wg = (int64_t)blockIdx.x - (oi > 0 ? list.wg_end[oi - 1] : 0);
+  const int quads = (op.nst + 3) / 4;
+  const int64_t per = ((op.rows + 63) / 64) * quads;   // waves of one matrix
+  const int64_t wv = wg * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t b = wv / per;
+  if (b >= op.batch) return;
+  const int64_t left = wv - b * per;
+  const int quad = (int)(left % quads);
+  const int lane = (int)(threadIdx.x & 63);
+  const int64_t row = (left / quads) * 64 + lane;
+  const uint32_t* words = op.words + b * op.words_bstride;
+  uint32_t w[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    w[k] = row < op.rows && 4 * quad + k < op.nst ? words[(int64_t)(4 * quad + k) * op.rows + row] : 15u;
+  float v[7];   // runs of one stage (4), two (2) and four (1)
+#pragma unroll
+  for (int k = 0; k < 4; ++k) v[k] = word_rho(w[k]);
+#pragma unroll
+  for (int k = 0; k < 2; ++k)
+    v[4 + k] = ldexpf(word_square(w[2 * k]) + word_square(w[2 * k + 1]),
+                      -2 * (int)min(w[2 * k] & 15u, w[2 * k + 1] & 15u));
+  v[6] = ldexpf((word_square(w[0]) + word_square(w[1])) + (word_square(w[2]) + word_square(w[3])),
+                -2 * (int)min(min(w[0] & 15u, w[1] & 15u), min(w[2] & 15u, w[3] & 15u)));
+#pragma unroll
+  for (int k = 0; k < 7; ++k) {
+    const uint32_t h = row16_max_bits(__float_as_uint(v[k]));
+    v[k] = __uint_as_float(max(h, (uint32_t)__shfl_xor((int)h, 16, 64))) * (1.0f + 0x1p-20f);   // past the sums' roundings
+  }
+  const int64_t unit = row / 32;
+  if ((lane & 31) != 0 || unit * 32 >= op.rows) return;
+  const int n1 = op.nst, n2 = (op.nst + 1) / 2;
+  float* rec = op.rec + b * op.rec_bstride + unit * chain_entries(op.nst);
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    if (4 * quad + k < n1) rec[4 * quad + k] = v[k];
+#pragma unroll
+  for (int k = 0; k < 2; ++k)
+    if (2 * quad + k < n2) rec[n1 + 2 * quad + k] = v[4 + k];
+  rec[n1 + n2 + quad] = v[6];
+}
+
+hipError_t launch_chain_levels(const ChainOp* ops, int count, hipStream_t st) {
+  if (count < 1 || count > kMaxChainOps) return hipErrorInvalidValue;
+  ChainList list;
+  list.count = count;
+  int64_t total = 0;
+  for (int i = 0; i < count; ++i) {
+    list.op[i] = ops[i];
+    total += (ops[i].batch * ((ops[i].rows + 63) / 64) * ((ops[i].nst + 3) / 4) + 3) / 4;
+    list.wg_end[i] = total;
+  }
+  if (total == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_chain_levels, dim3((uint32_t)total), dim3(256), 0, st, list);
+  return hipGetLastError();
 }
 
 // One thread per (row, stage) of a matrix: 32 code bytes and 4 scale bytes from the
@@ -844,7 +969,9 @@ __global__ __launch_bounds__(256) void k_untile_nvfp4(const uint8_t* codes, cons
   uint8_t* dc = out_codes ? out_codes + b * rows * (K / 2) + r * (K / 2) + st * 32 : nullptr;
   uint8_t* ds = out_scales ? out_scales + b * rows * (K / 16) + r * (K / 16) + st * 4 : nullptr;
   for (int k = 0; k < nb; ++k) {
-    if (out_codes) *reinterpret_cast<uint2*>(dc + 8 * k) = *reinterpret_cast<const uint2*>(sc + 8 * k);
+    if (out_codes)
+      *reinterpret_cast<uint2*>(dc + 8 * k) =
+          make_uint2(reinterpret_cast<const uint32_t*>(sc)[k], reinterpret_cast<const uint32_t*>(sc)[4 + k]);
     if (out_scales) ds[k] = ss[k];
   }
 }
@@ -861,7 +988,7 @@ hipError_t launch_untile_nvfp4(const uint8_t* codes, const uint8_t* scales, int6
 
 hipError_t launch_encode_x2(const float* x, int64_t batch, int64_t m, int64_t n, int64_t x_bstride,
                             uint32_t sign_mask, bool rotate, bool adaptive46, MatScalars* sc,
-                            int slot_n, int slot_m, const QOut& qx, const QOut& qxt, hipStream_t st,
+                            int slot_n, int slot_m, const OperandOut& qx, const OperandOut& qxt, hipStream_t st,
                             uint32_t reset_mask) {
   if (reset_mask & ((1u << slot_n) | (1u << slot_m))) return hipErrorInvalidValue;
   const dim3 grid((uint32_t)(cdiv(m, kT) * cdiv(n, kT)), (uint32_t)batch);
@@ -886,9 +1013,6 @@ hipError_t launch_amax(const Batch& in, int axis, uint32_t sign_mask, bool rotat
 hipError_t launch_encode(const Batch& in, int axis, uint32_t sign_mask, bool rotate, bool clip,
                          bool adaptive46, MatScalars* sc, int slot, const QOut& out,
                          float* tensor_scale, hipStream_t st) {
-  // chain records: row blocks over whole 64-column stages; the stage-major layout: row blocks
-  if (out.rhog && (axis != 1 || in.cols % 64 != 0 || in.rows % 16 != 0)) return hipErrorInvalidValue;
-  if (out.tiled && axis != 1) return hipErrorInvalidValue;
   const int64_t nblk = in.rows * in.cols / 16;
   const dim3 grid((uint32_t)((nblk + 255) / 256), (uint32_t)in.batch);
   if (axis == 1)
@@ -903,7 +1027,6 @@ hipError_t launch_encode(const Batch& in, int axis, uint32_t sign_mask, bool rot
 hipError_t launch_encode_sr(const Batch& in, uint32_t sign_mask, bool rotate, bool adaptive46,
                             MatScalars* sc, int slot, const QOut& out, float* tensor_scale,
                             uint64_t sr_key, hipStream_t st) {
-  if (out.rhog) return hipErrorInvalidValue;
   const int64_t nblk = in.rows * in.cols / 16;
   const dim3 grid((uint32_t)((nblk + 255) / 256), (uint32_t)in.batch);
   hipLaunchKernelGGL((k_encode<1, true>), grid, dim3(256), 0, st, in, sign_mask, (int)rotate, 0,

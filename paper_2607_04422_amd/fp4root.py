@@ -173,9 +173,8 @@ def fp4root_version() -> int:
 
 
 def fp4root_set_product_tiling(mode: int) -> int:
-    """0: tile form chosen per launch, 1: narrow (32 x 64 per wave), 2: wide (64 x 64)
-    for the Gram of qX and the update product; returns the previous mode.  Outputs are
-    the same bits in every mode."""
+    """0: tile form chosen per launch, 1: narrow (32 x 32 per wave), 2: wide (64 x 64);
+    returns the previous mode.  Outputs are the same bits in every mode."""
     code = load().fp4root_set_product_tiling(int(mode))
     if code < 0:
         raise Fp4RootError(code, "fp4root_set_product_tiling")
