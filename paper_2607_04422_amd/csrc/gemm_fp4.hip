@@ -269,6 +269,21 @@ FP4R_DEV uint32_t wave_max_bits(float v) {
 // ---------------------------------------------------------------------------
 // Exact NVFP4 product.
 
+// Zeroes a chain register with eight 64-bit moves (sixteen 32-bit ones otherwise); the
+// wait states at the end are those an MFMA reading it next needs.
+FP4R_DEV f32x16 zero16() {
+  typedef double f64x8 __attribute__((ext_vector_type(8)));
+  f64x8 z;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    double d;
+    if (k < 7) asm volatile("v_mov_b64 %0, 0" : "=v"(d));
+    else asm volatile("v_mov_b64 %0, 0\n\ts_nop 1" : "=v"(d));
+    z[k] = d;
+  }
+  return __builtin_bit_cast(f32x16, z);
+}
+
 template <int KB>
 using block_t = std::integral_constant<int, KB>;
 
@@ -488,7 +503,7 @@ FP4R_DEV void gemm_fp4_tile(const GemmFp4Args& g, int64_t wg, int tiles_m, int t
 #pragma unroll
           for (int j = 0; j < TN; ++j) {
             fold(i, j);
-            p[i][j] = zero;
+            p[i][j] = zero16();
           }
       }
     };
@@ -498,7 +513,7 @@ FP4R_DEV void gemm_fp4_tile(const GemmFp4Args& g, int64_t wg, int tiles_m, int t
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
           fold(i, j);
-          p[i][j] = zero;
+          p[i][j] = zero16();
         }
     }
     block(block_t<0>(), std::false_type());
