@@ -75,12 +75,15 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // not fill the chip with wide workgroups.
 template <int WM_, int WN_, int TM_, int TN_, int WPE_>
 struct Fp4Tiling {
-  static constexpr int WM = WM_, WN = WN_, TM = TM_, TN = TN_, WPE = WPE_;
+  static constexpr int WM = WM_, WN = WN_, TM = TM_, TN = TN_, WPE = WPE_, NW = WM_ * WN_;
   static constexpr int kTile = WM_ * TM_ * 32;
   static_assert(kTile == WN_ * TN_ * 32, "square workgroup tiles (symmetric products)");
 };
+constexpr int kFp4Waves = 4;
 using Fp4Wide = Fp4Tiling<2, 2, 2, 2, 2>;
 using Fp4Narrow = Fp4Tiling<2, 2, 1, 1, 4>;
+static_assert(Fp4Wide::NW == kFp4Waves && Fp4Narrow::NW == kFp4Waves && Fp4Wide::kTile == 2 * Fp4Narrow::kTile,
+              "a wide tile is four narrow ones of as many threads");
 
 // Output tile coordinates.  Symmetric products enumerate the upper triangle
 // row by row; others are row-major over (tiles_m x tiles_n).
@@ -287,27 +290,33 @@ FP4R_DEV f32x16 zero16() {
 template <int KB>
 using block_t = std::integral_constant<int, KB>;
 
-// One output tile of one product: workgroup wg of the product's tiles_per_mat *
-// batch tiles; fin (may be null) routes a last update's output to the callers'
-// matrices.  Every kernel entry below runs this body.
-template <int MODE, int WM_, int WN_, int TM, int TN, bool ACC32>
-FP4R_DEV void gemm_fp4_tile(const GemmFp4Args& g, int64_t wg, int tiles_m, int tiles_n, int64_t tiles_per_mat,
-                            const GemmFin* finp) {
-  constexpr int BM = WM_ * TM * 32, BN = WN_ * TN * 32, NT = WM_ * WN_ * 64, NW = WM_ * WN_;
-  // padded row of the FP32 output tile staged in LDS: rows stay 16-byte aligned, and
-  // the two half-waves of an MFMA-layout write (rows 4 apart) fall 32 banks apart
-  constexpr int kLdT = BN + 8;
+// LDS of one workgroup in form C.
+template <class C>
+struct Fp4Lds {
+  static constexpr int kOps = C::TM + C::TN;
   // ring of two raw stages per wave (see load_stage)
-  constexpr int kOps = TM + TN, kSlot = 512 + 1024 * kOps, kRing = 2 * kSlot;
-  constexpr size_t kMainBytes = (size_t)NW * kRing;
-  constexpr size_t kEpiBytes = (size_t)BM * kLdT * sizeof(float);
-  __shared__ __attribute__((aligned(16))) char smem[kMainBytes > kEpiBytes ? kMainBytes : kEpiBytes];
-  __shared__ uint64_t wflags[NW][2][kChainWindows];   // per wave: stages that chain, that continue a group
-  __shared__ uint32_t red[2][NW];   // per-wave amaxes (rows, columns)
+  static constexpr int kSlot = 512 + 1024 * kOps, kRing = 2 * kSlot;
+  // padded row of the FP32 output tile of the epilogue: rows stay 16-byte aligned, and
+  // the two half-waves of an MFMA-layout write (rows 4 apart) fall 32 banks apart
+  static constexpr int kLdT = C::kTile + 8;
+  static constexpr int kMain = C::NW * kRing, kEpi = C::kTile * kLdT * (int)sizeof(float);
+  static constexpr int kBytes = kMain > kEpi ? kMain : kEpi;
+};
+struct Fp4Shared {
+  uint64_t flags[kFp4Waves][2][kChainWindows];   // per wave: stages that chain, that continue a group
+  uint32_t red[2][kFp4Waves];                    // per-wave amaxes (rows, columns)
+};
+
+// Output tile (tm, tn) of matrix `mat` of one product in form C; finp (may be null)
+// routes a last update's output to the callers' matrices.  Every kernel entry below
+// runs this body.
+template <int MODE, class C, bool ACC32>
+FP4R_DEV void gemm_fp4_tile(const GemmFp4Args& g, int64_t mat, int tm, int tn, const GemmFin* finp, char* smem,
+                            Fp4Shared& sh) {
+  constexpr int WN_ = C::WN, TM = C::TM, TN = C::TN, NW = C::NW;
+  constexpr int BM = C::kTile, BN = C::kTile, NT = NW * 64;
+  constexpr int kOps = Fp4Lds<C>::kOps, kSlot = Fp4Lds<C>::kSlot, kRing = Fp4Lds<C>::kRing, kLdT = Fp4Lds<C>::kLdT;
   constexpr bool kSym = MODE != kModeUpdateX;
-  const int64_t mat = wg / tiles_per_mat;
-  int tm, tn;
-  tile_coords(wg % tiles_per_mat, tiles_m, tiles_n, kSym, tm, tn);
   const int64_t row0 = (int64_t)tm * BM, col0 = (int64_t)tn * BN;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -364,8 +373,8 @@ FP4R_DEV void gemm_fp4_tile(const GemmFp4Args& g, int64_t wg, int tiles_m, int t
       }
       const uint64_t mc = __builtin_amdgcn_ballot_w64(chain), mo = __builtin_amdgcn_ballot_w64(cont);
       if (lane == 0) {
-        wflags[wave][0][w] = mc;
-        wflags[wave][1][w] = mo;
+        sh.flags[wave][0][w] = mc;
+        sh.flags[wave][1][w] = mo;
       }
     }
   };
@@ -457,7 +466,7 @@ FP4R_DEV void gemm_fp4_tile(const GemmFp4Args& g, int64_t wg, int tiles_m, int t
     if (!ACC32 && (s & 63) == 0) {
       chain_mask = cont_mask = 0;
       if (s < kChainStages) {
-        const uint64_t c = wflags[wave][0][s >> 6], o = wflags[wave][1][s >> 6];
+        const uint64_t c = sh.flags[wave][0][s >> 6], o = sh.flags[wave][1][s >> 6];
         chain_mask = ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(c >> 32)) << 32) |
                      (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)c);
         cont_mask = ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(o >> 32)) << 32) |
@@ -659,80 +668,101 @@ FP4R_DEV void gemm_fp4_tile(const GemmFp4Args& g, int64_t wg, int tiles_m, int t
   if (do_rows || do_cols) {
     const uint32_t wr = wave_max_bits(rmax), wc = wave_max_bits(cmax);
     if (lane == 0) {
-      red[0][wave] = wr;
-      red[1][wave] = wc;
+      sh.red[0][wave] = wr;
+      sh.red[1][wave] = wc;
     }
     __syncthreads();
     if (threadIdx.x < 2 && (threadIdx.x == 0 ? do_rows : do_cols)) {
       uint32_t m = 0;
 #pragma unroll
-      for (int w = 0; w < NW; ++w) m = m > red[threadIdx.x][w] ? m : red[threadIdx.x][w];
+      for (int w = 0; w < NW; ++w) m = m > sh.red[threadIdx.x][w] ? m : sh.red[threadIdx.x][w];
       const float mf = g.amax_rotate ? 0.25f * __uint_as_float(m) : __uint_as_float(m);
       amax_record(&g.sc[mat], threadIdx.x == 0 ? g.amax_row_slot : g.amax_col_slot, blockIdx.x, mf);
     }
   }
 }
 
+// Workgroup `wg` of a launch: in the wide form the first `wide` workgroups take one wide
+// tile each and the later ones a quadrant (a narrow tile) of the wide tiles that follow,
+// four workgroups per wide tile; in the narrow form every workgroup takes one narrow tile.
+// t counts the tiles of the launch in the form's own size.
+struct TileSlot {
+  int64_t t;
+  int quadrant;   // -1: the whole tile
+};
+FP4R_DEV TileSlot tile_slot(int64_t wg, int64_t wide) {
+  if (wg < wide) return TileSlot{wg, -1};
+  return TileSlot{wide + (wg - wide) / 4, (int)((wg - wide) & 3)};
+}
+
+// The work of a slot whose tile is number t of product g.
+template <int MODE, class C, bool ACC32>
+FP4R_DEV void run_slot(const GemmFp4Args& g, int64_t t, int quadrant, int tiles_m, int tiles_n, int64_t tiles_per_mat,
+                       const GemmFin* fin, char* smem, Fp4Shared& sh) {
+  constexpr bool kSym = MODE != kModeUpdateX;
+  const int64_t mat = t / tiles_per_mat;
+  int tm, tn;
+  tile_coords(t % tiles_per_mat, tiles_m, tiles_n, kSym, tm, tn);
+  if constexpr (C::kTile == Fp4Wide::kTile) {
+    if (quadrant >= 0) {
+      const int ntm = 2 * tm + (quadrant >> 1), ntn = 2 * tn + (quadrant & 1);
+      if (kSym && ntn < ntm) return;   // the mirror of another quadrant
+      if ((int64_t)ntm * Fp4Narrow::kTile >= g.M || (int64_t)ntn * Fp4Narrow::kTile >= g.N) return;
+      gemm_fp4_tile<MODE, Fp4Narrow, ACC32>(g, mat, ntm, ntn, fin, smem, sh);
+      return;
+    }
+  }
+  gemm_fp4_tile<MODE, C, ACC32>(g, mat, tm, tn, fin, smem, sh);
+}
+
 // One product per launch (its arguments at fixed offsets).
-template <int MODE, int WM_, int WN_, int TM, int TN, int WPE, bool ACC32>
-__global__ __launch_bounds__(WM_* WN_ * 64) __attribute__((amdgpu_waves_per_eu(WPE)))
-void k_gemm_fp4(GemmFp4Args g, int tiles_m, int tiles_n, int64_t tiles_per_mat, GemmFin fin) {
-  gemm_fp4_tile<MODE, WM_, WN_, TM, TN, ACC32>(g, blockIdx.x, tiles_m, tiles_n, tiles_per_mat, &fin);
+template <int MODE, class C, bool ACC32>
+__global__ __launch_bounds__(C::NW * 64) __attribute__((amdgpu_waves_per_eu(C::WPE)))
+void k_gemm_fp4(GemmFp4Args g, int tiles_m, int tiles_n, int64_t tiles_per_mat, int64_t wide, GemmFin fin) {
+  __shared__ __attribute__((aligned(16))) char smem[Fp4Lds<C>::kBytes];
+  __shared__ Fp4Shared sh;
+  const TileSlot slot = tile_slot(blockIdx.x, wide);
+  run_slot<MODE, C, ACC32>(g, slot.t, slot.quadrant, tiles_m, tiles_n, tiles_per_mat, &fin, smem, sh);
 }
 
 // Several products of one mode per launch: each workgroup finds its product (uniform
-// over the workgroup) from the cumulative workgroup counts.
-template <int MODE, int WM_, int WN_, int TM, int TN, int WPE, bool ACC32>
-__global__ __launch_bounds__(WM_* WN_ * 64) __attribute__((amdgpu_waves_per_eu(WPE)))
+// over the workgroup) from the cumulative tile counts.
+template <int MODE, class C, bool ACC32>
+__global__ __launch_bounds__(C::NW * 64) __attribute__((amdgpu_waves_per_eu(C::WPE)))
 void k_gemm_fp4_multi(GemmFp4Batch gb) {
+  __shared__ __attribute__((aligned(16))) char smem[Fp4Lds<C>::kBytes];
+  __shared__ Fp4Shared sh;
+  const TileSlot slot = tile_slot(blockIdx.x, gb.wide);
   int pi = 0;
-  while (pi + 1 < gb.count && (int64_t)blockIdx.x >= gb.wg_end[pi]) ++pi;
-  const int64_t wg = (int64_t)blockIdx.x - (pi > 0 ? gb.wg_end[pi - 1] : 0);
-  gemm_fp4_tile<MODE, WM_, WN_, TM, TN, ACC32>(gb.p[pi], wg, gb.tiles_m[pi], gb.tiles_n[pi], gb.tiles_per_mat[pi],
-                                              nullptr);
+  while (pi + 1 < gb.count && slot.t >= gb.tile_end[pi]) ++pi;
+  const int64_t t = slot.t - (pi > 0 ? gb.tile_end[pi - 1] : 0);
+  run_slot<MODE, C, ACC32>(gb.p[pi], t, slot.quadrant, gb.tiles_m[pi], gb.tiles_n[pi], gb.tiles_per_mat[pi], nullptr,
+                           smem, sh);
 }
 
 template <int MODE, class C, bool ACC32>
-void launch_fp4_single(dim3 grid, hipStream_t st, const GemmFp4Args& g, int tm, int tn, int64_t per,
-                       const GemmFin& f) {
-  hipLaunchKernelGGL((k_gemm_fp4<MODE, C::WM, C::WN, C::TM, C::TN, C::WPE, ACC32>), grid, dim3(C::WM * C::WN * 64), 0,
-                     st, g, tm, tn, per, f);
+void launch_fp4_form(dim3 grid, hipStream_t st, const GemmFp4Batch& gb, const GemmFin& f) {
+  if (gb.count == 1)
+    hipLaunchKernelGGL((k_gemm_fp4<MODE, C, ACC32>), grid, dim3(C::NW * 64), 0, st, gb.p[0], (int)gb.tiles_m[0],
+                       (int)gb.tiles_n[0], gb.tiles_per_mat[0], gb.wide, f);
+  else if constexpr (MODE != kModeUpdateX)
+    hipLaunchKernelGGL((k_gemm_fp4_multi<MODE, C, ACC32>), grid, dim3(C::NW * 64), 0, st, gb);
 }
-template <int MODE, class C, bool ACC32>
-void launch_fp4_multi(dim3 grid, hipStream_t st, const GemmFp4Batch& gb) {
-  hipLaunchKernelGGL((k_gemm_fp4_multi<MODE, C::WM, C::WN, C::TM, C::TN, C::WPE, ACC32>), grid,
-                     dim3(C::WM * C::WN * 64), 0, st, gb);
+
+template <int MODE, bool ACC32>
+void launch_fp4_mode(bool wide, dim3 grid, hipStream_t st, const GemmFp4Batch& gb, const GemmFin& f) {
+  if (wide) launch_fp4_form<MODE, Fp4Wide, ACC32>(grid, st, gb, f);
+  else launch_fp4_form<MODE, Fp4Narrow, ACC32>(grid, st, gb, f);
 }
 
 // The kernel of one launch: mode, tile form and accumulation.
 template <bool ACC32>
 void launch_fp4_kernel(GemmMode mode, bool wide, dim3 grid, hipStream_t st, const GemmFp4Batch& gb,
                        const GemmFin& f) {
-  if (gb.count == 1) {
-    const GemmFp4Args& g = gb.p[0];
-    const int tm = gb.tiles_m[0], tn = gb.tiles_n[0];
-    const int64_t per = gb.tiles_per_mat[0];
-    switch (mode) {
-      case kModeGramA:
-        if (wide) launch_fp4_single<kModeGramA, Fp4Wide, ACC32>(grid, st, g, tm, tn, per, f);
-        else launch_fp4_single<kModeGramA, Fp4Narrow, ACC32>(grid, st, g, tm, tn, per, f);
-        break;
-      case kModeGramB:
-        if (wide) launch_fp4_single<kModeGramB, Fp4Wide, ACC32>(grid, st, g, tm, tn, per, f);
-        else launch_fp4_single<kModeGramB, Fp4Narrow, ACC32>(grid, st, g, tm, tn, per, f);
-        break;
-      default:
-        if (wide) launch_fp4_single<kModeUpdateX, Fp4Wide, ACC32>(grid, st, g, tm, tn, per, f);
-        else launch_fp4_single<kModeUpdateX, Fp4Narrow, ACC32>(grid, st, g, tm, tn, per, f);
-    }
-    return;
-  }
-  if (mode == kModeGramA) {
-    if (wide) launch_fp4_multi<kModeGramA, Fp4Wide, ACC32>(grid, st, gb);
-    else launch_fp4_multi<kModeGramA, Fp4Narrow, ACC32>(grid, st, gb);
-  } else {
-    if (wide) launch_fp4_multi<kModeGramB, Fp4Wide, ACC32>(grid, st, gb);
-    else launch_fp4_multi<kModeGramB, Fp4Narrow, ACC32>(grid, st, gb);
+  switch (mode) {
+    case kModeGramA: launch_fp4_mode<kModeGramA, ACC32>(wide, grid, st, gb, f); break;
+    case kModeGramB: launch_fp4_mode<kModeGramB, ACC32>(wide, grid, st, gb, f); break;
+    default: launch_fp4_mode<kModeUpdateX, ACC32>(wide, grid, st, gb, f);
   }
 }
 
@@ -741,6 +771,12 @@ void launch_fp4_kernel(GemmMode mode, bool wide, dim3 grid, hipStream_t st, cons
 // (272), 130 / 122 (528), 117 / 99 (600); update 17 / 26 (64), 43 / 48 (396), 85 / 76 (512),
 // 153 / 131 (1024).
 constexpr int64_t kWideMinTiles = 512;
+// A last round of at most this many wide tiles is cut into narrow ones: a wide tile
+// alone on its CU has one wave per SIMD and takes most of a full round's time.  Grams of
+// 4096 x 4096 (528 tiles) 126 -> 107 and 140 -> 117 us, of 4 x 2048 x 2048 (544) 75 -> 64 and
+// 87 -> 72 us, update of 3072 x 3072 (576) 108 -> 92 us; rounds filled by more than a third
+// measured the same either way.
+constexpr int64_t kFp4Round = 512, kTailMax = 192;
 
 std::atomic<int> g_product_tiling{0};
 
@@ -785,10 +821,12 @@ hipError_t launch_gemm_fp4_batch(GemmMode mode, const GemmFp4Args* list, int cou
     gb.tiles_n[k] = tiles_n;
     gb.tiles_per_mat[k] = per;
     total += per * g.batch;
-    gb.wg_end[k] = total;
+    gb.tile_end[k] = total;
   }
   if (gb.count == 0) return hipSuccess;
-  const dim3 grid((uint32_t)total);
+  const int64_t rest = total % kFp4Round;
+  gb.wide = wide && forced == 0 && rest <= kTailMax ? total - rest : total;
+  const dim3 grid((uint32_t)(gb.wide + 4 * (total - gb.wide)));
   // several products per launch: the symmetric products only
   if (gb.count > 1 && ((fin && fin->count > 0) || mode == kModeUpdateX)) return hipErrorInvalidValue;
   GemmFin f;

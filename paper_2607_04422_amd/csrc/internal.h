@@ -304,7 +304,8 @@ struct GemmFp4Batch {
   GemmFp4Args p[kMaxGemmProblems];
   int32_t tiles_m[kMaxGemmProblems], tiles_n[kMaxGemmProblems];
   int64_t tiles_per_mat[kMaxGemmProblems];
-  int64_t wg_end[kMaxGemmProblems];   // cumulative workgroup counts
+  int64_t tile_end[kMaxGemmProblems];   // cumulative tile counts
+  int64_t wide;   // tiles taken whole, one workgroup each; four workgroups for each later tile
   int32_t count;
 };
 
