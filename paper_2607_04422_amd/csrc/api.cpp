@@ -311,12 +311,10 @@ int run_step_fp4(const StepGroup* gs, int count, uint32_t flags, uint64_t seed, 
     const StepGroup& sg = gs[i];
     const StepWs& w = *sg.w;
     uint32_t reset = (1u << kSlotA) | (1u << kSlotB) | (1u << nxn) | (1u << nxm);
-    const Batch bx{sg.x, sg.batch, sg.m, sg.n, sg.n, sg.bstride};
     if (x_amax_needed) {
       FP4R_TRY(launch_reset_scalars(w.sc, sg.batch, reset | (1u << xn) | (1u << xm), false, st));
       reset = 0;
-      FP4R_TRY(launch_amax(bx, 1, mask, rot, false, w.sc, xn, status, st));
-      FP4R_TRY(launch_amax(bx, 0, mask, rot, false, w.sc, xm, status, st));
+      FP4R_TRY(launch_amax_x2(sg.x, sg.batch, sg.m, sg.n, sg.bstride, mask, rot, w.sc, xn, xm, status, st));
     }
     const OperandOut qx = operand_out(w.qx_c, w.qx_s, sg.m, sg.n, w.words_x, rec(w.rec_x));
     const OperandOut qxt = operand_out(w.qxt_c, w.qxt_s, sg.n, sg.m, w.words_xt, rec(w.rec_xt));

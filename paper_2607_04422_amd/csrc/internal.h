@@ -175,6 +175,11 @@ hipError_t launch_untile_nvfp4(const uint8_t* codes, const uint8_t* scales, int6
 hipError_t launch_amax(const Batch& in, int axis, uint32_t sign_mask, bool rotate, bool clip,
                        MatScalars* sc, int slot, uint32_t* status, hipStream_t st);
 
+// Both amaxes of a batch of contiguous m x n matrices (row blocks into slot_n, column
+// blocks into slot_m) from one read; non-finite elements set the status word.
+hipError_t launch_amax_x2(const float* x, int64_t batch, int64_t m, int64_t n, int64_t x_bstride, uint32_t sign_mask,
+                          bool rotate, MatScalars* sc, int slot_n, int slot_m, uint32_t* status, hipStream_t st);
+
 // Encode with the tensor scale derived from amax slot `slot` of sc[b]; writes sc[b].sg[slot]
 // and, when tensor_scale != nullptr, tensor_scale[b].
 hipError_t launch_encode(const Batch& in, int axis, uint32_t sign_mask, bool rotate, bool clip,

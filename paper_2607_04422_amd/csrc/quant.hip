@@ -457,6 +457,83 @@ __global__ __launch_bounds__(256) void k_prep_copy(MatChunk ch, MatScalars* sc, 
   }
 }
 
+// Rotated amaxes of X along n and along m from one read (X as given, no clipping): the
+// tile and the block passes of k_prep_copy.  A block with a non-finite element sets the
+// status and does not count.  One read instead of one per axis: 165 -> 95 us on
+// 4 x 3072 x 8192.
+__global__ __launch_bounds__(256) void k_amax_x2(const float* x, int64_t m, int64_t n, int64_t x_bstride,
+                                                 uint32_t mask, int rotate, MatScalars* sc, int slot_n,
+                                                 int slot_m, uint32_t* status) {
+  __shared__ float tile[kT][kT + 1];
+  __shared__ float red[4];
+  const int64_t b = blockIdx.y;
+  const uint32_t tn = (uint32_t)cdiv(n, kT);
+  const int64_t r0 = (int64_t)(blockIdx.x / tn) * kT, c0 = (int64_t)(blockIdx.x % tn) * kT;
+  const float* X = x + b * x_bstride;
+  bool bad = false;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int v = (int)threadIdx.x + 256 * k, i = v >> 4, q = v & 15;
+    if (r0 + i < m && c0 + 4 * q < n) {
+      const float4 a = *reinterpret_cast<const float4*>(X + (r0 + i) * n + c0 + 4 * q);
+      tile[i][4 * q] = a.x; tile[i][4 * q + 1] = a.y; tile[i][4 * q + 2] = a.z; tile[i][4 * q + 3] = a.w;
+      bad |= !(fabsf(a.x) <= 3.40282347e38f) | !(fabsf(a.y) <= 3.40282347e38f) |
+             !(fabsf(a.z) <= 3.40282347e38f) | !(fabsf(a.w) <= 3.40282347e38f);
+    }
+  }
+  const bool any_bad = __syncthreads_or(bad);
+  if (any_bad && threadIdx.x == 0) atomicOr(status, kStatusNonFinite);
+  auto block_amax = [&](float (&u)[16]) {
+    bool ok = true;
+    if (any_bad) {
+#pragma unroll
+      for (int k = 0; k < 16; ++k) ok = ok && ((__float_as_uint(u[k]) & 0x7F800000u) != 0x7F800000u);
+    }
+    float v = 0.0f;
+    if (rotate) {
+      v = 0.25f * rot16_absmax4(u, mask);
+    } else {
+#pragma unroll
+      for (int k = 0; k < 16; ++k) v = fmaxf(v, fabsf(u[k]));
+    }
+    return ok ? v : 0.0f;
+  };
+  float mr = 0.0f, mc = 0.0f;
+  {
+    const int i = threadIdx.x >> 2, q = threadIdx.x & 3;
+    if (r0 + i < m && c0 + 16 * q < n) {
+      float u[16];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) u[k] = tile[i][16 * q + k];
+      mr = block_amax(u);
+    }
+  }
+  {
+    const int j = threadIdx.x & 63, q = threadIdx.x >> 6;
+    if (c0 + j < n && r0 + 16 * q < m) {
+      float u[16];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) u[k] = tile[16 * q + k][j];
+      mc = block_amax(u);
+    }
+  }
+  const float br = block_max_256(mr, red);
+  __syncthreads();
+  const float bc = block_max_256(mc, red);
+  if (threadIdx.x == 0) {
+    amax_record(&sc[b], slot_n, blockIdx.x, br);
+    amax_record(&sc[b], slot_m, blockIdx.x, bc);
+  }
+}
+
+hipError_t launch_amax_x2(const float* x, int64_t batch, int64_t m, int64_t n, int64_t x_bstride, uint32_t sign_mask,
+                          bool rotate, MatScalars* sc, int slot_n, int slot_m, uint32_t* status, hipStream_t st) {
+  const dim3 grid((uint32_t)(cdiv(m, kT) * cdiv(n, kT)), (uint32_t)batch);
+  hipLaunchKernelGGL(k_amax_x2, grid, dim3(256), 0, st, x, m, n, x_bstride, sign_mask, (int)rotate, sc, slot_n,
+                     slot_m, status);
+  return hipGetLastError();
+}
+
 // Copy-out: caller M (rows x cols) from canonical X (transposed back when tall).
 __global__ __launch_bounds__(256) void k_copy_out(MatChunk ch, const float* xbase, int64_t x_bstride) {
   __shared__ float tile[kT][kT + 1];
