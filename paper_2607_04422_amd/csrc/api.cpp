@@ -68,6 +68,8 @@ bool aligned(const void* p, size_t a) { return ((uintptr_t)p % a) == 0; }
 // bytes, are then addressed with 32-bit offsets too.
 constexpr int64_t kMaxDim = int64_t(1) << 21;
 constexpr int64_t kMaxElems = int64_t(1) << 36;
+// Row strides: 16 rows of 2^33 - 4 floats are 512 GiB, more than the device holds.
+constexpr int64_t kMaxLd = (int64_t(1) << 33) - 4;
 bool dims_ok(int64_t r, int64_t c) {
   return r > 0 && c > 0 && r % 16 == 0 && c % 16 == 0 && r <= kMaxDim && c <= kMaxDim && r * c <= kMaxElems;
 }
@@ -223,6 +225,12 @@ Fp4Operand tiled_operand(const uint8_t* c, const uint8_t* s, int64_t rows, int64
   o.levels = use_levels(K) ? 3 : 1;
   return o;
 }
+// The operand of the matrices from `first` on.
+void advance(Fp4Operand& o, int64_t first) {
+  o.codes += first * o.codes_bstride;
+  o.scales += first * o.scales_bstride;
+  if (o.rec) o.rec += first * o.rec_bstride;
+}
 // The chain levels of an operand's row words.
 ChainOp chain_op(const uint32_t* words, float* rec, int64_t batch, int64_t rows, int64_t K) {
   return ChainOp{words, rec, words_stride(rows, K), rec_stride(rows, K), rows, (int32_t)((K + 63) / 64),
@@ -255,7 +263,7 @@ struct StepGroup {
   int64_t batch, m, n, bstride;
   const StepWs* w;
   float a, b, c;
-  const MatChunk* fin = nullptr;
+  const std::vector<MatChunk>* fin = nullptr;
 };
 
 // The product args of one group's step, common parts.
@@ -306,14 +314,13 @@ int run_step_fp4(const StepGroup* gs, int count, uint32_t flags, uint64_t seed, 
   const int xn = xs, xm = xs + 1, nxn = xs ^ 2, nxm = (xs ^ 2) + 1;
   ChainQueue chains(st);
   // qX and qXt; the amax slots recorded later in the step are cleared by the encoder
-  // of X (or before the amax passes of X when those run first)
+  // of X (a single step starts with every slot clear)
   for (int i = 0; i < count; ++i) {
     const StepGroup& sg = gs[i];
     const StepWs& w = *sg.w;
     uint32_t reset = (1u << kSlotA) | (1u << kSlotB) | (1u << nxn) | (1u << nxm);
     if (x_amax_needed) {
-      FP4R_TRY(launch_reset_scalars(w.sc, sg.batch, reset | (1u << xn) | (1u << xm), false, st));
-      reset = 0;
+      reset = 0;   // a single step: its scalars were just reset
       FP4R_TRY(launch_amax_x2(sg.x, sg.batch, sg.m, sg.n, sg.bstride, mask, rot, w.sc, xn, xm, status, st));
     }
     const OperandOut qx = operand_out(w.qx_c, w.qx_s, sg.m, sg.n, w.words_x, rec(w.rec_x));
@@ -373,16 +380,6 @@ int run_step_fp4(const StepGroup* gs, int count, uint32_t flags, uint64_t seed, 
     FP4R_TRY(launch_encode_operand(w.A, sg.batch, sg.m, sg.m, sg.m * sg.m, mask, rot, ad, w.sc, kSlotB, qb, st));
     FP4R_TRY(chains.add(qb, w.rec_a, sg.batch, sg.m, sg.m));
     FP4R_TRY(chains.flush());
-    // last step: X_{k+1} goes straight to the callers' matrices
-    GemmFin fin;
-    if (sg.fin) {
-      fin.count = sg.fin->count;
-      for (int f = 0; f < sg.fin->count; ++f) {
-        fin.out[f] = sg.fin->m[f].out;
-        fin.ld[f] = sg.fin->m[f].ld_out;
-        fin.tall[f] = sg.fin->m[f].rows > sg.fin->m[f].cols ? 1 : 0;
-      }
-    }
     if (tr) {
       FP4R_TRY(export_operand(tr->qx_codes, tr->qx_scales, w.qx_c, w.qx_s, sg.batch, sg.m, sg.n, st));
       FP4R_TRY(launch_export_scalar(w.sc, sg.batch, 1, xn, tr->qx_sg, st));
@@ -391,18 +388,42 @@ int run_step_fp4(const StepGroup* gs, int count, uint32_t flags, uint64_t seed, 
       FP4R_TRY(export_operand(tr->qb_codes, tr->qb_scales, w.qa_c, w.qa_s, sg.batch, sg.m, sg.m, st));
       FP4R_TRY(launch_export_scalar(w.sc, sg.batch, 1, kSlotB, tr->qb_sg, st));
     }
-    FP4R_TRY(launch_products(kModeUpdateX, 2, gs + i, 1, [&](const StepGroup& u) {
-      GemmFp4Args g = product_args(u, next_mask, rot, acc32);
-      g.a = tiled_operand(u.w->qa_c, u.w->qa_s, u.m, u.m, rec(u.w->rec_a));
-      g.b = tiled_operand(u.w->qxt_c, u.w->qxt_s, u.n, u.m, rec(u.w->rec_xt));
-      g.M = u.m; g.N = u.n; g.K = u.m;
-      g.slot_a = kSlotB; g.slot_b = xm;
-      g.out = u.x; g.out_bstride = u.bstride; g.aux = u.x;
-      g.ca = u.a;
-      g.amax_row_slot = nxn; g.amax_col_slot = nxm;
-      if (u.fin) g.amax_row_slot = g.amax_col_slot = -1;   // last step: no amaxes needed
-      return g;
-    }, st, sg.fin ? &fin : nullptr));
+    // last step: X_{k+1} goes straight to the callers' matrices, a chunk per launch
+    const size_t parts = sg.fin ? sg.fin->size() : 1;
+    for (size_t c = 0; c < parts; ++c) {
+      const int64_t first = (int64_t)c * kMaxChunk;
+      GemmFin fin;
+      if (sg.fin) {
+        const MatChunk& ch = (*sg.fin)[c];
+        fin.count = ch.count;
+        for (int f = 0; f < ch.count; ++f) {
+          fin.out[f] = ch.m[f].out;
+          fin.ld[f] = ch.m[f].ld_out();
+          fin.tall[f] = ch.m[f].tall() ? 1 : 0;
+        }
+      }
+      const int rc = launch_products(kModeUpdateX, 2, gs + i, 1, [&](const StepGroup& u) {
+        GemmFp4Args g = product_args(u, next_mask, rot, acc32);
+        g.a = tiled_operand(u.w->qa_c, u.w->qa_s, u.m, u.m, rec(u.w->rec_a));
+        g.b = tiled_operand(u.w->qxt_c, u.w->qxt_s, u.n, u.m, rec(u.w->rec_xt));
+        g.M = u.m; g.N = u.n; g.K = u.m;
+        g.slot_a = kSlotB; g.slot_b = xm;
+        g.out = u.x; g.out_bstride = u.bstride; g.aux = u.x;
+        g.ca = u.a;
+        g.amax_row_slot = nxn; g.amax_col_slot = nxm;
+        if (u.fin) {
+          g.amax_row_slot = g.amax_col_slot = -1;   // last step: no amaxes needed
+          g.batch = fin.count;
+          g.sc += first;
+          advance(g.a, first);
+          advance(g.b, first);
+          g.out += first * g.out_bstride;
+          g.aux += first * g.out_bstride;
+        }
+        return g;
+      }, st, sg.fin ? &fin : nullptr);
+      if (rc != FP4ROOT_OK) return rc;
+    }
   }
   return FP4ROOT_OK;
 }
@@ -456,24 +477,21 @@ std::vector<Group> make_groups(const fp4root_matrix* mats, int64_t count) {
   return groups;
 }
 
-int64_t row_tiles(int64_t rows) { return (rows + kPrepRowsPerBlock - 1) / kPrepRowsPerBlock; }
-int64_t sq_tiles(int64_t rows, int64_t cols) { return ((rows + 63) / 64) * ((cols + 63) / 64); }
-
-// Fill a chunk of up to kMaxChunk matrices; `square` selects 64 x 64 tiles,
-// otherwise blocks of kPrepRowsPerBlock rows.
-MatChunk make_chunk(const std::vector<MatDesc>& all, size_t first, size_t count, bool square) {
+// The chunk of `count` matrices of a list from `first` on (canonical shape m x n, quantile
+// index and fraction as given).
+MatChunk make_chunk(const std::vector<MatRef>& all, size_t first, size_t count, int64_t m, int64_t n, int64_t lo,
+                    double frac) {
   MatChunk ch;
   std::memset(&ch, 0, sizeof(ch));
   ch.count = (int)count;
-  int64_t tiles = 0;
-  for (size_t i = 0; i < count; ++i) {
-    ch.m[i] = all[first + i];
-    ch.m[i].tile_begin = tiles;
-    tiles += square ? sq_tiles(ch.m[i].rows, ch.m[i].cols) : row_tiles(ch.m[i].rows);
-  }
-  ch.total_tiles = tiles;
+  ch.rows = m;
+  ch.cols = n;
+  ch.lo = lo;
+  ch.frac = frac;
+  for (size_t i = 0; i < count; ++i) ch.m[i] = all[first + i];
   return ch;
 }
+size_t chunk_hist_words(int64_t batch) { return (size_t)std::min<int64_t>(batch, kMaxChunk) * 2 * kHistBins; }
 
 void quantile_index(int64_t n, float q, int64_t& lo, double& frac) {
   const double h = (double)q * (double)(n - 1);
@@ -488,22 +506,25 @@ struct GroupWs {
   uint32_t* hist = nullptr;
   double* partial = nullptr;
   uint32_t* partial_cnt = nullptr;
+  uint32_t* cand_cnt = nullptr;
 };
 
-void carve_group(Carver& cv, const Group& gr, const fp4root_matrix* mats, bool bf16, GroupWs& w) {
+void carve_group(Carver& cv, const Group& gr, bool bf16, GroupWs& w) {
   const int64_t B = (int64_t)gr.members.size();
   carve_step(cv, B, gr.m, gr.n, bf16, w.step);
   w.X = cv.take<float>((size_t)(B * gr.m * gr.n));
-  w.hist = cv.take<uint32_t>((size_t)std::min<int64_t>(B, kMaxChunk) * 2 * kHistBins);
-  int64_t maxp = 0;
-  for (size_t c0 = 0; c0 < gr.members.size(); c0 += kMaxChunk) {
-    int64_t p = 0;
-    for (size_t i = c0; i < std::min(gr.members.size(), c0 + kMaxChunk); ++i)
-      p += row_tiles(mats[gr.members[i]].rows);
-    maxp = std::max(maxp, p);
+  w.hist = cv.take<uint32_t>(chunk_hist_words(B));
+  // tiles of the largest chunk (a smaller one may cut its matrices finer)
+  const int64_t quads = gr.m * gr.n / 4, last = B % kMaxChunk;
+  int64_t tiles = 0;
+  for (int64_t c : {std::min<int64_t>(B, kMaxChunk), last}) {
+    if (c == 0) continue;
+    const int64_t t = hist_tiles(quads, c);
+    tiles = std::max(tiles, t * c);
   }
-  w.partial = cv.take<double>((size_t)maxp);
-  w.partial_cnt = cv.take<uint32_t>((size_t)maxp);
+  w.partial = cv.take<double>((size_t)tiles * 2);
+  w.partial_cnt = cv.take<uint32_t>((size_t)tiles * 2);
+  w.cand_cnt = cv.take<uint32_t>((size_t)tiles * 4);
 }
 
 int validate_matrices(const fp4root_matrix* mats, int64_t count) {
@@ -513,6 +534,7 @@ int validate_matrices(const fp4root_matrix* mats, int64_t count) {
     if (!a.in || !a.out) return FP4ROOT_ERR_INVALID_ARG;
     if (!dims_ok(a.rows, a.cols)) return FP4ROOT_ERR_SHAPE;
     if (a.ld_in < a.cols || a.ld_out < a.cols || a.ld_in % 4 || a.ld_out % 4) return FP4ROOT_ERR_SHAPE;
+    if (a.ld_in > kMaxLd || a.ld_out > kMaxLd) return FP4ROOT_ERR_SHAPE;
     if (!aligned(a.in, 16) || !aligned(a.out, 16)) return FP4ROOT_ERR_INVALID_ARG;
     if ((const void*)a.in == (const void*)a.out && a.ld_in != a.ld_out) return FP4ROOT_ERR_INVALID_ARG;
   }
@@ -546,10 +568,10 @@ size_t orthogonalize_ws_size(const fp4root_matrix* mats, int64_t count, const fp
     if (bf16) {
       Carver cv(nullptr);
       cv.off = kAlign;
-      carve_group(cv, gr, mats, bf16, w);
+      carve_group(cv, gr, bf16, w);
       need = std::max(need, cv.off);
     } else {
-      carve_group(all, gr, mats, bf16, w);
+      carve_group(all, gr, bf16, w);
       need = std::max(need, all.off);
     }
   }
@@ -561,13 +583,13 @@ size_t orthogonalize_ws_size(const fp4root_matrix* mats, int64_t count, const fp
 // ---------------------------------------------------------------------------
 // Fixed scratch of fp4root_quantize_noalloc: a file-scope device array, one copy
 // per GPU, shared by every call on that GPU (overlapping calls on one GPU race).
-// Its largest use is fp4root_quantize_workspace for kNoAllocMaxBatch matrices
-// with clipping (the status word, the per-matrix scalars and the radix histograms
-// of one chunk of matrices).
+// Its largest use is kNoAllocMaxBatch matrices with clipping (the status word, the
+// per-matrix scalars and the radix histograms of one chunk of matrices).
 constexpr int64_t kNoAllocMaxBatch = 256;
+constexpr int kNoAllocChunk = 32;
 constexpr size_t kNoAllocScratchBytes =
     kAlign + (kNoAllocMaxBatch * sizeof(MatScalars) + kAlign - 1) / kAlign * kAlign +
-    (size_t)kMaxChunk * 2 * kHistBins * sizeof(uint32_t);
+    (size_t)kNoAllocChunk * 2 * kHistBins * sizeof(uint32_t);
 static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes];
 
 namespace {
@@ -667,13 +689,25 @@ int fp4root_device_status(const void* ws, void* stream) {
   return FP4ROOT_OK;
 }
 
+namespace {
+// Count words of the clip passes' segments (4 per tile of the largest chunk).
+int64_t quantize_cand_counts(int64_t batch, int64_t rows, int64_t cols) {
+  if (batch <= 0 || rows <= 0 || cols <= 0) return 0;
+  const int64_t quads = rows * cols / 4, full = std::min<int64_t>(batch, kMaxChunk), last = batch % kMaxChunk;
+  const int64_t t = hist_tiles(quads, full) * full;
+  return 4 * (last ? std::max(t, hist_tiles(quads, last) * last) : t);
+}
+}  // namespace
+
 size_t fp4root_quantize_workspace(int64_t batch, int64_t rows, int64_t cols, uint32_t flags) {
-  (void)rows; (void)cols;
   if (batch < 0) return 0;
   Carver cv(nullptr);
   cv.off = kAlign;
   cv.take<MatScalars>((size_t)batch);
-  if (flags & FP4ROOT_F_CLIP) cv.take<uint32_t>((size_t)std::min<int64_t>(batch, kMaxChunk) * 2 * kHistBins);
+  if (flags & FP4ROOT_F_CLIP) {
+    cv.take<uint32_t>(chunk_hist_words(batch));
+    cv.take<uint32_t>((size_t)quantize_cand_counts(batch, rows, cols));
+  }
   return cv.off;
 }
 
@@ -695,31 +729,41 @@ int check_quantize(const float* x, int64_t batch, int64_t rows, int64_t cols, in
 }
 
 // The launches of fp4root_quantize (arguments checked, batch > 0) on the scratch
-// memory at ws (at least fp4root_quantize_workspace bytes); every part of it that
-// must start at zero is cleared by a kernel first.
+// memory at ws: with `collect` fp4root_quantize_workspace bytes, otherwise
+// noalloc_scratch_bytes (the clip passes then read the matrix three times, in chunks of
+// kNoAllocChunk).  Every part that must start at zero is cleared by a kernel first.
 int quantize_launch(const float* x, int64_t batch, int64_t rows, int64_t cols, int64_t ld, int64_t batch_stride,
                     int axis, uint32_t flags, float clip_quantile, uint64_t seed, int32_t step, uint8_t* codes,
-                    uint8_t* scales, float* tensor_scale, float* clip_threshold, void* ws, hipStream_t st) {
+                    uint8_t* scales, float* tensor_scale, float* clip_threshold, void* ws, bool collect,
+                    hipStream_t st) {
   const bool clip = flags & FP4ROOT_F_CLIP;
+  const size_t chunk = collect ? kMaxChunk : kNoAllocChunk;
+  const size_t hist_words = std::min((size_t)batch, chunk) * 2 * kHistBins;
   Carver cv(ws);
   uint32_t* status = cv.take<uint32_t>(1);
   MatScalars* sc = cv.take<MatScalars>((size_t)batch);
-  uint32_t* hist = clip ? cv.take<uint32_t>((size_t)std::min<int64_t>(batch, kMaxChunk) * 2 * kHistBins) : nullptr;
-  FP4R_TRY(launch_fill_u32(status, 0u, 1, st));
-  FP4R_TRY(launch_reset_scalars(sc, batch, ~0u, true, st));
+  uint32_t* hist = clip ? cv.take<uint32_t>(hist_words) : nullptr;
+  uint32_t* cnt = clip && collect ? cv.take<uint32_t>((size_t)quantize_cand_counts(batch, rows, cols)) : nullptr;
+  FP4R_TRY(launch_init(status, sc, batch, hist, clip ? (int64_t)hist_words : 0, st));
   if (clip) {
-    std::vector<MatDesc> all((size_t)batch);
-    for (int64_t b = 0; b < batch; ++b) {
-      MatDesc& d = all[(size_t)b];
-      std::memset(&d, 0, sizeof(d));
-      d.in = x + b * batch_stride;
-      d.rows = rows; d.cols = cols; d.ld_in = ld;
-      quantile_index(rows * cols, clip_quantile, d.lo, d.frac);
-    }
-    for (size_t c0 = 0; c0 < all.size(); c0 += kMaxChunk) {
-      const size_t cnt = std::min(all.size() - c0, (size_t)kMaxChunk);
-      const MatChunk ch = make_chunk(all, c0, cnt, false);
-      FP4R_TRY(launch_clip_threshold(ch, sc + c0, hist, status, st));
+    int64_t lo;
+    double frac;
+    quantile_index(rows * cols, clip_quantile, lo, frac);
+    std::vector<MatRef> all((size_t)batch);
+    for (int64_t b = 0; b < batch; ++b) all[(size_t)b] = MatRef{x + b * batch_stride, nullptr, (uint32_t)(ld / 4), 0u};
+    for (size_t c0 = 0; c0 < all.size(); c0 += chunk) {
+      const size_t cnt_mats = std::min(all.size() - c0, chunk);
+      const MatChunk ch = make_chunk(all, c0, cnt_mats, rows, cols, lo, frac);
+      ClipScratch cs;
+      cs.hist = hist;
+      if (collect) {
+        // segments in the code output, written by the encoder later: half a byte per element
+        cs.cand = reinterpret_cast<float*>(codes + (int64_t)c0 * (rows * cols / 2));
+        cs.cand_stride = rows * cols / 8;
+        cs.cand_shift = 3;
+        cs.cnt = cnt;
+      }
+      FP4R_TRY(launch_clip_threshold(ch, sc + c0, status, cs, 0.0f, st));
     }
   }
   const Batch in{x, batch, rows, cols, ld, batch_stride};
@@ -727,8 +771,7 @@ int quantize_launch(const float* x, int64_t batch, int64_t rows, int64_t cols, i
   const bool rot = flags & FP4ROOT_F_HADAMARD, ad = flags & FP4ROOT_F_ADAPTIVE46;
   const uint32_t mask = sign_mask(seed, step);
   FP4R_TRY(launch_amax(in, axis, mask, rot, clip, sc, 0, status, st));
-  FP4R_TRY(launch_encode(in, axis, mask, rot, clip, ad, sc, 0, q, tensor_scale, st));
-  if (clip_threshold) FP4R_TRY(launch_export_scalar(sc, batch, 0, 0, clip_threshold, st));
+  FP4R_TRY(launch_encode(in, axis, mask, rot, clip, ad, sc, 0, q, tensor_scale, st, clip_threshold));
   return FP4ROOT_OK;
 }
 }  // namespace
@@ -744,7 +787,7 @@ int fp4root_quantize(const float* x, int64_t batch, int64_t rows, int64_t cols, 
   if (!ws || ws_bytes < fp4root_quantize_workspace(batch, rows, cols, flags)) return FP4ROOT_ERR_WORKSPACE;
   if (batch == 0) return FP4ROOT_OK;
   return quantize_launch(x, batch, rows, cols, ld, batch_stride, axis, flags, clip_quantile, seed, step, codes,
-                         scales, tensor_scale, clip_threshold, ws, (hipStream_t)stream);
+                         scales, tensor_scale, clip_threshold, ws, true, (hipStream_t)stream);
 }
 
 size_t fp4root_momentum_workspace(int64_t batch, int64_t rows, int64_t cols) {
@@ -781,8 +824,7 @@ int momentum_update_launch(const float* g, float* m, int64_t batch, int64_t rows
   const bool rot = flags & FP4ROOT_F_HADAMARD, ad = flags & FP4ROOT_F_ADAPTIVE46;
   const float b1 = beta, b2 = 1.0f - beta;   // b2 = fl32(1 - beta)
   const uint32_t mask = sign_mask(seed, step), prev_mask = step > 0 ? sign_mask(seed, step - 1) : 0u;
-  if (reset_status) FP4R_TRY(launch_fill_u32(status, 0u, 1, st));
-  FP4R_TRY(launch_reset_scalars(sc, batch, ~0u, true, st));
+  FP4R_TRY(launch_init(reset_status ? status : nullptr, sc, batch, nullptr, 0, st));
   FP4R_TRY(launch_mom_update(g, m, batch, rows, cols, codes, scales, tensor_scale, step > 0, prev_mask,
                              mask, rot, b1, b2, sc, status, st));
   const Batch in{m, batch, rows, cols, cols, rows * cols};
@@ -863,8 +905,7 @@ int fp4root_qadamw_update(uint16_t* w, const float* g, float* m, int64_t n, uint
   };
   const bool rot = flags & FP4ROOT_F_HADAMARD, ad = flags & FP4ROOT_F_ADAPTIVE46;
   const uint32_t mask = sign_mask(seed, step), prev_mask = step > 0 ? sign_mask(seed, step - 1) : 0u;
-  FP4R_TRY(launch_fill_u32(status, 0u, 1, st));
-  FP4R_TRY(launch_reset_scalars(sc, 1, ~0u, true, st));
+  FP4R_TRY(launch_init(status, sc, 1, nullptr, 0, st));
   // pass 1: first moment (read only), its rotated amax, second moment and weights
   QAdamWLaunch q;
   q.w = w; q.g = g; q.m_out = m; q.mcodes = m_codes; q.mscales = m_scales; q.m_prev_sg = m_tensor_scale;
@@ -1010,8 +1051,7 @@ int fp4root_ns_step(float* x, int64_t batch, int64_t m, int64_t n, int64_t batch
   uint32_t* status = cv.take<uint32_t>(1);
   StepWs w;
   carve_step(cv, batch, m, n, bf16, w);
-  FP4R_TRY(launch_fill_u32(status, 0u, 1, st));
-  FP4R_TRY(launch_reset_scalars(w.sc, batch, ~0u, true, st));
+  FP4R_TRY(launch_init(status, w.sc, batch, nullptr, 0, st));
   if (bf16) {
     if (batch_stride != m * n && batch > 1) return FP4ROOT_ERR_UNSUPPORTED;
     FP4R_TRY(launch_cast_bf16(x, batch, m, n, batch_stride, w.xb, st));
@@ -1028,14 +1068,14 @@ int fp4root_quantize_noalloc(const float* x, int64_t batch, int64_t rows, int64_
   const int rc = check_quantize(x, batch, rows, cols, ld, batch_stride, axis, flags, clip_quantile, codes, scales,
                                 tensor_scale);
   if (rc != FP4ROOT_OK) return rc;
-  if (fp4root_quantize_workspace(batch, rows, cols, flags) > kNoAllocScratchBytes) return FP4ROOT_ERR_WORKSPACE;
+  if (batch > kNoAllocMaxBatch) return FP4ROOT_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)stream;
   void* ws = nullptr;
   const int rs = scratch_address(&ws);
   if (rs != FP4ROOT_OK) return rs;
   if (batch > 0)
     FP4R_TRY_RC(quantize_launch(x, batch, rows, cols, ld, batch_stride, axis, flags, clip_quantile, seed, step,
-                                codes, scales, tensor_scale, clip_threshold, ws, st));
+                                codes, scales, tensor_scale, clip_threshold, ws, false, st));
   else
     FP4R_TRY(launch_fill_u32(reinterpret_cast<uint32_t*>(ws), 0u, 1, st));
   // the status word is the scratch's first word (see quantize_launch)
@@ -1059,48 +1099,56 @@ int orthogonalize_launch(const fp4root_matrix* mats, int64_t count, const fp4roo
   const bool bf16 = cfg->flags & FP4ROOT_F_BF16_PATH;
   const bool clip = cfg->flags & FP4ROOT_F_CLIP;
   uint32_t* status = reinterpret_cast<uint32_t*>(ws);
-  if (reset_status) FP4R_TRY(launch_fill_u32(status, 0u, 1, st));
-  if (count == 0) return FP4ROOT_OK;
+  if (count == 0) return reset_status && launch_fill_u32(status, 0u, 1, st) != hipSuccess ? FP4ROOT_ERR_HIP : FP4ROOT_OK;
   const std::vector<Group> groups = make_groups(mats, count);
   const size_t ng = groups.size();
 
   // per group: descriptors, workspace, coefficients, output route
   std::vector<GroupWs> gw(ng);
-  std::vector<std::vector<MatDesc>> gall(ng);
+  std::vector<std::vector<MatRef>> gall(ng);
   std::vector<std::vector<float>> gco(ng);
-  std::vector<MatChunk> gout(ng);
-  std::vector<char> gfused(ng, 0);
+  std::vector<std::vector<MatChunk>> gout(ng);   // chunks of the last update's outputs
   Carver shared(ws);   // NVFP4: every group's workspace side by side
   shared.off = kAlign;
   auto prepare = [&](size_t gi) -> int {
     const Group& gr = groups[gi];
     const int64_t B = (int64_t)gr.members.size(), m = gr.m, n = gr.n;
     GroupWs& w = gw[gi];
-    std::vector<MatDesc>& all = gall[gi];
+    std::vector<MatRef>& all = gall[gi];
     all.resize((size_t)B);
     for (int64_t i = 0; i < B; ++i) {
       const fp4root_matrix& a = mats[gr.members[(size_t)i]];
-      MatDesc& d = all[(size_t)i];
-      std::memset(&d, 0, sizeof(d));
-      d.in = a.in; d.out = a.out;
-      d.rows = a.rows; d.cols = a.cols; d.ld_in = a.ld_in; d.ld_out = a.ld_out;
-      quantile_index(a.rows * a.cols, cfg->clip_quantile, d.lo, d.frac);
+      all[(size_t)i] = MatRef{a.in, a.out, (uint32_t)(a.ld_in / 4),
+                              (uint32_t)(a.ld_out / 4) | (a.rows > a.cols ? 0x80000000u : 0u)};
     }
-    FP4R_TRY(launch_reset_scalars(w.step.sc, B, ~0u, true, st));
+    int64_t lo = 0;
+    double frac = 0.0;
+    if (clip) quantile_index(m * n, cfg->clip_quantile, lo, frac);
+    FP4R_TRY(launch_init(reset_status && gi == 0 ? status : nullptr, w.step.sc, B, w.hist,
+                         clip ? (int64_t)chunk_hist_words(B) : 0, st));
     // clip, normalise, orient
     for (size_t c0 = 0; c0 < all.size(); c0 += kMaxChunk) {
       const size_t cnt = std::min(all.size() - c0, (size_t)kMaxChunk);
-      const MatChunk rows_ch = make_chunk(all, c0, cnt, false);
-      const MatChunk tile_ch = make_chunk(all, c0, cnt, true);
-      // with clipping, the last radix pass also yields the norm of the clipped matrix
-      if (clip)
-        FP4R_TRY(launch_clip_threshold(rows_ch, w.step.sc + c0, w.hist, status, st, w.partial,
-                                       w.partial_cnt, cfg->eps));
-      else
-        FP4R_TRY(launch_inv_norm(rows_ch, w.step.sc + c0, w.partial, cfg->eps, status, st));
-      FP4R_TRY(launch_prep_copy(tile_ch, w.step.sc + c0, w.X + (int64_t)c0 * m * n, m * n,
-                                sign_mask(cfg->seed, 0), cfg->flags & FP4ROOT_F_HADAMARD, kSlotXn,
-                                kSlotXm, st));
+      const MatChunk ch = make_chunk(all, c0, cnt, m, n, lo, frac);
+      float* const X = w.X + (int64_t)c0 * m * n;
+      // with clipping, the passes also yield the norm of the clipped matrix; they collect
+      // elements in X, which the copy overwrites
+      if (clip) {
+        ClipScratch cs;
+        cs.hist = w.hist;
+        cs.cand = X;
+        cs.cand_stride = m * n;
+        cs.cnt = w.cand_cnt;
+        cs.psum = w.partial;
+        cs.pcnt = w.partial_cnt;
+        FP4R_TRY(launch_clip_threshold(ch, w.step.sc + c0, status, cs, cfg->eps, st));
+      } else {
+        FP4R_TRY(launch_inv_norm(ch, w.step.sc + c0, w.partial, cfg->eps, status, st));
+      }
+      FP4R_TRY(launch_prep_copy(ch, w.step.sc + c0, X, m * n, sign_mask(cfg->seed, 0),
+                                cfg->flags & FP4ROOT_F_HADAMARD, kSlotXn, kSlotXm, st));
+      // the last update is written straight to the callers' matrices
+      if (!bf16 && cfg->steps > 0) gout[gi].push_back(ch);
     }
     std::vector<float>& co = gco[gi];
     co.assign((size_t)std::max(cfg->steps, 1) * 3, 0.0f);
@@ -1108,18 +1156,16 @@ int orthogonalize_launch(const fp4root_matrix* mats, int64_t count, const fp4roo
       std::memcpy(co.data(), cfg->coeffs, sizeof(float) * 3 * (size_t)cfg->steps);
     else
       default_coeffs_impl(m, n, cfg->steps, co.data());
-    // a group of at most kMaxChunk matrices gets its last update written straight to
-    // the callers' matrices; otherwise a copy kernel writes them back afterwards
-    gfused[gi] = !bf16 && cfg->steps > 0 && B <= kMaxChunk;
-    gout[gi] = make_chunk(all, 0, gfused[gi] ? (size_t)B : 0, true);
     return FP4ROOT_OK;
   };
+  // without an update product that writes the outputs (no steps, or the BF16 path)
   auto write_back = [&](size_t gi) -> int {
     const Group& gr = groups[gi];
-    for (size_t c0 = 0; c0 < gall[gi].size() && !gfused[gi]; c0 += kMaxChunk) {
+    if (!gout[gi].empty()) return FP4ROOT_OK;
+    for (size_t c0 = 0; c0 < gall[gi].size(); c0 += kMaxChunk) {
       const size_t cnt = std::min(gall[gi].size() - c0, (size_t)kMaxChunk);
-      const MatChunk tile_ch = make_chunk(gall[gi], c0, cnt, true);
-      FP4R_TRY(launch_copy_out(tile_ch, gw[gi].X + (int64_t)c0 * gr.m * gr.n, gr.m * gr.n, st));
+      const MatChunk ch = make_chunk(gall[gi], c0, cnt, gr.m, gr.n, 0, 0.0);
+      FP4R_TRY(launch_copy_out(ch, gw[gi].X + (int64_t)c0 * gr.m * gr.n, gr.m * gr.n, st));
     }
     return FP4ROOT_OK;
   };
@@ -1131,7 +1177,7 @@ int orthogonalize_launch(const fp4root_matrix* mats, int64_t count, const fp4roo
       const int64_t B = (int64_t)gr.members.size(), m = gr.m, n = gr.n;
       Carver cv(ws);
       cv.off = kAlign;
-      carve_group(cv, gr, mats, bf16, gw[gi]);
+      carve_group(cv, gr, bf16, gw[gi]);
       int rc = prepare(gi);
       if (rc != FP4ROOT_OK) return rc;
       if (cfg->steps > 0) FP4R_TRY(launch_cast_bf16(gw[gi].X, B, m, n, m * n, gw[gi].step.xb, st));
@@ -1148,7 +1194,7 @@ int orthogonalize_launch(const fp4root_matrix* mats, int64_t count, const fp4roo
 
   // NVFP4: every group prepared, then each NS step over all groups at once
   for (size_t gi = 0; gi < ng; ++gi) {
-    carve_group(shared, groups[gi], mats, false, gw[gi]);
+    carve_group(shared, groups[gi], false, gw[gi]);
     const int rc = prepare(gi);
     if (rc != FP4ROOT_OK) return rc;
   }
@@ -1158,7 +1204,7 @@ int orthogonalize_launch(const fp4root_matrix* mats, int64_t count, const fp4roo
       const Group& gr = groups[gi];
       const float* c3 = &gco[gi][3 * (size_t)k];
       sgs[gi] = StepGroup{gw[gi].X, (int64_t)gr.members.size(), gr.m, gr.n, gr.m * gr.n, &gw[gi].step,
-                          c3[0], c3[1], c3[2], gfused[gi] && k == cfg->steps - 1 ? &gout[gi] : nullptr};
+                          c3[0], c3[1], c3[2], k == cfg->steps - 1 ? &gout[gi] : nullptr};
     }
     const int rc = run_step_fp4(sgs.data(), (int)ng, cfg->flags, cfg->seed, k, 2 * (k & 1), false, status,
                                 nullptr, st);

@@ -11,23 +11,42 @@ namespace fp4r {
 constexpr uint32_t kStatusNonFinite = 1u;
 
 // ---------------------------------------------------------------------------
-// Matrix lists for the stages that read caller matrices (clipping, copies).
-constexpr int kMaxChunk = 32;
+// Matrix lists for the stages that read caller matrices (clipping, copies): up to
+// kMaxChunk matrices of one canonical shape m x n, passed by value.
+constexpr int kMaxChunk = 128;
 
-struct MatDesc {
-  const float* in;     // caller matrix, row-major
+struct MatRef {
+  const float* in;     // caller matrix, row-major: m x n, or n x m when tall
   float* out;          // caller output (copy-out stage) or nullptr
-  int64_t rows, cols, ld_in, ld_out;
-  int64_t lo;          // quantile order statistic index floor(q (N - 1))
-  double frac;         // q (N - 1) - lo
-  int64_t tile_begin;  // first flat block index of this matrix in a launch
+  uint32_t ld_in4;     // row strides in 16-byte units
+  uint32_t ld_out4;    // bit 31: tall
+  __host__ __device__ bool tall() const { return ld_out4 >> 31; }
+  __host__ __device__ int64_t ld_in() const { return (int64_t)ld_in4 * 4; }
+  __host__ __device__ int64_t ld_out() const { return (int64_t)(ld_out4 & 0x7FFFFFFFu) * 4; }
 };
 
 struct MatChunk {
-  MatDesc m[kMaxChunk];
+  MatRef m[kMaxChunk];
+  int64_t rows, cols;    // canonical shape (a tall matrix is stored cols x rows)
+  int64_t lo;            // quantile order statistic index floor(q (N - 1))
+  double frac;           // q (N - 1) - lo
   int count;
-  int64_t total_tiles;
 };
+
+// The clip passes cut a matrix into tiles of this many 16-byte quads (a power of two): at
+// most 1024 workgroups per matrix, since each ends with atomic adds to the same few
+// histogram bins (first pass on one 4096 x 4096: 28 us with 1024, 82 with 4096), and at
+// most 4096 in all (the second pass, which issues the most instructions per element, on 12
+// matrices of 25 M elements: 364, 212, 140 and 127 us per launch with 512 .. 4096).
+inline int64_t hist_tile_quads(int64_t quads, int64_t count) {
+  int64_t q = 512;
+  while (quads > q * 1024 || quads * count > q * 4096) q *= 2;
+  return q;
+}
+inline int64_t hist_tiles(int64_t quads, int64_t count) {
+  const int64_t q = hist_tile_quads(quads, count);
+  return (quads + q - 1) / q;
+}
 
 // Per-matrix scalars kept in the workspace (one struct per matrix).
 // Amax records are maxima over many workgroups.  To keep same-address atomics
@@ -71,26 +90,41 @@ constexpr int kNumSlots = 6;
 
 // Radix select histogram: [2 ranks][2048 bins] per matrix.
 constexpr int kHistBins = 2048;
-constexpr int kPrepRowsPerBlock = 8;
 
 // ---------------------------------------------------------------------------
 // Launchers (all asynchronous on `st`; return hipSuccess or the launch error).
 
 hipError_t launch_fill_u32(uint32_t* p, uint32_t value, int64_t n, hipStream_t st);
 
-// Quantile of |x| per matrix in the chunk; writes sc[i].tau (ranks lo, lo+1).
-// hist: chunk.count * 2 * kHistBins words of scratch.  status: device word.
-// With psum / pcnt (chunk.total_tiles doubles / words of scratch) it also writes
-// sc[i].inv_norm = fl32(1/(||clamp(M, tau)|| + eps)), as launch_inv_norm does.
-hipError_t launch_clip_threshold(const MatChunk& ch, MatScalars* sc, uint32_t* hist,
-                                 uint32_t* status, hipStream_t st, double* psum = nullptr,
-                                 uint32_t* pcnt = nullptr, float eps = 0.0f);
+// Start of a call: zero the status word (may be null), reset n scalar records (amaxes and
+// tensor scales 0, tau +inf, inv_norm 1) and zero hist_words words of hist.
+hipError_t launch_init(uint32_t* status, MatScalars* sc, int64_t n, uint32_t* hist, int64_t hist_words,
+                       hipStream_t st);
+
+// Scratch of the clip threshold beside the histograms (which must be zero on entry and
+// are zero again afterwards): with `cand` (per matrix cand_stride floats, 2^-cand_shift
+// of its elements at least) the second pass collects the elements that may still hold
+// the order statistics and the last pass reads only those; cnt: 4 words per tile.  With
+// psum / pcnt (2 tiles doubles / words per matrix; cand needed) it also
+// writes inv_norm = fl32(1/(||clamp(M, tau)|| + eps)), as launch_inv_norm does.
+struct ClipScratch {
+  uint32_t* hist = nullptr;   // count * 2 * kHistBins words
+  float* cand = nullptr;
+  int64_t cand_stride = 0;
+  int cand_shift = 0;
+  uint32_t* cnt = nullptr;
+  double* psum = nullptr;
+  uint32_t* pcnt = nullptr;
+};
+// Quantile of |x| per matrix in the chunk; writes sc[i].tau.  status: device word.
+hipError_t launch_clip_threshold(const MatChunk& ch, MatScalars* sc, uint32_t* status, const ClipScratch& w, float eps,
+                                 hipStream_t st);
 
 // *out = 0, or -4 (non-finite input seen) from the status word *status.
 hipError_t launch_status_out(const uint32_t* status, int32_t* out, hipStream_t st);
 
 // Frobenius norm of the clipped matrices: sc[i].inv_norm = fl32(1/(||.|| + eps)).
-// partial: chunk.total_tiles doubles of scratch.  A NaN or infinite entry sets
+// partial: hist_tiles doubles per matrix of scratch.  A NaN or infinite entry sets
 // kStatusNonFinite in *status.
 hipError_t launch_inv_norm(const MatChunk& ch, MatScalars* sc, double* partial, float eps,
                            uint32_t* status, hipStream_t st);
@@ -181,10 +215,10 @@ hipError_t launch_amax_x2(const float* x, int64_t batch, int64_t m, int64_t n, i
                           bool rotate, MatScalars* sc, int slot_n, int slot_m, uint32_t* status, hipStream_t st);
 
 // Encode with the tensor scale derived from amax slot `slot` of sc[b]; writes sc[b].sg[slot]
-// and, when tensor_scale != nullptr, tensor_scale[b].
+// and, when tensor_scale != nullptr, tensor_scale[b] (tau_out likewise: the clip threshold).
 hipError_t launch_encode(const Batch& in, int axis, uint32_t sign_mask, bool rotate, bool clip,
                          bool adaptive46, MatScalars* sc, int slot, const QOut& out,
-                         float* tensor_scale, hipStream_t st);
+                         float* tensor_scale, hipStream_t st, float* tau_out = nullptr);
 
 // The operand Q1x16 of a batch of contiguous rows x K matrices (row blocks), with the
 // tensor scale from amax slot `slot`; writes sc[b].sg[slot].
@@ -246,7 +280,7 @@ hipError_t launch_qadamw(const QAdamWLaunch& p, hipStream_t st);
 // Both quantisations of X (m x n, row stride n) from one read: qX along n into
 // qx (slot_n), qXt along m into qxt (slot_m, stored transposed).
 // reset_mask: amax slots of every matrix set to zero by the launch (for the
-// products that run after it; never slot_n or slot_m), as launch_reset_scalars does.
+// products that run after it; never slot_n or slot_m).
 hipError_t launch_encode_x2(const float* x, int64_t batch, int64_t m, int64_t n, int64_t x_bstride,
                             uint32_t sign_mask, bool rotate, bool adaptive46, MatScalars* sc,
                             int slot_n, int slot_m, const OperandOut& qx, const OperandOut& qxt, hipStream_t st,
@@ -350,10 +384,6 @@ hipError_t launch_bf16_update_blaslt(const uint16_t* b16, const uint16_t* xb, fl
 // matrix stride x_bstride; Xb contiguous (stride m*n).
 hipError_t launch_cast_bf16(const float* x, int64_t batch, int64_t m, int64_t n, int64_t x_bstride,
                             uint16_t* xb, hipStream_t st);
-
-// Zero the amax slots selected by `slot_mask` (bit i = slot i) of n scalar
-// records; `full` also resets every tensor scale, tau (+inf) and inv_norm (1).
-hipError_t launch_reset_scalars(MatScalars* sc, int64_t n, uint32_t slot_mask, bool full, hipStream_t st);
 
 // out[i] = sc[i].tau (which = 0) or sc[i].sg[slot] (which = 1).
 hipError_t launch_export_scalar(const MatScalars* sc, int64_t n, int which, int slot, float* out,

@@ -22,307 +22,410 @@ hipError_t launch_fill_u32(uint32_t* p, uint32_t value, int64_t n, hipStream_t s
   return hipGetLastError();
 }
 
-FP4R_DEV int find_matrix(const MatChunk& ch, int64_t tile) {
-  int mi = 0;
-  for (int i = 1; i < ch.count; ++i)
-    if (ch.m[i].tile_begin <= tile) mi = i;
-  return mi;
-}
-
-// ---------------------------------------------------------------------------
-// Clip threshold: tau = fl32(v[lo] + f (v[lo+1] - v[lo])) over the sorted |M|,
-// found with a three-pass radix select on the binary32 bit patterns (31-bit keys,
-// digits of 11, 10 and 10 bits).  Both ranks are tracked in the same passes.
-//
-// The last pass can also give the Frobenius norm of clamp(M, tau): by then the
-// 21-bit key prefixes p0 <= p1 of v[lo] and v[lo+1] are known, tau lies between
-// the two, and no element lies strictly between them, so an element whose prefix
-// is below p0 is not clipped (its square goes into a binary64 partial of the
-// block), one above p1 is clipped to tau (it is only counted), and the elements
-// with prefix p0 or p1 are exactly the pass's histograms (a key is the bit
-// pattern of |x|), which the select step sums in bin order once tau is known.
-
-__global__ void k_clip_init(MatChunk ch, MatScalars* sc) {
-  const int i = threadIdx.x;
-  if (i >= ch.count) return;
-  const MatDesc& d = ch.m[i];
-  const int64_t n = d.rows * d.cols;
-  MatScalars& s = sc[i];
-  s.sel_prefix[0] = s.sel_prefix[1] = 0;
-  s.sel_rank[0] = (uint32_t)d.lo;
-  s.sel_rank[1] = (uint32_t)(d.lo + 1 < n ? d.lo + 1 : d.lo);
-}
-
-__global__ __launch_bounds__(256) void k_radix_hist(MatChunk ch, const MatScalars* sc,
-                                                    uint32_t* hist, uint32_t* status, int pass,
-                                                    double* psum, uint32_t* pcnt) {
-  __shared__ uint32_t h[2][kHistBins];
-  __shared__ double red[256];
-  __shared__ uint32_t above_all;
-  for (int i = threadIdx.x; i < 2 * kHistBins; i += 256) (&h[0][0])[i] = 0;
-  __syncthreads();
-  const int64_t tile = blockIdx.x;
-  const int mi = find_matrix(ch, tile);
-  const MatDesc& d = ch.m[mi];
-  const int64_t r0 = (tile - d.tile_begin) * kPrepRowsPerBlock;
-  const int64_t r1 = r0 + kPrepRowsPerBlock < d.rows ? r0 + kPrepRowsPerBlock : d.rows;
-  const uint32_t p0 = sc[mi].sel_prefix[0], p1 = sc[mi].sel_prefix[1];
-  const bool two = pass > 0 && p0 != p1;
-  const int pshift = pass == 1 ? 20 : 10;
-  const bool norm = pass == 2 && psum != nullptr;
-  double acc = 0.0;     // squares of the elements below prefix p0, in this thread's order
-  uint32_t above = 0;   // elements above prefix p1
-  if (threadIdx.x == 0) above_all = 0;
-  bool bad = false;
-  // The block's rows as one sequence of 16-byte quads (row r, quad c), thread t taking
-  // quads t, t + 256, ...; four loads are issued before any is used.
-  const uint32_t c4 = (uint32_t)(d.cols / 4);
-  const uint32_t nq = (uint32_t)(r1 - r0) * c4;
-  uint32_t rr = threadIdx.x / c4, cc = threadIdx.x - rr * c4;   // position of quad threadIdx.x
-  auto step = [&]() {   // advance by 256 quads
-    cc += 256u;
-    while (cc >= c4) {
-      cc -= c4;
-      ++rr;
-    }
-  };
-  for (uint32_t q0 = threadIdx.x; q0 < nq; q0 += 1024u) {
-    float4 v[4];
+__global__ __launch_bounds__(256) void k_init(uint32_t* status, MatScalars* sc, int64_t n, uint4* hist,
+                                              int64_t hist_quads) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i == 0 && status) *status = 0u;
+  if (i < n) {
+    MatScalars& s = sc[i];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      v[u] = q0 + 256u * u < nq ? reinterpret_cast<const float4*>(d.in + (r0 + rr) * d.ld_in)[cc]
-                                : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-      step();
-    }
+    for (int l = 0; l < kAmaxSpread; ++l)
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      if (q0 + 256u * u >= nq) break;
-      const float e[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+      for (int k = 0; k < kNumSlots; ++k) s.amax[l].v[k] = 0u;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const uint32_t key = __float_as_uint(e[j]) & 0x7FFFFFFFu;
-        if (key >= 0x7F800000u) { bad = true; continue; }
-        uint32_t digit;
-        if (pass == 0) {
-          atomicAdd(&h[0][key >> 20], 1u);
-          continue;
-        }
-        digit = pass == 1 ? ((key >> 10) & 1023u) : (key & 1023u);
-        const uint32_t pre = key >> pshift;
-        if (pre == p0) atomicAdd(&h[0][digit], 1u);
-        if (two && pre == p1) atomicAdd(&h[1][digit], 1u);
-        if (norm) {
-          if (pre < p0) {
-            const double x = (double)e[j];
-            acc = acc + x * x;
-          } else if (pre > p1) {
-            ++above;
-          }
-        }
-      }
-    }
+    for (int k = 0; k < kNumSlots; ++k) s.sg[k] = 0.0f;
+    s.tau = __uint_as_float(0x7F800000u);   // +inf: clamping is the identity
+    s.inv_norm = 1.0f;
   }
-  if (bad) atomicOr(status, kStatusNonFinite);
-  if (norm) {
-    red[threadIdx.x] = acc;
-    if (above) atomicAdd(&above_all, above);
-  }
-  __syncthreads();
-  if (norm) {
-    for (int off = 128; off > 0; off >>= 1) {   // fixed-order tree
-      if ((int)threadIdx.x < off) red[threadIdx.x] = red[threadIdx.x] + red[threadIdx.x + off];
-      __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-      psum[tile] = red[0];
-      pcnt[tile] = above_all;
-    }
-  }
-  const int nb = pass == 0 ? 2048 : 1024;
-  for (int b = threadIdx.x; b < nb; b += 256) {
-    if (h[0][b]) atomicAdd(&hist[(mi * 2 + 0) * kHistBins + b], h[0][b]);
-    if (two && h[1][b]) atomicAdd(&hist[(mi * 2 + 1) * kHistBins + b], h[1][b]);
-  }
+  if (i < hist_quads) hist[i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
-__global__ __launch_bounds__(256) void k_radix_select(MatChunk ch, MatScalars* sc, uint32_t* hist,
-                                                      int pass, const double* psum, const uint32_t* pcnt,
-                                                      float eps) {
-  __shared__ uint32_t part[256];
-  __shared__ uint32_t found_prefix[2], found_rank[2];
-  __shared__ double red[256];
-  __shared__ unsigned long long above_all;
-  const int mi = blockIdx.x;
-  const int t = threadIdx.x;
-  MatScalars& s = sc[mi];
-  const int nb = pass == 0 ? 2048 : 1024;
-  const int per = nb / 256;
-  const bool two = pass > 0 && s.sel_prefix[0] != s.sel_prefix[1];
-  for (int rr = 0; rr < 2; ++rr) {
-    const uint32_t* hh = hist + (mi * 2 + (two ? rr : 0)) * kHistBins;
-    uint32_t local = 0;
-    for (int j = 0; j < per; ++j) local += hh[t * per + j];
-    part[t] = local;
-    __syncthreads();
-    for (int off = 1; off < 256; off <<= 1) {   // inclusive Hillis-Steele scan
-      const uint32_t add = t >= off ? part[t - off] : 0u;
-      __syncthreads();
-      part[t] += add;
-      __syncthreads();
-    }
-    const uint32_t incl = part[t];
-    const uint32_t excl = incl - local;
-    const uint32_t target = s.sel_rank[rr];
-    if (target >= excl && target < incl) {   // exactly one thread owns the target rank
-      uint32_t cum = excl;
-      for (int j = 0; j < per; ++j) {
-        const uint32_t c = hh[t * per + j];
-        if (target < cum + c) {
-          const uint32_t bin = (uint32_t)(t * per + j);
-          found_prefix[rr] = pass == 0 ? bin : ((s.sel_prefix[rr] << 10) | bin);
-          found_rank[rr] = target - cum;
-          break;
-        }
-        cum += c;
-      }
-    }
-    __syncthreads();
-  }
-  if (pass == 2 && psum) {
-    // ||clamp(M, tau)||^2 in a fixed order: the blocks' partials below p0, the
-    // elements of the two prefixes from the histograms (bin order), the elements
-    // above p1 at tau^2 each
-    const MatDesc& d = ch.m[mi];
-    const double v0 = (double)__uint_as_float(found_prefix[0]);
-    const double v1 = (double)__uint_as_float(found_prefix[1]);
-    const float tau = (float)__dadd_rn(v0, __dmul_rn(d.frac, __dsub_rn(v1, v0)));
-    if (t == 0) above_all = 0;
-    const int64_t nt = (d.rows + kPrepRowsPerBlock - 1) / kPrepRowsPerBlock;
-    double below = 0.0;
-    unsigned long long above = 0;
-    for (int64_t i = t; i < nt; i += 256) {
-      below = below + psum[d.tile_begin + i];
-      above += pcnt[d.tile_begin + i];
-    }
-    double cand = 0.0;
-    for (int rr = 0; rr < (two ? 2 : 1); ++rr) {
-      const uint32_t* hh = hist + (mi * 2 + rr) * kHistBins;
-      for (int j = 0; j < 4; ++j) {
-        const uint32_t bin = (uint32_t)(4 * t + j), c = hh[bin];
-        if (c) {
-          const double x = (double)fminf(__uint_as_float((s.sel_prefix[rr] << 10) | bin), tau);
-          cand = cand + (double)c * (x * x);
-        }
-      }
-    }
-    __syncthreads();
-    atomicAdd(&above_all, above);
-    red[t] = below;
-    __syncthreads();
-    for (int off = 128; off > 0; off >>= 1) {
-      if (t < off) red[t] = red[t] + red[t + off];
-      __syncthreads();
-    }
-    const double sum_below = red[0];
-    __syncthreads();
-    red[t] = cand;
-    __syncthreads();
-    for (int off = 128; off > 0; off >>= 1) {
-      if (t < off) red[t] = red[t] + red[t + off];
-      __syncthreads();
-    }
-    if (t == 0) {
-      const double tt = (double)tau * (double)tau;
-      const double total = __dadd_rn(__dadd_rn(sum_below, red[0]), __dmul_rn((double)above_all, tt));
-      const double nu = __dsqrt_rn(total);
-      s.inv_norm = (float)__ddiv_rn(1.0, __dadd_rn(nu, (double)eps));
-    }
-    __syncthreads();
-  }
-  for (int b = t; b < 2 * kHistBins; b += 256) hist[mi * 2 * kHistBins + b] = 0u;
-  if (t == 0) {
-    s.sel_prefix[0] = found_prefix[0];
-    s.sel_prefix[1] = found_prefix[1];
-    s.sel_rank[0] = found_rank[0];
-    s.sel_rank[1] = found_rank[1];
-    if (pass == 2) {
-      const double v0 = (double)__uint_as_float(found_prefix[0]);
-      const double v1 = (double)__uint_as_float(found_prefix[1]);
-      const double f = ch.m[mi].frac;
-      s.tau = (float)__dadd_rn(v0, __dmul_rn(f, __dsub_rn(v1, v0)));
-    }
-  }
-}
-
-hipError_t launch_clip_threshold(const MatChunk& ch, MatScalars* sc, uint32_t* hist,
-                                 uint32_t* status, hipStream_t st, double* psum, uint32_t* pcnt,
-                                 float eps) {
-  hipError_t e = launch_fill_u32(hist, 0u, (int64_t)ch.count * 2 * kHistBins, st);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_clip_init, dim3(1), dim3(kMaxChunk), 0, st, ch, sc);
-  for (int pass = 0; pass < 3; ++pass) {
-    hipLaunchKernelGGL(k_radix_hist, dim3((uint32_t)ch.total_tiles), dim3(256), 0, st, ch, sc,
-                       hist, status, pass, psum, pcnt);
-    hipLaunchKernelGGL(k_radix_select, dim3(ch.count), dim3(256), 0, st, ch, sc, hist, pass,
-                       (const double*)psum, (const uint32_t*)pcnt, eps);
-  }
+hipError_t launch_init(uint32_t* status, MatScalars* sc, int64_t n, uint32_t* hist, int64_t hist_words,
+                       hipStream_t st) {
+  const int64_t quads = hist ? hist_words / 4 : 0, threads = n > quads ? n : quads;
+  if (threads <= 0 && !status) return hipSuccess;
+  hipLaunchKernelGGL(k_init, dim3((uint32_t)(threads / 256 + 1)), dim3(256), 0, st, status, sc, n,
+                     reinterpret_cast<uint4*>(hist), quads);
   return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
-// Frobenius norm of clamp(M, tau): per-block binary64 partials in a fixed
-// order, then one fixed-order sum per matrix (deterministic).
+// Clip threshold: tau = fl32(v[lo] + f (v[lo+1] - v[lo])) over the sorted |M|,
+// found with a radix select on the binary32 bit patterns (31-bit keys, digits of 11, 10
+// and 10 bits).  Both ranks are tracked in the same passes.
+//
+// The first pass reads the matrix for the top digit.  The second reads it again for the
+// next digit of the elements with the selected top digits (about half a percent of a
+// heavy-tailed matrix), and each wave also appends those elements to a segment of its
+// own; the last pass reads the segments only (a third full read took as long as each of
+// the others, 119 us of 1070 per 3B-set group).  A wave whose segment is too short reads
+// its part of the matrix again instead.
+//
+// The Frobenius norm of clamp(M, tau) comes out of the same passes: tau lies between
+// v[lo] and v[lo+1], and no element lies strictly between them, so an element whose
+// known prefix is below that of v[lo] is not clipped (its square goes into a binary64
+// partial of the block) and one above that of v[lo+1] is clipped to tau (it is only
+// counted); the elements of the two full prefixes are exactly the last histograms (a key
+// is the bit pattern of |x|), which the select step sums in bin order once tau is known.
+// Partials are formed and added in a fixed order.
 
-__global__ __launch_bounds__(256) void k_sumsq(MatChunk ch, const MatScalars* sc, double* partial,
-                                               uint32_t* status) {
-  __shared__ double red[256];
-  const int64_t tile = blockIdx.x;
-  const int mi = find_matrix(ch, tile);
-  const MatDesc& d = ch.m[mi];
-  const float tau = sc[mi].tau;
-  const int64_t r0 = (tile - d.tile_begin) * kPrepRowsPerBlock;
-  const int64_t r1 = r0 + kPrepRowsPerBlock < d.rows ? r0 + kPrepRowsPerBlock : d.rows;
-  double acc = 0.0;
-  bool bad = false;   // a NaN or infinite entry (the clamp would hide a NaN)
-  for (int64_t r = r0; r < r1; ++r) {
-    const float4* row = reinterpret_cast<const float4*>(d.in + r * d.ld_in);
-    for (int64_t c = threadIdx.x; c < d.cols / 4; c += 256) {
-      const float4 v = row[c];
-      const float e[4] = {v.x, v.y, v.z, v.w};
+// A workgroup's part of a matrix: quads t, t + 256, ... of quads [q0, q0 + nq), four
+// loads issued before any is used; f(element value) in order.
+struct QuadWalk {
+  const float* base;
+  int64_t ld;
+  uint32_t c4, cc;
+  int64_t rr;
+  bool flat;
+};
+FP4R_DEV QuadWalk quad_walk(const MatChunk& ch, const MatRef& r, int64_t q0) {
+  QuadWalk w;
+  const int64_t c4 = (r.tall() ? ch.rows : ch.cols) / 4;
+  w.ld = r.ld_in();
+  w.c4 = (uint32_t)c4;
+  w.flat = w.ld == 4 * c4;
+  w.base = r.in;
+  if (w.flat) {
+    w.base += 4 * (q0 + threadIdx.x);
+    w.rr = 0;
+    w.cc = 0;
+  } else {
+    const int64_t row = q0 / c4;
+    const uint32_t c = (uint32_t)(q0 - row * c4) + threadIdx.x;
+    w.rr = row + c / w.c4;
+    w.cc = c % w.c4;
+  }
+  return w;
+}
+FP4R_DEV float4 walk_load(QuadWalk& w) {   // the next quad of this thread
+  if (w.flat) {
+    const float4 v = *reinterpret_cast<const float4*>(w.base);
+    w.base += 1024;
+    return v;
+  }
+  const float4 v = reinterpret_cast<const float4*>(w.base + w.rr * w.ld)[w.cc];
+  w.cc += 256u;
+  if (w.cc >= w.c4) {
+    const uint32_t d = w.cc / w.c4;
+    w.rr += d;
+    w.cc -= d * w.c4;
+  }
+  return v;
+}
+template <class F>
+FP4R_DEV void walk_quads(QuadWalk w, uint32_t nq, F f) {
+  for (uint32_t q0 = threadIdx.x; q0 < nq; q0 += 1024u) {
+    float4 v[4];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        bad |= !(fabsf(e[j]) <= 3.40282347e38f);
-        const double x = (double)fminf(fmaxf(e[j], -tau), tau);
+    for (int u = 0; u < 4; ++u)
+      v[u] = q0 + 256u * u < nq ? walk_load(w) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const bool live = q0 + 256u * u < nq;
+      f(v[u].x, live);
+      f(v[u].y, live);
+      f(v[u].z, live);
+      f(v[u].w, live);
+    }
+  }
+}
+
+// Fixed-order sum over 256 threads (thread 0 gets it).
+FP4R_DEV double block_sum_256(double v, double* red) {
+  red[threadIdx.x] = v;
+  __syncthreads();
+  for (int off = 128; off > 0; off >>= 1) {
+    if ((int)threadIdx.x < off) red[threadIdx.x] = red[threadIdx.x] + red[threadIdx.x + off];
+    __syncthreads();
+  }
+  return red[0];
+}
+
+struct ClipArgs {
+  uint32_t* hist;
+  float* cand;
+  int64_t cand_stride;
+  uint32_t* cnt;
+  double* psum;
+  uint32_t* pcnt;
+  uint32_t tile_quads, tiles;
+  int32_t cand_shift;
+};
+
+// Number of floats of a wave's segment in a tile of nq quads, and where it starts.
+FP4R_DEV uint32_t seg_cap(const ClipArgs& a, uint32_t nq) { return nq >> a.cand_shift; }
+FP4R_DEV float* seg_base(const ClipArgs& a, int mi, uint32_t tile, uint32_t nq, uint32_t wave) {
+  return a.cand + (int64_t)mi * a.cand_stride + (((int64_t)tile * a.tile_quads * 4) >> a.cand_shift) +
+         (int64_t)wave * seg_cap(a, nq);
+}
+
+template <int PASS>
+__global__ __launch_bounds__(256) void k_radix_hist(MatChunk ch, const MatScalars* sc, uint32_t* status, ClipArgs a) {
+  constexpr int kBins = PASS == 0 ? 2048 : 1024, kSets = PASS == 0 ? 1 : 2;
+  __shared__ uint32_t h[kSets][kBins];
+  __shared__ double red[256];
+  __shared__ uint32_t above_all;
+  for (int i = threadIdx.x; i < kSets * kBins; i += 256) (&h[0][0])[i] = 0;
+  if (threadIdx.x == 0) above_all = 0;
+  __syncthreads();
+  const bool last = PASS == 2 && a.cand != nullptr;   // reads the segments
+  const int mi = (int)(blockIdx.x / a.tiles);
+  const uint32_t tile = blockIdx.x - (uint32_t)mi * a.tiles;
+  const MatRef& r = ch.m[mi];
+  const int64_t quads = ch.rows * ch.cols / 4;
+  const uint32_t p0 = PASS > 0 ? sc[mi].sel_prefix[0] : 0u, p1 = PASS > 0 ? sc[mi].sel_prefix[1] : 0u;
+  const bool two = PASS > 0 && p0 != p1;
+  const uint32_t wave = threadIdx.x >> 6;
+  double acc = 0.0;     // squares of the elements below prefix p0, in this thread's order
+  uint32_t above = 0;   // elements above prefix p1
+  bool bad = false;
+  // one element of the digit's candidates and the norm (pre: the prefix known so far)
+  auto count_key = [&](uint32_t key, uint32_t pre, uint32_t digit, bool live) {
+    if (live && pre == p0) atomicAdd(&h[0][digit], 1u);
+    if (kSets > 1 && two && live && pre == p1) atomicAdd(&h[kSets - 1][digit], 1u);
+    if (a.psum) {
+      if (live && pre < p0) {
+        const double x = (double)__uint_as_float(key);
         acc = acc + x * x;
+      } else if (live && pre > p1) {
+        ++above;
+      }
+    }
+  };
+  {
+    const int64_t q0 = (int64_t)tile * a.tile_quads;
+    const uint32_t nq = (uint32_t)(quads - q0 < a.tile_quads ? quads - q0 : a.tile_quads);
+    if constexpr (PASS == 0) {
+      walk_quads(quad_walk(ch, r, q0), nq, [&](float x, bool live) {
+        const uint32_t key = __float_as_uint(x) & 0x7FFFFFFFu;
+        if (!live) return;
+        if (key >= 0x7F800000u) { bad = true; return; }
+        atomicAdd(&h[0][key >> 20], 1u);
+      });
+    } else if constexpr (PASS == 1) {
+      float* const seg = a.cand ? seg_base(a, mi, tile, nq, wave) : nullptr;
+      const uint32_t cap = seg_cap(a, nq);
+      uint32_t n = 0;   // elements collected by this wave (uniform)
+      walk_quads(quad_walk(ch, r, q0), nq, [&](float x, bool live) {
+        const uint32_t key = __float_as_uint(x) & 0x7FFFFFFFu;
+        live = live && key < 0x7F800000u;
+        const uint32_t pre = key >> 20;
+        count_key(key, pre, (key >> 10) & 1023u, live);
+        if (a.cand) {
+          const bool mine = live && (pre == p0 || pre == p1);
+          const uint64_t mask = __builtin_amdgcn_ballot_w64(mine);
+          if (mask) {
+            const uint32_t at = n + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                                              __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+            if (mine && at < cap) seg[at] = x;
+            n += (uint32_t)__builtin_popcountll(mask);
+          }
+        }
+      });
+      // lanes leave the walk together or not at all, except past the end of the tile: the
+      // count of the lane that stayed longest (lane 0) is the wave's
+      n = __builtin_amdgcn_readfirstlane(n);
+      if (a.cand && (threadIdx.x & 63) == 0) a.cnt[((int64_t)mi * a.tiles + tile) * 4 + wave] = n;
+    } else if (last) {
+      const uint32_t cap = seg_cap(a, nq);
+      const uint32_t n = a.cnt[((int64_t)mi * a.tiles + tile) * 4 + wave];
+      if (n <= cap) {
+        const float* const seg = seg_base(a, mi, tile, nq, wave);
+        for (uint32_t i = threadIdx.x & 63; i < n; i += 64) {
+          const uint32_t key = __float_as_uint(seg[i]) & 0x7FFFFFFFu;
+          count_key(key, key >> 10, key & 1023u, true);
+        }
+      } else {
+        walk_quads(quad_walk(ch, r, q0), nq, [&](float x, bool live) {
+          const uint32_t key = __float_as_uint(x) & 0x7FFFFFFFu, top = key >> 20;
+          count_key(key, key >> 10, key & 1023u, live && (top == p0 >> 10 || top == p1 >> 10));
+        });
+      }
+    } else {
+      walk_quads(quad_walk(ch, r, q0), nq, [&](float x, bool live) {
+        const uint32_t key = __float_as_uint(x) & 0x7FFFFFFFu;
+        count_key(key, key >> 10, key & 1023u, live && key < 0x7F800000u);
+      });
+    }
+  }
+  if (PASS == 0 && bad) atomicOr(status, kStatusNonFinite);
+  if (PASS > 0 && a.psum) {
+    // partials: one per tile from the second pass, then one per tile from the last
+    if (above) atomicAdd(&above_all, above);
+    const double sum = block_sum_256(acc, red);
+    if (threadIdx.x == 0) {
+      const int64_t at = (int64_t)mi * 2 * a.tiles + (PASS == 2 ? a.tiles : 0u) + tile;
+      a.psum[at] = sum;
+      a.pcnt[at] = above_all;
+    }
+  }
+  __syncthreads();
+  for (int b = threadIdx.x; b < kBins; b += 256) {
+    if (h[0][b]) atomicAdd(&a.hist[(mi * 2 + 0) * kHistBins + b], h[0][b]);
+    if (kSets > 1 && two && h[kSets - 1][b]) atomicAdd(&a.hist[(mi * 2 + 1) * kHistBins + b], h[kSets - 1][b]);
+  }
+}
+
+// Selects the digit of both ranks from the histograms (cleared for the next pass): one
+// workgroup per matrix, bins in thread order, a shuffle scan over each wave and the wave
+// totals through LDS (8.4 us as a 256-entry LDS scan per rank).
+template <int PASS>
+__global__ __launch_bounds__(256) void k_radix_select(MatChunk ch, MatScalars* sc, ClipArgs a, float eps) {
+  constexpr int kPer = (PASS == 0 ? 2048 : 1024) / 256;   // bins per thread
+  __shared__ uint32_t wsum[2][4];
+  __shared__ uint32_t found_prefix[2], found_rank[2];
+  __shared__ double red[256];
+  __shared__ unsigned long long above_all;
+  const int mi = blockIdx.x;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  MatScalars& s = sc[mi];
+  const int64_t n = ch.rows * ch.cols;
+  const uint32_t pre0 = PASS > 0 ? s.sel_prefix[0] : 0u, pre1 = PASS > 0 ? s.sel_prefix[1] : 0u;
+  const bool two = pre0 != pre1;
+  uint32_t* const hist = a.hist + (int64_t)mi * 2 * kHistBins;
+  uint32_t c[2][kPer], local[2], incl[2];
+#pragma unroll
+  for (int rr = 0; rr < 2; ++rr) {
+    const uint4* hh = reinterpret_cast<const uint4*>(hist + (two ? rr : 0) * kHistBins + t * kPer);
+    local[rr] = 0;
+#pragma unroll
+    for (int j = 0; j < kPer / 4; ++j) {
+      const uint4 v = hh[j];
+      c[rr][4 * j] = v.x; c[rr][4 * j + 1] = v.y; c[rr][4 * j + 2] = v.z; c[rr][4 * j + 3] = v.w;
+      local[rr] += v.x + v.y + v.z + v.w;
+    }
+    incl[rr] = local[rr];
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint32_t up = (uint32_t)__shfl_up((int)incl[rr], off, 64);
+      if (lane >= off) incl[rr] += up;
+    }
+    if (lane == 63) wsum[rr][wave] = incl[rr];
+  }
+  if (t < 2) found_prefix[t] = found_rank[t] = 0;   // ranks past the counted (finite) elements
+  if (t == 0) above_all = 0;
+  __syncthreads();
+#pragma unroll
+  for (int rr = 0; rr < 2; ++rr) {
+    uint32_t before = 0;
+#pragma unroll
+    for (int w = 0; w < 3; ++w)
+      if (w < wave) before += wsum[rr][w];
+    uint32_t cum = before + incl[rr] - local[rr];
+    const uint32_t target = PASS > 0 ? s.sel_rank[rr] : (uint32_t)(rr == 0 || ch.lo + 1 >= n ? ch.lo : ch.lo + 1);
+    if (target >= cum && target - cum < local[rr]) {   // exactly one thread owns the target rank
+#pragma unroll
+      for (int j = 0; j < kPer; ++j) {
+        if (target >= cum && target - cum < c[rr][j]) {
+          const uint32_t bin = (uint32_t)(t * kPer + j);
+          found_prefix[rr] = PASS == 0 ? bin : (((rr ? pre1 : pre0) << 10) | bin);
+          found_rank[rr] = target - cum;
+        }
+        cum += c[rr][j];
       }
     }
   }
-  if (__builtin_amdgcn_ballot_w64(bad) != 0 && (threadIdx.x & 63) == 0) atomicOr(status, kStatusNonFinite);
-  red[threadIdx.x] = acc;
   __syncthreads();
-  for (int off = 128; off > 0; off >>= 1) {
-    if ((int)threadIdx.x < off) red[threadIdx.x] = red[threadIdx.x] + red[threadIdx.x + off];
-    __syncthreads();
+  const uint32_t f0 = found_prefix[0], f1 = found_prefix[1];
+  if (PASS == 2) {
+    const double v0 = (double)__uint_as_float(f0), v1 = (double)__uint_as_float(f1);
+    const float tau = (float)__dadd_rn(v0, __dmul_rn(ch.frac, __dsub_rn(v1, v0)));
+    if (t == 0) s.tau = tau;
+    if (a.psum) {
+      // ||clamp(M, tau)||^2 in a fixed order: the partials below v[lo]'s prefix, the
+      // elements of the two prefixes from the histograms (bin order), the elements above
+      // at tau^2 each
+      const int64_t np = (int64_t)2 * a.tiles;
+      double below = 0.0;
+      unsigned long long above = 0;
+      for (int64_t i = t; i < np; i += 256) {
+        below = below + a.psum[mi * np + i];
+        above += a.pcnt[mi * np + i];
+      }
+      double cand = 0.0;
+#pragma unroll
+      for (int rr = 0; rr < 2; ++rr) {
+        if (rr == 1 && !two) break;
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+          const uint32_t bin = (uint32_t)(t * kPer + j);
+          if (c[rr][j]) {
+            const double x = (double)fminf(__uint_as_float(((rr ? pre1 : pre0) << 10) | bin), tau);
+            cand = cand + (double)c[rr][j] * (x * x);
+          }
+        }
+      }
+      if (above) atomicAdd(&above_all, above);
+      const double sum_below = block_sum_256(below, red);
+      __syncthreads();
+      const double sum_cand = block_sum_256(cand, red);
+      if (t == 0) {
+        const double tt = (double)tau * (double)tau;
+        const double total = __dadd_rn(__dadd_rn(sum_below, sum_cand), __dmul_rn((double)above_all, tt));
+        const double nu = __dsqrt_rn(total);
+        s.inv_norm = (float)__ddiv_rn(1.0, __dadd_rn(nu, (double)eps));
+      }
+    }
   }
-  if (threadIdx.x == 0) partial[tile] = red[0];
+  for (int b = t; b < 2 * kHistBins / 4; b += 256) reinterpret_cast<uint4*>(hist)[b] = make_uint4(0u, 0u, 0u, 0u);
+  if (t == 0) {
+    s.sel_prefix[0] = f0;
+    s.sel_prefix[1] = f1;
+    s.sel_rank[0] = found_rank[0];
+    s.sel_rank[1] = found_rank[1];
+  }
 }
 
-__global__ __launch_bounds__(256) void k_norm_final(MatChunk ch, MatScalars* sc, const double* partial,
-                                                    float eps) {
+hipError_t launch_clip_threshold(const MatChunk& ch, MatScalars* sc, uint32_t* status, const ClipScratch& w, float eps,
+                                 hipStream_t st) {
+  if (ch.count < 1) return hipSuccess;
+  if (w.psum && !w.cand) return hipErrorInvalidValue;
+  const int64_t quads = ch.rows * ch.cols / 4, tiles = hist_tiles(quads, ch.count);
+  ClipArgs a;
+  a.hist = w.hist; a.cand = w.cand; a.cand_stride = w.cand_stride; a.cnt = w.cnt; a.psum = w.psum; a.pcnt = w.pcnt;
+  a.tile_quads = (uint32_t)hist_tile_quads(quads, ch.count);
+  a.tiles = (uint32_t)tiles;
+  a.cand_shift = w.cand_shift;
+  const dim3 full((uint32_t)(tiles * ch.count)), sel((uint32_t)ch.count), wg(256);
+  hipLaunchKernelGGL(k_radix_hist<0>, full, wg, 0, st, ch, sc, status, a);
+  hipLaunchKernelGGL(k_radix_select<0>, sel, wg, 0, st, ch, sc, a, eps);
+  hipLaunchKernelGGL(k_radix_hist<1>, full, wg, 0, st, ch, sc, status, a);
+  hipLaunchKernelGGL(k_radix_select<1>, sel, wg, 0, st, ch, sc, a, eps);
+  hipLaunchKernelGGL(k_radix_hist<2>, full, wg, 0, st, ch, sc, status, a);
+  hipLaunchKernelGGL(k_radix_select<2>, sel, wg, 0, st, ch, sc, a, eps);
+  return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
+// Frobenius norm of the matrices without clipping: per-tile binary64 partials in a
+// fixed order, then one fixed-order sum per matrix (deterministic).
+
+__global__ __launch_bounds__(256) void k_sumsq(MatChunk ch, double* partial, uint32_t* status, uint32_t tile_quads,
+                                               uint32_t tiles) {
+  __shared__ double red[256];
+  const int mi = (int)(blockIdx.x / tiles);
+  const int64_t q0 = (int64_t)(blockIdx.x - (uint32_t)mi * tiles) * tile_quads, quads = ch.rows * ch.cols / 4;
+  const uint32_t nq = (uint32_t)(quads - q0 < tile_quads ? quads - q0 : tile_quads);
+  double acc = 0.0;
+  bool bad = false;   // a NaN or infinite entry
+  walk_quads(quad_walk(ch, ch.m[mi], q0), nq, [&](float v, bool live) {   // quads past the end are zero
+    bad |= live && !(fabsf(v) <= 3.40282347e38f);
+    const double x = (double)fminf(fmaxf(v, -__builtin_inff()), __builtin_inff());
+    acc = acc + x * x;
+  });
+  if (__builtin_amdgcn_ballot_w64(bad) != 0 && (threadIdx.x & 63) == 0) atomicOr(status, kStatusNonFinite);
+  const double sum = block_sum_256(acc, red);
+  if (threadIdx.x == 0) partial[blockIdx.x] = sum;
+}
+
+__global__ __launch_bounds__(256) void k_norm_final(MatScalars* sc, const double* partial, float eps, uint32_t tiles) {
   __shared__ double red[256];
   const int mi = blockIdx.x;
-  const MatDesc& d = ch.m[mi];
-  const int64_t nt = (d.rows + kPrepRowsPerBlock - 1) / kPrepRowsPerBlock;
   double acc = 0.0;
-  for (int64_t i = threadIdx.x; i < nt; i += 256) acc = acc + partial[d.tile_begin + i];
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int off = 128; off > 0; off >>= 1) {
-    if ((int)threadIdx.x < off) red[threadIdx.x] = red[threadIdx.x] + red[threadIdx.x + off];
-    __syncthreads();
-  }
+  for (uint32_t i = threadIdx.x; i < tiles; i += 256) acc = acc + partial[(int64_t)mi * tiles + i];
+  const double total = block_sum_256(acc, red);
   if (threadIdx.x == 0) {
-    const double nu = __dsqrt_rn(red[0]);
+    const double nu = __dsqrt_rn(total);
     sc[mi].inv_norm = (float)__ddiv_rn(1.0, __dadd_rn(nu, (double)eps));
   }
 }
@@ -340,8 +443,10 @@ hipError_t launch_status_out(const uint32_t* status, int32_t* out, hipStream_t s
 
 hipError_t launch_inv_norm(const MatChunk& ch, MatScalars* sc, double* partial, float eps,
                            uint32_t* status, hipStream_t st) {
-  hipLaunchKernelGGL(k_sumsq, dim3((uint32_t)ch.total_tiles), dim3(256), 0, st, ch, sc, partial, status);
-  hipLaunchKernelGGL(k_norm_final, dim3(ch.count), dim3(256), 0, st, ch, sc, partial, eps);
+  const int64_t quads = ch.rows * ch.cols / 4, tiles = hist_tiles(quads, ch.count);
+  hipLaunchKernelGGL(k_sumsq, dim3((uint32_t)(tiles * ch.count)), dim3(256), 0, st, ch, partial, status,
+                     (uint32_t)hist_tile_quads(quads, ch.count), (uint32_t)tiles);
+  hipLaunchKernelGGL(k_norm_final, dim3(ch.count), dim3(256), 0, st, sc, (const double*)partial, eps, (uint32_t)tiles);
   return hipGetLastError();
 }
 
@@ -368,12 +473,13 @@ __global__ __launch_bounds__(256) void k_prep_copy(MatChunk ch, MatScalars* sc, 
                                                    int slot_n, int slot_m) {
   __shared__ float tile[kT][kT + 1];
   __shared__ float red[4];
-  const int64_t t = blockIdx.x;
-  const int mi = find_matrix(ch, t);
-  const MatDesc& d = ch.m[mi];
-  const bool tall = d.rows > d.cols;
-  const int64_t xm = tall ? d.cols : d.rows, xn = tall ? d.rows : d.cols;   // canonical m x n
-  const uint32_t tcols = (uint32_t)cdiv(xn, kT), tt = (uint32_t)(t - d.tile_begin);
+  const int64_t xm = ch.rows, xn = ch.cols;   // canonical m x n
+  const uint32_t tcols = (uint32_t)cdiv(xn, kT), per = (uint32_t)cdiv(xm, kT) * tcols;
+  const int mi = (int)(blockIdx.x / per);
+  const uint32_t tt = blockIdx.x - (uint32_t)mi * per;
+  const MatRef& d = ch.m[mi];
+  const bool tall = d.tall();
+  const int64_t ld_in = d.ld_in();
   const int64_t xr0 = (int64_t)(tt / tcols) * kT, xc0 = (int64_t)(tt % tcols) * kT;   // canonical tile origin
   float* X = xbase + (int64_t)mi * x_bstride;
   const float tau = sc[mi].tau;
@@ -387,7 +493,7 @@ __global__ __launch_bounds__(256) void k_prep_copy(MatChunk ch, MatScalars* sc, 
     if (!tall) {
       const int64_t r = xr0 + i, c = xc0 + 4 * q;
       if (r < xm && c < xn) {
-        float4 a = *reinterpret_cast<const float4*>(d.in + r * d.ld_in + c);
+        float4 a = *reinterpret_cast<const float4*>(d.in + r * ld_in + c);
         a.x = fminf(fmaxf(a.x, -tau), tau) * inv;
         a.y = fminf(fmaxf(a.y, -tau), tau) * inv;
         a.z = fminf(fmaxf(a.z, -tau), tau) * inv;
@@ -398,8 +504,8 @@ __global__ __launch_bounds__(256) void k_prep_copy(MatChunk ch, MatScalars* sc, 
     } else {
       // M row xc0 + i, M columns xr0 + 4q .. + 3  ->  X rows xr0 + 4q .. + 3, column xc0 + i
       const int64_t r = xc0 + i, c = xr0 + 4 * q;
-      if (r < d.rows && c < d.cols) {
-        const float4 a = *reinterpret_cast<const float4*>(d.in + r * d.ld_in + c);
+      if (r < xn && c < xm) {
+        const float4 a = *reinterpret_cast<const float4*>(d.in + r * ld_in + c);
         tile[4 * q][i] = fminf(fmaxf(a.x, -tau), tau) * inv;
         tile[4 * q + 1][i] = fminf(fmaxf(a.y, -tau), tau) * inv;
         tile[4 * q + 2][i] = fminf(fmaxf(a.z, -tau), tau) * inv;
@@ -537,14 +643,16 @@ hipError_t launch_amax_x2(const float* x, int64_t batch, int64_t m, int64_t n, i
 // Copy-out: caller M (rows x cols) from canonical X (transposed back when tall).
 __global__ __launch_bounds__(256) void k_copy_out(MatChunk ch, const float* xbase, int64_t x_bstride) {
   __shared__ float tile[kT][kT + 1];
-  const int64_t t = blockIdx.x;
-  const int mi = find_matrix(ch, t);
-  const MatDesc& d = ch.m[mi];
-  const bool tall = d.rows > d.cols;
-  const uint32_t tcols = (uint32_t)cdiv(d.cols, kT), tt = (uint32_t)(t - d.tile_begin);
+  const int64_t per = cdiv(ch.rows, kT) * cdiv(ch.cols, kT);
+  const int mi = (int)(blockIdx.x / per);
+  const uint32_t tt = (uint32_t)(blockIdx.x - mi * per);
+  const MatRef& d = ch.m[mi];
+  const bool tall = d.tall();
+  const int64_t rows = tall ? ch.cols : ch.rows, cols = tall ? ch.rows : ch.cols, ld_out = d.ld_out();
+  const uint32_t tcols = (uint32_t)cdiv(cols, kT);
   const int64_t br = (int64_t)(tt / tcols) * kT, bc = (int64_t)(tt % tcols) * kT;   // tile origin in M coordinates
   const float* X = xbase + (int64_t)mi * x_bstride;
-  const int64_t xld = tall ? d.rows : d.cols;
+  const int64_t xld = tall ? rows : cols;
   // 16-byte accesses (see k_prep_copy): thread -> quads v = threadIdx.x + 256 k,
   // row v / 16 of the tile, columns 4 (v % 16) .. + 3
   if (!tall) {
@@ -552,8 +660,8 @@ __global__ __launch_bounds__(256) void k_copy_out(MatChunk ch, const float* xbas
     for (int k = 0; k < 4; ++k) {
       const int v = (int)threadIdx.x + 256 * k, i = v >> 4, q = v & 15;
       const int64_t r = br + i, c = bc + 4 * q;
-      if (r < d.rows && c < d.cols)
-        *reinterpret_cast<float4*>(d.out + r * d.ld_out + c) = *reinterpret_cast<const float4*>(X + r * xld + c);
+      if (r < rows && c < cols)
+        *reinterpret_cast<float4*>(d.out + r * ld_out + c) = *reinterpret_cast<const float4*>(X + r * xld + c);
     }
     return;
   }
@@ -562,7 +670,7 @@ __global__ __launch_bounds__(256) void k_copy_out(MatChunk ch, const float* xbas
   for (int k = 0; k < 4; ++k) {
     const int v = (int)threadIdx.x + 256 * k, i = v >> 4, q = v & 15;
     const int64_t c = bc + i, r = br + 4 * q;
-    if (r < d.rows && c < d.cols) {
+    if (r < rows && c < cols) {
       const float4 a = *reinterpret_cast<const float4*>(X + c * xld + r);
       tile[4 * q][i] = a.x; tile[4 * q + 1][i] = a.y; tile[4 * q + 2][i] = a.z; tile[4 * q + 3][i] = a.w;
     }
@@ -572,21 +680,21 @@ __global__ __launch_bounds__(256) void k_copy_out(MatChunk ch, const float* xbas
   for (int k = 0; k < 4; ++k) {
     const int v = (int)threadIdx.x + 256 * k, i = v >> 4, q = v & 15;
     const int64_t r = br + i, c = bc + 4 * q;
-    if (r < d.rows && c < d.cols)
-      *reinterpret_cast<float4*>(d.out + r * d.ld_out + c) =
+    if (r < rows && c < cols)
+      *reinterpret_cast<float4*>(d.out + r * ld_out + c) =
           make_float4(tile[i][4 * q], tile[i][4 * q + 1], tile[i][4 * q + 2], tile[i][4 * q + 3]);
   }
 }
 
 hipError_t launch_prep_copy(const MatChunk& ch, MatScalars* sc, float* x, int64_t x_bstride,
                             uint32_t mask, bool rotate, int slot_n, int slot_m, hipStream_t st) {
-  hipLaunchKernelGGL(k_prep_copy, dim3((uint32_t)ch.total_tiles), dim3(256), 0, st, ch, sc, x,
+  hipLaunchKernelGGL(k_prep_copy, dim3((uint32_t)(cdiv(ch.rows, kT) * cdiv(ch.cols, kT) * ch.count)), dim3(256), 0, st, ch, sc, x,
                      x_bstride, mask, (int)rotate, slot_n, slot_m);
   return hipGetLastError();
 }
 
 hipError_t launch_copy_out(const MatChunk& ch, const float* x, int64_t x_bstride, hipStream_t st) {
-  hipLaunchKernelGGL(k_copy_out, dim3((uint32_t)ch.total_tiles), dim3(256), 0, st, ch, x, x_bstride);
+  hipLaunchKernelGGL(k_copy_out, dim3((uint32_t)(cdiv(ch.rows, kT) * cdiv(ch.cols, kT) * ch.count)), dim3(256), 0, st, ch, x, x_bstride);
   return hipGetLastError();
 }
 
@@ -724,7 +832,7 @@ FP4R_DEV uint64_t sr_block_codes(const float (&u)[16], float kf, uint32_t scale,
 template <int AXIS, bool SR = false>
 __global__ __launch_bounds__(256) void k_encode(Batch in, uint32_t mask, int rotate, int clip,
                                                 int adaptive, MatScalars* sc, int slot, QOut out,
-                                                float* tensor_scale, uint64_t sr_key = 0) {
+                                                float* tensor_scale, float* tau_out, uint64_t sr_key) {
   const int64_t b = blockIdx.y;
   const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int64_t nblk = in.rows * in.cols / 16;
@@ -732,6 +840,7 @@ __global__ __launch_bounds__(256) void k_encode(Batch in, uint32_t mask, int rot
   if (g == 0) {
     sc[b].sg[slot] = sg;
     if (tensor_scale) tensor_scale[b] = sg;
+    if (tau_out) tau_out[b] = sc[b].tau;
   }
   if (g >= nblk) return;
   int64_t r = 0, c = 0;
@@ -1089,15 +1198,15 @@ hipError_t launch_amax(const Batch& in, int axis, uint32_t sign_mask, bool rotat
 
 hipError_t launch_encode(const Batch& in, int axis, uint32_t sign_mask, bool rotate, bool clip,
                          bool adaptive46, MatScalars* sc, int slot, const QOut& out,
-                         float* tensor_scale, hipStream_t st) {
+                         float* tensor_scale, hipStream_t st, float* tau_out) {
   const int64_t nblk = in.rows * in.cols / 16;
   const dim3 grid((uint32_t)((nblk + 255) / 256), (uint32_t)in.batch);
   if (axis == 1)
     hipLaunchKernelGGL((k_encode<1, false>), grid, dim3(256), 0, st, in, sign_mask, (int)rotate, (int)clip,
-                       (int)adaptive46, sc, slot, out, tensor_scale, (uint64_t)0);
+                       (int)adaptive46, sc, slot, out, tensor_scale, tau_out, (uint64_t)0);
   else
     hipLaunchKernelGGL((k_encode<0, false>), grid, dim3(256), 0, st, in, sign_mask, (int)rotate, (int)clip,
-                       (int)adaptive46, sc, slot, out, tensor_scale, (uint64_t)0);
+                       (int)adaptive46, sc, slot, out, tensor_scale, tau_out, (uint64_t)0);
   return hipGetLastError();
 }
 
@@ -1107,7 +1216,7 @@ hipError_t launch_encode_sr(const Batch& in, uint32_t sign_mask, bool rotate, bo
   const int64_t nblk = in.rows * in.cols / 16;
   const dim3 grid((uint32_t)((nblk + 255) / 256), (uint32_t)in.batch);
   hipLaunchKernelGGL((k_encode<1, true>), grid, dim3(256), 0, st, in, sign_mask, (int)rotate, 0,
-                     (int)adaptive46, sc, slot, out, tensor_scale, sr_key);
+                     (int)adaptive46, sc, slot, out, tensor_scale, (float*)nullptr, sr_key);
   return hipGetLastError();
 }
 
@@ -1253,30 +1362,6 @@ hipError_t launch_cast_bf16(const float* x, int64_t batch, int64_t m, int64_t n,
 
 // ---------------------------------------------------------------------------
 // Small per-matrix scalar kernels.
-
-__global__ void k_reset_scalars(MatScalars* sc, int64_t n, uint32_t slot_mask, int full) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  MatScalars& s = sc[i];
-#pragma unroll
-  for (int k = 0; k < kNumSlots; ++k)
-    if ((slot_mask >> k) & 1u)
-#pragma unroll
-      for (int l = 0; l < kAmaxSpread; ++l) s.amax[l].v[k] = 0u;
-  if (full) {
-#pragma unroll
-    for (int k = 0; k < kNumSlots; ++k) s.sg[k] = 0.0f;
-    s.tau = __uint_as_float(0x7F800000u);   // +inf: clamping is the identity
-    s.inv_norm = 1.0f;
-  }
-}
-
-hipError_t launch_reset_scalars(MatScalars* sc, int64_t n, uint32_t slot_mask, bool full, hipStream_t st) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_reset_scalars, dim3((uint32_t)((n + 255) / 256)), dim3(256), 0, st, sc, n,
-                     slot_mask, (int)full);
-  return hipGetLastError();
-}
 
 __global__ void k_export_scalar(const MatScalars* sc, int64_t n, int which, int slot, float* out) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
