@@ -797,10 +797,8 @@ FP4R_DEV double e2m1_grid(uint32_t idx) {
 // below it (the round-to-nearest quotient is within one ulp of x), and
 // rho (hi - lo) r < (|u| - lo r) 2^24 is exact in binary64 (every term has at
 // most 48 significant bits; |u| - lo r is a difference of numbers within a factor 2).
-FP4R_DEV uint64_t sr_block_codes(const float (&u)[16], float kf, uint32_t scale, float sg, uint64_t rtn,
-                                 uint64_t key, uint64_t e0) {
-  const float r = e4m3_value(scale) * sg;
-  if (!(r > 0.0f)) return rtn & 0x8888888888888888ull;   // magnitudes 0, signs kept
+FP4R_DEV uint64_t sr_block_codes_exact(const float (&u)[16], float kf, float r, uint64_t rtn, uint64_t key,
+                                       uint64_t e0) {
   const double rd = (double)r;
   // element e0 + i takes 24 bits of SplitMix64 output (e0 + i) / 2 + 1 (e0 is even):
   // bits 40..63 for even i, bits 16..39 for odd i
@@ -827,6 +825,36 @@ FP4R_DEV uint64_t sr_block_codes(const float (&u)[16], float kf, uint32_t scale,
     out |= (uint64_t)((c & 8u) | idx) << (4 * i);
   }
   return out;
+}
+
+// The same codes decided in binary32 wherever that is certain.  The index, with the
+// grid's points as its whole numbers, is the concave p(x) = min(2 x, x + 2, x / 2 + 4, 7),
+// and the rule above is floor(p(x) + 1 - rho 2^-24) away from whole values of that sum.
+// It is computed with x = |u| rcp(r): rcp within 2^-23, a slope times x of at most 4, and
+// two roundings of at most 2^-22, so within 2^-20 in all; a block with an element within
+// 2^-19 of a whole number (one in 2^14) takes the binary64 comparisons.  Both were issue
+// bound: TIMES
+FP4R_DEV uint64_t sr_block_codes(const float (&u)[16], float kf, uint32_t scale, float sg, uint64_t rtn,
+                                 uint64_t key, uint64_t e0) {
+  const float r = e4m3_value(scale) * sg;
+  if (!(r > 0.0f)) return rtn & 0x8888888888888888ull;   // magnitudes 0, signs kept
+  bool sure = r > 0x1p-100f && r < 0x1p+100f;
+  const float i1 = __builtin_amdgcn_rcpf(r) * (kf == 1.0f ? 1.0f : 0.25f), i2 = i1 + i1, ih = 0.5f * i1;
+  const uint64_t z0 = key + 0x9E3779B97F4A7C15ull * (e0 / 2 + 1);
+  uint64_t zk = 0;
+  uint32_t w[2] = {0u, 0u};
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    if ((i & 1) == 0) zk = splitmix64_mix(z0 + 0x9E3779B97F4A7C15ull * (uint64_t)(i / 2));
+    const uint32_t rho = (uint32_t)(zk >> ((i & 1) ? 16 : 40)) & 0xFFFFFFu;
+    const float a = fabsf(u[i]);
+    const float p = fminf(fminf(fminf(fmaf(a, i2, 1.0f), fmaf(a, i1, 3.0f)), fmaf(a, ih, 5.0f)), 8.0f);
+    const float t = fmaf((float)rho, -0x1p-24f, p);
+    sure = sure & (fabsf(__builtin_amdgcn_fractf(t) - 0.5f) < 0.5f - 0x1p-19f);   // false for NaN
+    w[i >> 3] |= (uint32_t)t << (4 * (i & 7));
+  }
+  if (!sure) return sr_block_codes_exact(u, kf, r, rtn, key, e0);
+  return (rtn & 0x8888888888888888ull) | (uint64_t)w[0] | ((uint64_t)w[1] << 32);
 }
 
 template <int AXIS, bool SR = false>
