@@ -95,6 +95,15 @@ FP4R_DEV uint64_t splitmix64_at(uint64_t state, uint64_t index) {
   return splitmix64_mix(state + 0x9E3779B97F4A7C15ull * index);
 }
 
+// No infinity or NaN among the 16: the largest of the bits without their signs (one shift
+// and half a three-way maximum per element).
+FP4R_DEV bool finite16(const float (&u)[16]) {
+  uint32_t m = 0;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) m = max(m, __float_as_uint(u[i]) << 1);
+  return m < (0x7F800000u << 1);
+}
+
 // Binary32 -> BF16 bit pattern, round to nearest, ties to even (finite inputs).
 FP4R_DEV uint16_t bf16_rne(float f) {
   const uint32_t u = __float_as_uint(f);

@@ -60,6 +60,35 @@ FP4R_DEV double dpp_d(double v) {
   return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
 
+// The square roots and quotients of the AdamW step are the correctly rounded binary32 ones,
+// without the scaling and special cases of the general sequences; blocks with operands
+// outside the range use the general operations.  The pass over 25 M elements is bound by
+// issue: 77 us with these, 92 without (75 with the weights' pairwise BF16 conversion).
+constexpr float kFastLo = 0x1p-100f, kFastHi = 0x1p+40f;
+
+// sqrt(v): g = v rsq(v) within a few ulp, corrected by its residual (exact in one fma).
+// Whether the last rounding is right for every significand depends on the rsq table, so
+// it was compared with the general square root over every binary32 value of
+// [2^-100, 2^100] on gfx950: none differs.
+FP4R_DEV float fast_sqrt(float v) {
+  const float r = __builtin_amdgcn_rsqf(fmaxf(v, kFastLo));
+  const float g = v * r, d = fmaf(-g, g, v);
+  return fmaf(d, 0.5f * r, g);
+}
+
+// fl32(a / b) with rb = fl64(1 / b), for a quotient in the normal range (or a = 0): a / b
+// lies at least 2^-49 (relative) from every binary32 midpoint m, since a - m b is a
+// multiple of the last place of the 49-bit product and not 0 (m is odd with 25 bits, a has
+// 24), and a rb in binary64 is within 2^-52 of it.
+FP4R_DEV float fast_div(float a, double rb) { return (float)((double)a * rb); }
+
+// 1 / b in binary64, within 2^-52: the residual e of rcp(b) is below 2^-22, so
+// x (1 + e + e^2) leaves 2^-66 and two roundings.
+FP4R_DEV double recip64(float b) {
+  const double x = (double)__builtin_amdgcn_rcpf(b), e = __builtin_fma(-(double)b, x, 1.0);
+  return __builtin_fma(x, __builtin_fma(e, e, e), x);
+}
+
 struct QAdamWArgs {
   uint16_t* w;
   const float* g;
@@ -76,6 +105,8 @@ struct QAdamWArgs {
   int has_prev, rotate, adaptive;
   uint32_t prev_mask, mask;
   float b2, c2, bc1, bc2, eps, lr, c1w;
+  double rbc1, rbc2;       // 1 / bc1, 1 / bc2
+  int eps_ok;              // the quick quotients' bounds on bc1, bc2 and eps hold
   uint32_t* status;
 };
 
@@ -96,9 +127,7 @@ __global__ __launch_bounds__(256) void k_qadamw(QAdamWArgs a) {
       g[4 * q] = x.x; g[4 * q + 1] = x.y; g[4 * q + 2] = x.z; g[4 * q + 3] = x.w;
     }
   }
-  bool ok = true;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) ok = ok && ((__float_as_uint(g[i]) & 0x7F800000u) != 0x7F800000u);
+  const bool ok = finite16(g);
   if (live && !ok) atomicOr(a.status, kStatusNonFinite);
   // this step's first moment, and the rotated amax of it for the second pass
   mom_block(g, a.mcodes, a.mscales, e0, m_prev_sg, a.has_prev != 0, a.prev_mask, a.rotate != 0, a.b1, a.c1m, m);
@@ -152,14 +181,25 @@ __global__ __launch_bounds__(256) void k_qadamw(QAdamWArgs a) {
     }
   }
   float v[16], y[16];
-  double bs = 0.0;
+  // Every v of the block is 0 or in [kFastLo, kFastHi]; v >= 0, so its bits order it, less
+  // 1 puts 0 last, and infinities and NaN lie above every number.
+  uint32_t vmin = ~0u, vmax = 0u;
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
     const float gg = g[i] * g[i];
     v[i] = (float)__builtin_fma((double)a.b2, (double)vh[i], (double)a.c2 * (double)gg);
-    y[i] = __builtin_sqrtf(v[i]);
-    bs += (double)y[i];
+    y[i] = fast_sqrt(v[i]);
+    vmin = min(vmin, __float_as_uint(v[i]) - 1u);
+    vmax = max(vmax, __float_as_uint(v[i]));
   }
+  const bool v_ok = vmin >= __float_as_uint(kFastLo) - 1u && vmax <= __float_as_uint(kFastHi);
+  if (!v_ok) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) y[i] = __builtin_sqrtf(v[i]);
+  }
+  double bs = 0.0;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) bs += (double)y[i];
   bs = bs + dpp_d<0xB1>(bs);    // lanes l, l ^ 1
   bs = bs + dpp_d<0x4E>(bs);    // l ^ 2
   bs = bs + dpp_d<0x141>(bs);   // the other quad of the half-row
@@ -178,20 +218,33 @@ __global__ __launch_bounds__(256) void k_qadamw(QAdamWArgs a) {
   const uint4 w0 = wp[0], w1 = wp[1];
   const uint32_t ww[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
   uint32_t out[8];
+  float upd16[16];
+  // The quotients lie in the normal range or are 0: bc1, bc2 <= 1, so m / bc1 and v / bc2
+  // are no smaller than m and v; with eps <= 2^20 (eps_ok) the divisor is at most 2^21, so a
+  // normal m never leads to 0, and a smaller than normal quotient is seen by its bits.
+  uint32_t qmin = ~0u, qmax = 0u, bmax = 0u;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const float mh = fast_div(m[i], a.rbc1), vb = fast_div(v[i], a.rbc2);
+    upd16[i] = fast_div(mh, recip64(fast_sqrt(vb) + a.eps));
+    const uint32_t m2 = __float_as_uint(m[i]) << 1;
+    qmin = min(qmin, m2 - 1u);
+    qmin = min(qmin, (__float_as_uint(upd16[i]) << 1) - 1u);
+    qmax = max(qmax, m2);
+    bmax = max(bmax, __float_as_uint(vb));
+  }
+  if (!(a.eps_ok && v_ok && bmax <= __float_as_uint(kFastHi) && qmin >= (0x00800000u << 1) - 1u &&
+        qmax < (0x7F800000u << 1))) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) upd16[i] = (m[i] / a.bc1) / (__builtin_sqrtf(v[i] / a.bc2) + a.eps);
+  }
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
-    uint32_t pair = 0;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int i = 2 * k + h;
-      const float wv = __uint_as_float(h ? (ww[k] & 0xFFFF0000u) : (ww[k] << 16));
-      const float mh = m[i] / a.bc1;
-      const float den = __builtin_sqrtf(v[i] / a.bc2) + a.eps;
-      const float upd = mh / den;
-      const float t0 = wv * a.c1w, t1 = a.lr * upd;
-      pair |= (uint32_t)bf16_rne(t0 - t1) << (16 * h);
-    }
-    out[k] = pair;
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    const float w0 = __uint_as_float(ww[k] << 16) * a.c1w, w1 = __uint_as_float(ww[k] & 0xFFFF0000u) * a.c1w;
+    const f32x2 t = {w0 - a.lr * upd16[2 * k], w1 - a.lr * upd16[2 * k + 1]};
+    out[k] = __builtin_bit_cast(uint32_t, __builtin_convertvector(t, bf16x2));   // v_cvt_pk_bf16_f32: bf16_rne
   }
   if (live) {
     uint4* wo = reinterpret_cast<uint4*>(a.w + e0);
@@ -212,6 +265,10 @@ hipError_t launch_qadamw(const QAdamWLaunch& p, hipStream_t st) {
   a.has_prev = p.has_prev; a.rotate = p.rotate; a.adaptive = p.adaptive;
   a.prev_mask = p.prev_mask; a.mask = p.mask;
   a.b2 = p.b2; a.c2 = p.c2; a.bc1 = p.bc1; a.bc2 = p.bc2; a.eps = p.eps; a.lr = p.lr; a.c1w = p.c1w;
+  a.rbc1 = 1.0 / (double)p.bc1;
+  a.rbc2 = 1.0 / (double)p.bc2;
+  a.eps_ok = p.bc1 > 0x1p-100f && p.bc1 <= 1.0f && p.bc2 > 0x1p-100f && p.bc2 <= 1.0f && p.eps >= kFastLo &&
+             p.eps <= 0x1p+20f;
   a.status = p.status;
   if (a.nblk <= 0) return hipSuccess;
   const dim3 grid((uint32_t)((a.nblk + 255) / 256));

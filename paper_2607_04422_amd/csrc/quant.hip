@@ -741,10 +741,7 @@ FP4R_DEV bool load_block_at(const Batch& in, int64_t b, int64_t r, int64_t c, fl
 #pragma unroll
     for (int i = 0; i < 16; ++i) u[i] = x[(r + i) * in.ld + c];
   }
-  bool ok = true;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) ok = ok && ((__float_as_uint(u[i]) & 0x7F800000u) != 0x7F800000u);
-  return ok;
+  return finite16(u);
 }
 
 template <int AXIS>
@@ -1274,9 +1271,7 @@ __global__ __launch_bounds__(256) void k_mom_update(const float* g, float* m, in
       const float4 v = gp[q];
       x[4 * q] = v.x; x[4 * q + 1] = v.y; x[4 * q + 2] = v.z; x[4 * q + 3] = v.w;
     }
-    bool ok = true;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) ok = ok && ((__float_as_uint(x[i]) & 0x7F800000u) != 0x7F800000u);
+    const bool ok = finite16(x);
     if (!ok) atomicOr(status, kStatusNonFinite);
     float mv[16];
     mom_block(x, codes, scales, e0, has_prev ? prev_sg[b] : 0.0f, has_prev, prev_mask, rotate, b1, b2, mv);
