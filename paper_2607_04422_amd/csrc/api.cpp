@@ -812,11 +812,10 @@ int check_momentum(const float* g, const float* m, int64_t batch, int64_t rows, 
   return FP4ROOT_OK;
 }
 
-// The launches of fp4root_momentum_update (arguments already checked); the status
-// word is cleared first only when reset_status is set.
+// The launches of fp4root_momentum_update (arguments already checked).
 int momentum_update_launch(const float* g, float* m, int64_t batch, int64_t rows, int64_t cols, uint8_t* codes,
                            uint8_t* scales, float* tensor_scale, float beta, uint32_t flags, uint64_t seed,
-                           int32_t step, void* ws, bool reset_status, hipStream_t st) {
+                           int32_t step, void* ws, hipStream_t st) {
   if (batch == 0) return FP4ROOT_OK;
   Carver cv(ws);
   uint32_t* status = cv.take<uint32_t>(1);
@@ -824,7 +823,7 @@ int momentum_update_launch(const float* g, float* m, int64_t batch, int64_t rows
   const bool rot = flags & FP4ROOT_F_HADAMARD, ad = flags & FP4ROOT_F_ADAPTIVE46;
   const float b1 = beta, b2 = 1.0f - beta;   // b2 = fl32(1 - beta)
   const uint32_t mask = sign_mask(seed, step), prev_mask = step > 0 ? sign_mask(seed, step - 1) : 0u;
-  FP4R_TRY(launch_init(reset_status ? status : nullptr, sc, batch, nullptr, 0, st));
+  FP4R_TRY(launch_init(status, sc, batch, nullptr, 0, st));
   FP4R_TRY(launch_mom_update(g, m, batch, rows, cols, codes, scales, tensor_scale, step > 0, prev_mask,
                              mask, rot, b1, b2, sc, status, st));
   const Batch in{m, batch, rows, cols, cols, rows * cols};
@@ -847,7 +846,7 @@ int fp4root_momentum_update(const float* g, float* m, int64_t batch, int64_t row
   if (rc != FP4ROOT_OK) return rc;
   if (!ws || ws_bytes < fp4root_momentum_workspace(batch, rows, cols)) return FP4ROOT_ERR_WORKSPACE;
   return momentum_update_launch(g, m, batch, rows, cols, codes, scales, tensor_scale, beta, flags, seed, step, ws,
-                                true, (hipStream_t)stream);
+                                (hipStream_t)stream);
 }
 
 namespace {
@@ -958,10 +957,9 @@ size_t fp4root_root_step_workspace(const fp4root_param* params, int64_t count, c
   if (count < 0 || (count > 0 && !params) || !ns) return 0;
   size_t need = kAlign;
   for (int64_t i = 0; i < count; ++i) {
-    const size_t mw = fp4root_momentum_workspace(1, params[i].rows, params[i].cols);
-    if (mw == 0) return 0;
-    need = std::max(need, mw);
+    if (!dims_ok(params[i].rows, params[i].cols)) return 0;
   }
+  need = std::max(need, fp4root_momentum_workspace(std::min<int64_t>(count, kMaxRootChunk), 16, 16));
   if (count > 0) {
     const std::vector<fp4root_matrix> mats = root_matrices(params, count);
     const size_t ow = fp4root_orthogonalize_workspace(mats.data(), count, ns);
@@ -974,6 +972,45 @@ size_t fp4root_root_step_workspace(const fp4root_param* params, int64_t count, c
 namespace {
 int orthogonalize_launch(const fp4root_matrix* mats, int64_t count, const fp4root_ns_config* cfg, void* ws,
                          bool reset_status, hipStream_t st);
+}  // namespace
+
+namespace {
+bool overlap(const void* a, int64_t na, const void* b, int64_t nb) {
+  const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
+  return x < y + (uintptr_t)nb && y < x + (uintptr_t)na;
+}
+
+// Two parameters that must not share a launch: one writes what the other reads or writes
+// (one weight listed twice, for instance), so their order counts.
+bool depend(const fp4root_param& a, const fp4root_param& b) {
+  const int64_t na = a.rows * a.cols, nb = b.rows * b.cols;
+  return overlap(a.w, 2 * na, b.w, 2 * nb) || overlap(a.m, 4 * na, b.m, 4 * nb) || overlap(a.g, 4 * na, b.m, 4 * nb) ||
+         overlap(a.m, 4 * na, b.g, 4 * nb) || overlap(a.m_codes, na / 2, b.m_codes, nb / 2) ||
+         overlap(a.m_scales, na / 16, b.m_scales, nb / 16) || a.m_tensor_scale == b.m_tensor_scale;
+}
+
+// The longest run of parameters from `first` on that one launch of each kind can take.
+void root_chunk(const fp4root_param* params, int64_t count, int64_t first, const fp4root_root_config& rc,
+                RootChunk& ch) {
+  ch.count = 0;
+  int64_t end = 0;
+  for (int64_t i = first; i < count && ch.count < kMaxRootChunk; ++i) {
+    const fp4root_param& p = params[i];
+    const int64_t nblk = p.rows * p.cols / 16, wgs = (nblk + 255) / 256;
+    bool fits = end + wgs <= kMaxRootBlocks;
+    for (int64_t k = first; k < i && fits; ++k) fits = !depend(params[k], p);
+    if (ch.count > 0 && !fits) break;
+    const uint64_t seed = rc.momentum_seed + (uint64_t)i;
+    // scale 0: the default update scale sqrt(max(1, rows / cols)), rounded once
+    const float s = p.scale > 0.0f ? p.scale
+                                   : (float)std::sqrt(std::max(1.0, (double)p.rows / (double)p.cols));
+    end += wgs;
+    ch.p[ch.count] = RootRef{p.g, p.m, p.m_codes, p.m_scales, p.m_tensor_scale, p.w, nblk,
+                             splitmix64(seed ^ 0x5352ull, (uint64_t)rc.step + 1), sign_mask(seed, rc.step),
+                             rc.step > 0 ? sign_mask(seed, rc.step - 1) : 0u, rc.lr * s};
+    ch.end[ch.count++] = (uint32_t)end;
+  }
+}
 }  // namespace
 
 int fp4root_root_step(const fp4root_param* params, int64_t count, const fp4root_root_config* rc,
@@ -1000,23 +1037,26 @@ int fp4root_root_step(const fp4root_param* params, int64_t count, const fp4root_
   hipStream_t st = (hipStream_t)stream;
   // one status word for the whole step (the first word of the workspace, shared by
   // the stages, which run in stream order and reuse the rest of the workspace)
-  FP4R_TRY(launch_fill_u32(reinterpret_cast<uint32_t*>(ws), 0u, 1, st));
-  for (int64_t i = 0; i < count; ++i) {
-    const fp4root_param& p = params[i];
-    const int rc1 = momentum_update_launch(p.g, p.m, 1, p.rows, p.cols, p.m_codes, p.m_scales, p.m_tensor_scale,
-                                           rc->beta, rc->momentum_flags, rc->momentum_seed + (uint64_t)i, rc->step,
-                                           ws, false, st);
-    if (rc1 != FP4ROOT_OK) return rc1;
+  uint32_t* status = reinterpret_cast<uint32_t*>(ws);
+  if (count == 0) FP4R_TRY(launch_fill_u32(status, 0u, 1, st));
+  Carver cv(ws);
+  cv.take<uint32_t>(1);
+  MatScalars* sc = cv.take<MatScalars>((size_t)std::min<int64_t>(count, kMaxRootChunk));
+  const float b1 = rc->beta, b2 = 1.0f - b1;   // b2 = fl32(1 - beta)
+  const uint32_t mf = rc->momentum_flags;
+  const float lw = rc->lr * rc->wd, c1 = 1.0f - lw;
+  RootChunk ch;
+  for (int64_t i = 0; i < count; i += ch.count) {
+    root_chunk(params, count, i, *rc, ch);
+    FP4R_TRY(launch_init(i == 0 ? status : nullptr, sc, ch.count, nullptr, 0, st));
+    FP4R_TRY(launch_root_momentum(ch, rc->step > 0, mf & FP4ROOT_F_HADAMARD, mf & FP4ROOT_F_ADAPTIVE46,
+                                  mf & FP4ROOT_F_STOCHASTIC, b1, b2, sc, status, st));
   }
   const int rc2 = orthogonalize_launch(mats.data(), count, ns, ws, false, st);
   if (rc2 != FP4ROOT_OK) return rc2;
-  for (int64_t i = 0; i < count; ++i) {
-    const fp4root_param& p = params[i];
-    // scale 0: the default update scale sqrt(max(1, rows / cols)), rounded once
-    const float s = p.scale > 0.0f ? p.scale
-                                   : (float)std::sqrt(std::max(1.0, (double)p.rows / (double)p.cols));
-    const int rc3 = fp4root_apply_update(p.w, p.m, p.rows * p.cols, rc->lr, rc->wd, s, stream);
-    if (rc3 != FP4ROOT_OK) return rc3;
+  for (int64_t i = 0; i < count; i += ch.count) {
+    root_chunk(params, count, i, *rc, ch);
+    FP4R_TRY(launch_root_apply(ch, c1, st));
   }
   return FP4ROOT_OK;
 }

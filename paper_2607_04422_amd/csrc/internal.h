@@ -245,6 +245,45 @@ hipError_t launch_mom_update(const float* g, float* m, int64_t batch, int64_t ro
 // elements (a multiple of 8; W and O 16-byte aligned).
 hipError_t launch_apply_update(uint16_t* w, const float* o, int64_t count, float c1, float c2, hipStream_t st);
 
+// Parameters of an optimizer step, for the launches that take several at a time (the
+// workgroups of parameter i are [end[i - 1], end[i]) of the grid).
+constexpr int kMaxRootChunk = 32;
+constexpr int64_t kMaxRootBlocks = int64_t(1) << 28;   // per launch, when it takes more than one parameter
+struct RootRef {
+  const float* g;
+  float* m;
+  uint8_t* codes;
+  uint8_t* scales;
+  float* tensor_scale;
+  uint16_t* w;
+  int64_t nblk;          // 16-element blocks
+  uint64_t sr_key;
+  uint32_t mask, prev_mask;
+  float c2;              // fl32(lr s)
+};
+struct RootChunk {
+  RootRef p[kMaxRootChunk];
+  uint32_t end[kMaxRootChunk];
+  int count;
+};
+// The parameter of a workgroup and its index among that parameter's workgroups (uniform).
+__device__ inline int root_param(const RootChunk& ch, uint32_t wg, uint32_t& local) {
+  int lo = 0, hi = ch.count - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi) >> 1;
+    if (wg < ch.end[mid]) hi = mid;
+    else lo = mid + 1;
+  }
+  local = wg - (lo ? ch.end[lo - 1] : 0u);
+  return lo;
+}
+// launch_mom_update, then launch_encode_sr (or launch_encode) of each parameter's m;
+// parameter i of the chunk uses sc[i].
+hipError_t launch_root_momentum(const RootChunk& ch, bool has_prev, bool rotate, bool adaptive, bool sr, float b1,
+                                float b2, MatScalars* sc, uint32_t* status, hipStream_t st);
+// launch_apply_update of each parameter (O = m).
+hipError_t launch_root_apply(const RootChunk& ch, float c1, hipStream_t st);
+
 // Second pass of a quantized-state AdamW step on a flat parameter of n elements:
 // re-derive m_t from g and the unchanged previous first-moment state and encode it
 // in place (stochastically when sr), tensor scale from amax slot 0 of sc[0].

@@ -8,25 +8,41 @@
 
 namespace fp4r {
 
+FP4R_DEV void apply_octet(uint16_t* w, const float* o, int64_t i, float c1, float c2) {
+  const uint4 wv = reinterpret_cast<const uint4*>(w)[i];
+  const float4 o0 = reinterpret_cast<const float4*>(o)[2 * i];
+  const float4 o1 = reinterpret_cast<const float4*>(o)[2 * i + 1];
+  const float ov[8] = {o0.x, o0.y, o0.z, o0.w, o1.x, o1.y, o1.z, o1.w};
+  const uint32_t ww[4] = {wv.x, wv.y, wv.z, wv.w};
+  uint32_t out[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const float w0 = __uint_as_float(ww[k] << 16), w1 = __uint_as_float(ww[k] & 0xFFFF0000u);
+    const float a0 = w0 * c1, b0 = c2 * ov[2 * k];
+    const float a1 = w1 * c1, b1 = c2 * ov[2 * k + 1];
+    out[k] = (uint32_t)bf16_rne(a0 - b0) | ((uint32_t)bf16_rne(a1 - b1) << 16);
+  }
+  reinterpret_cast<uint4*>(w)[i] = make_uint4(out[0], out[1], out[2], out[3]);
+}
+
 __global__ __launch_bounds__(256) void k_apply_update(uint16_t* w, const float* o, int64_t n8, float c1,
                                                       float c2) {
   const int64_t stride = (int64_t)gridDim.x * 256;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n8; i += stride) {
-    const uint4 wv = reinterpret_cast<const uint4*>(w)[i];
-    const float4 o0 = reinterpret_cast<const float4*>(o)[2 * i];
-    const float4 o1 = reinterpret_cast<const float4*>(o)[2 * i + 1];
-    const float ov[8] = {o0.x, o0.y, o0.z, o0.w, o1.x, o1.y, o1.z, o1.w};
-    const uint32_t ww[4] = {wv.x, wv.y, wv.z, wv.w};
-    uint32_t out[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const float w0 = __uint_as_float(ww[k] << 16), w1 = __uint_as_float(ww[k] & 0xFFFF0000u);
-      const float a0 = w0 * c1, b0 = c2 * ov[2 * k];
-      const float a1 = w1 * c1, b1 = c2 * ov[2 * k + 1];
-      out[k] = (uint32_t)bf16_rne(a0 - b0) | ((uint32_t)bf16_rne(a1 - b1) << 16);
-    }
-    reinterpret_cast<uint4*>(w)[i] = make_uint4(out[0], out[1], out[2], out[3]);
-  }
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n8; i += stride) apply_octet(w, o, i, c1, c2);
+}
+
+// Several parameters, two octets per thread (ch.end counts workgroups of 256 blocks).
+__global__ __launch_bounds__(256) void k_root_apply(RootChunk ch, float c1) {
+  uint32_t wg;
+  const RootRef& p = ch.p[root_param(ch, blockIdx.x, wg)];
+  const int64_t i = (int64_t)wg * 512 + threadIdx.x;
+  if (i < p.nblk * 2) apply_octet(p.w, p.m, i, c1, p.c2);
+  if (i + 256 < p.nblk * 2) apply_octet(p.w, p.m, i + 256, c1, p.c2);
+}
+
+hipError_t launch_root_apply(const RootChunk& ch, float c1, hipStream_t st) {
+  hipLaunchKernelGGL(k_root_apply, dim3(ch.end[ch.count - 1]), dim3(256), 0, st, ch, c1);
+  return hipGetLastError();
 }
 
 hipError_t launch_apply_update(uint16_t* w, const float* o, int64_t count, float c1, float c2, hipStream_t st) {

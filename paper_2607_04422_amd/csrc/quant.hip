@@ -1252,18 +1252,13 @@ hipError_t launch_encode_sr(const Batch& in, uint32_t sign_mask, bool rotate, bo
 // inverse rotation), forms m = fl32(b1 m_hat + b2 g) (exact products, one binary64
 // rounding, then binary32), writes m and records the amax of m rotated with
 // `mask` (the tensor scale of the next state) in amax slot 0.
-__global__ __launch_bounds__(256) void k_mom_update(const float* g, float* m, int64_t rows, int64_t cols,
-                                                    const uint8_t* codes, const uint8_t* scales,
-                                                    const float* prev_sg, int has_prev, uint32_t prev_mask,
-                                                    uint32_t mask, int rotate, float b1, float b2,
-                                                    MatScalars* sc, uint32_t* status) {
+FP4R_DEV void mom_update_block(const float* g, float* m, int64_t e0, bool in, const uint8_t* codes,
+                               const uint8_t* scales, float prev_sg, int has_prev, uint32_t prev_mask,
+                               uint32_t mask, int rotate, float b1, float b2, MatScalars* sc, uint32_t wg,
+                               uint32_t* status) {
   __shared__ float red[4];
-  const int64_t b = blockIdx.y;
-  const int64_t blk = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t nblk = rows * cols / 16;
   float amax = 0.0f;
-  if (blk < nblk) {
-    const int64_t e0 = b * rows * cols + blk * 16;
+  if (in) {
     float x[16];
     const float4* gp = reinterpret_cast<const float4*>(g + e0);
 #pragma unroll
@@ -1274,7 +1269,7 @@ __global__ __launch_bounds__(256) void k_mom_update(const float* g, float* m, in
     const bool ok = finite16(x);
     if (!ok) atomicOr(status, kStatusNonFinite);
     float mv[16];
-    mom_block(x, codes, scales, e0, has_prev ? prev_sg[b] : 0.0f, has_prev, prev_mask, rotate, b1, b2, mv);
+    mom_block(x, codes, scales, e0, prev_sg, has_prev, prev_mask, rotate, b1, b2, mv);
     float4* mp = reinterpret_cast<float4*>(m + e0);
 #pragma unroll
     for (int q = 0; q < 4; ++q) mp[q] = make_float4(mv[4 * q], mv[4 * q + 1], mv[4 * q + 2], mv[4 * q + 3]);
@@ -1291,8 +1286,69 @@ __global__ __launch_bounds__(256) void k_mom_update(const float* g, float* m, in
   __syncthreads();
   if (threadIdx.x == 0) {
     const float mm = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-    amax_record(&sc[b], 0, blockIdx.x, mm);
+    amax_record(sc, 0, wg, mm);
   }
+}
+
+__global__ __launch_bounds__(256) void k_mom_update(const float* g, float* m, int64_t rows, int64_t cols,
+                                                    const uint8_t* codes, const uint8_t* scales,
+                                                    const float* prev_sg, int has_prev, uint32_t prev_mask,
+                                                    uint32_t mask, int rotate, float b1, float b2,
+                                                    MatScalars* sc, uint32_t* status) {
+  const int64_t b = blockIdx.y;
+  const int64_t blk = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  mom_update_block(g, m, b * rows * cols + blk * 16, blk < rows * cols / 16, codes, scales,
+                   has_prev ? prev_sg[b] : 0.0f, has_prev, prev_mask, mask, rotate, b1, b2, &sc[b], blockIdx.x,
+                   status);
+}
+
+// The two passes over the parameters of an optimizer step.  One launch of each kind for up
+// to kMaxRootChunk of them: small parameters are bound by the launches (12 parameters of 64
+// to 256 K elements: 188 us in 49 launches of their own, 25 in 4).
+__global__ __launch_bounds__(256) void k_root_mom_update(RootChunk ch, int has_prev, int rotate, float b1, float b2,
+                                                         MatScalars* sc, uint32_t* status) {
+  uint32_t wg;
+  const int i = root_param(ch, blockIdx.x, wg);
+  const RootRef& p = ch.p[i];
+  const int64_t blk = (int64_t)wg * 256 + threadIdx.x;
+  mom_update_block(p.g, p.m, blk * 16, blk < p.nblk, p.codes, p.scales, has_prev ? p.tensor_scale[0] : 0.0f, has_prev,
+                   p.prev_mask, p.mask, rotate, b1, b2, &sc[i], wg, status);
+}
+
+template <bool SR>
+__global__ __launch_bounds__(256) void k_root_mom_encode(RootChunk ch, int rotate, int adaptive, MatScalars* sc) {
+  uint32_t wg;
+  const int i = root_param(ch, blockIdx.x, wg);
+  const RootRef& p = ch.p[i];
+  const int64_t blk = (int64_t)wg * 256 + threadIdx.x;
+  const float sg = tensor_scale_from_amax(amax_read(sc[i], 0));
+  if (blk == 0) p.tensor_scale[0] = sg;
+  if (blk >= p.nblk) return;
+  float u[16];
+  const float4* mp = reinterpret_cast<const float4*>(p.m + blk * 16);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const float4 v = mp[q];
+    u[4 * q] = v.x; u[4 * q + 1] = v.y; u[4 * q + 2] = v.z; u[4 * q + 3] = v.w;
+  }
+  const float kf = rotate_for_quant(u, p.mask, rotate, sg);
+  uint32_t scale, n2;
+  uint64_t c;
+  quant_block(u, sg, adaptive != 0, scale, c, n2, false, kf);
+  if constexpr (SR) c = sr_block_codes(u, kf, scale, sg, c, p.sr_key, (uint64_t)(blk * 16));
+  *reinterpret_cast<uint2*>(p.codes + blk * 8) = make_uint2((uint32_t)c, (uint32_t)(c >> 32));
+  p.scales[blk] = (uint8_t)scale;
+}
+
+hipError_t launch_root_momentum(const RootChunk& ch, bool has_prev, bool rotate, bool adaptive, bool sr, float b1,
+                                float b2, MatScalars* sc, uint32_t* status, hipStream_t st) {
+  const dim3 grid(ch.end[ch.count - 1]);
+  hipLaunchKernelGGL(k_root_mom_update, grid, dim3(256), 0, st, ch, (int)has_prev, (int)rotate, b1, b2, sc, status);
+  if (sr)
+    hipLaunchKernelGGL(k_root_mom_encode<true>, grid, dim3(256), 0, st, ch, (int)rotate, (int)adaptive, sc);
+  else
+    hipLaunchKernelGGL(k_root_mom_encode<false>, grid, dim3(256), 0, st, ch, (int)rotate, (int)adaptive, sc);
+  return hipGetLastError();
 }
 
 // Re-encode the first moment of a flat parameter (batch 1, n elements) in place,
