@@ -745,7 +745,7 @@ void launch_fp4_form(dim3 grid, hipStream_t st, const GemmFp4Batch& gb, const Ge
   if (gb.count == 1)
     hipLaunchKernelGGL((k_gemm_fp4<MODE, C, ACC32>), grid, dim3(C::NW * 64), 0, st, gb.p[0], (int)gb.tiles_m[0],
                        (int)gb.tiles_n[0], gb.tiles_per_mat[0], gb.wide, f);
-  else if constexpr (MODE != kModeUpdateX)
+  else
     hipLaunchKernelGGL((k_gemm_fp4_multi<MODE, C, ACC32>), grid, dim3(C::NW * 64), 0, st, gb);
 }
 
@@ -827,8 +827,6 @@ hipError_t launch_gemm_fp4_batch(GemmMode mode, const GemmFp4Args* list, int cou
   const int64_t rest = total % kFp4Round;
   gb.wide = wide && forced == 0 && rest <= kTailMax ? total - rest : total;
   const dim3 grid((uint32_t)(gb.wide + 4 * (total - gb.wide)));
-  // several products per launch: the symmetric products only
-  if (gb.count > 1 && ((fin && fin->count > 0) || mode == kModeUpdateX)) return hipErrorInvalidValue;
   GemmFin f;
   if (fin) f = *fin;
   if (gb.p[0].acc32) launch_fp4_kernel<true>(mode, wide, grid, st, gb, f);

@@ -220,11 +220,25 @@ hipError_t launch_encode(const Batch& in, int axis, uint32_t sign_mask, bool rot
                          bool adaptive46, MatScalars* sc, int slot, const QOut& out,
                          float* tensor_scale, hipStream_t st, float* tau_out = nullptr);
 
-// The operand Q1x16 of a batch of contiguous rows x K matrices (row blocks), with the
-// tensor scale from amax slot `slot`; writes sc[b].sg[slot].
-hipError_t launch_encode_operand(const float* x, int64_t batch, int64_t rows, int64_t K, int64_t bstride,
-                                 uint32_t sign_mask, bool rotate, bool adaptive46, MatScalars* sc, int slot,
-                                 const OperandOut& out, hipStream_t st);
+// One problem of the operand encoders: a batch of contiguous rows x K matrices and the
+// operands it becomes: Q1x16 along K with the tensor scale from amax slot `slot_n` (and the
+// transposed one from `slot_m` for launch_encode_x2); the scales go to sc[b].sg.
+struct EncodeArgs {
+  const float* x;
+  int64_t batch, rows, K, bstride;
+  MatScalars* sc;
+  OperandOut q, qt;
+};
+constexpr int kMaxEncode = 4;
+struct EncodeBatch {
+  EncodeArgs p[kMaxEncode];
+  uint32_t per[kMaxEncode], end[kMaxEncode];   // workgroups per matrix; up to and with problem i
+  int count;
+};
+
+// The operands of up to kMaxEncode problems (row blocks) in one launch.
+hipError_t launch_encode_operand(const EncodeArgs* list, int count, uint32_t sign_mask, bool rotate, bool adaptive46,
+                                 int slot, hipStream_t st);
 
 // launch_encode along rows (axis 1, no clipping) with the element
 // magnitudes rounded stochastically (fp4root_momentum_update); draws from `sr_key`.
@@ -320,10 +334,8 @@ hipError_t launch_qadamw(const QAdamWLaunch& p, hipStream_t st);
 // qx (slot_n), qXt along m into qxt (slot_m, stored transposed).
 // reset_mask: amax slots of every matrix set to zero by the launch (for the
 // products that run after it; never slot_n or slot_m).
-hipError_t launch_encode_x2(const float* x, int64_t batch, int64_t m, int64_t n, int64_t x_bstride,
-                            uint32_t sign_mask, bool rotate, bool adaptive46, MatScalars* sc,
-                            int slot_n, int slot_m, const OperandOut& qx, const OperandOut& qxt, hipStream_t st,
-                            uint32_t reset_mask = 0);
+hipError_t launch_encode_x2(const EncodeArgs* list, int count, uint32_t sign_mask, bool rotate, bool adaptive46,
+                            int slot_n, int slot_m, hipStream_t st, uint32_t reset_mask);
 
 // ---------------------------------------------------------------------------
 // GEMMs (all operands K-contiguous: C[i][j] = sum_k A[i][k] B[j][k]).
@@ -387,10 +399,9 @@ struct GemmFp4Batch {
   int32_t count;
 };
 
-// count products of one mode (1 <= count <= kMaxGemmProblems; more than one for the
-// symmetric products only) in one launch, the products with the longest contraction
-// first; fin (host, may be null) routes the output of a single update product to the
-// callers' matrices.
+// count products of one mode (1 <= count <= kMaxGemmProblems) in one launch, the products
+// with the longest contraction first; fin (host, may be null) routes the output of a
+// single update product to the callers' matrices.
 hipError_t launch_gemm_fp4_batch(GemmMode mode, const GemmFp4Args* list, int count, hipStream_t st,
                                  const GemmFin* fin = nullptr);
 // Tile form of the NVFP4 products (0: chosen per launch, 1: narrow, 2: wide; see

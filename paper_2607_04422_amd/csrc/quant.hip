@@ -909,18 +909,58 @@ FP4R_DEV uint2 quad_stage_words(uint64_t codes, int q) {
   return q < 2 ? make_uint2(l0, l1) : make_uint2(h0, h1);
 }
 
+// The operand encoders take several problems per launch (one per shape group of a step:
+// ten launches of 5 us instead of five for two groups of small matrices, and no gap between
+// them), each workgroup finding its own; one problem alone needs no search, and its matrices
+// are the grid's second dimension.
+struct EncodeSlot {
+  int problem;
+  int64_t mat;
+  uint32_t wg;   // within the matrix
+};
+template <bool MULTI>
+FP4R_DEV EncodeSlot encode_slot(const EncodeBatch& eb) {
+  if (!MULTI) return EncodeSlot{0, (int64_t)blockIdx.y, blockIdx.x};
+  int i = 0;
+  while (i + 1 < eb.count && blockIdx.x >= eb.end[i]) ++i;
+  const uint32_t local = blockIdx.x - (i ? eb.end[i - 1] : 0u), mat = local / eb.per[i];
+  return EncodeSlot{i, (int64_t)mat, local - mat * eb.per[i]};
+}
+
+// The table of a launch over list[0 .. count) with per(i) workgroups per matrix; false when
+// the problems must go one by one (a grid too long for 32 bits).
+template <class F>
+bool encode_table(const EncodeArgs* list, int count, F per, EncodeBatch& eb) {
+  eb.count = count;
+  int64_t end = 0;
+  for (int i = 0; i < count; ++i) {
+    eb.p[i] = list[i];
+    const int64_t n = per(list[i]);
+    end += n * list[i].batch;
+    if (count > 1 && end > int64_t(1) << 30) return false;
+    eb.per[i] = (uint32_t)n;
+    eb.end[i] = (uint32_t)end;
+  }
+  return true;
+}
+
 // A products' operand from row blocks: each wave takes 16 rows x one 64-element stage,
 // lane 4i + k block k of row i (consecutive waves take consecutive stages of a row
 // group, so a workgroup reads whole 256-byte row segments).
-__global__ __launch_bounds__(256) void k_encode_operand(const float* x, int64_t rows, int64_t K, int64_t bstride,
-                                                        uint32_t mask, int rotate, int adaptive, MatScalars* sc,
-                                                        int slot, OperandOut out) {
-  const int64_t b = blockIdx.y;
+template <bool MULTI>
+__global__ __launch_bounds__(256) void k_encode_operand(EncodeBatch eb, uint32_t mask, int rotate, int adaptive,
+                                                        int slot) {
+  const EncodeSlot es = encode_slot<MULTI>(eb);
+  const EncodeArgs& ea = eb.p[es.problem];
+  const float* const x = ea.x;
+  const int64_t rows = ea.rows, K = ea.K, bstride = ea.bstride, b = es.mat;
+  MatScalars* const sc = ea.sc;
+  const OperandOut& out = ea.q;
   const uint32_t nst = (uint32_t)((K + 63) / 64);
   // uniform over the wave, so the division by the stage count is scalar work
-  const uint32_t wv = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t wv = es.wg * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const float sg = tensor_scale_from_amax(amax_read(sc[b], slot));
-  if (blockIdx.x == 0 && threadIdx.x == 0) sc[b].sg[slot] = sg;
+  if (es.wg == 0 && threadIdx.x == 0) sc[b].sg[slot] = sg;
   const uint32_t rg = wv / nst, st = wv - rg * nst;
   if ((int64_t)rg * 16 >= rows) return;   // rows is a multiple of 16: whole waves leave
   const int lane = (int)(threadIdx.x & 63), q = lane & 3;
@@ -953,14 +993,26 @@ __global__ __launch_bounds__(256) void k_encode_operand(const float* x, int64_t 
   }
 }
 
-hipError_t launch_encode_operand(const float* x, int64_t batch, int64_t rows, int64_t K, int64_t bstride,
-                                 uint32_t sign_mask, bool rotate, bool adaptive46, MatScalars* sc, int slot,
-                                 const OperandOut& out, hipStream_t st) {
-  if (rows % 16 != 0 || K % 16 != 0) return hipErrorInvalidValue;
-  const int64_t waves = rows / 16 * ((K + 63) / 64);
-  const dim3 grid((uint32_t)((waves + 3) / 4), (uint32_t)batch);
-  hipLaunchKernelGGL(k_encode_operand, grid, dim3(256), 0, st, x, rows, K, bstride, sign_mask, (int)rotate,
-                     (int)adaptive46, sc, slot, out);
+hipError_t launch_encode_operand(const EncodeArgs* list, int count, uint32_t sign_mask, bool rotate, bool adaptive46,
+                                 int slot, hipStream_t st) {
+  if (count < 1 || count > kMaxEncode) return hipErrorInvalidValue;
+  for (int i = 0; i < count; ++i)
+    if (list[i].rows % 16 != 0 || list[i].K % 16 != 0) return hipErrorInvalidValue;
+  EncodeBatch eb;
+  auto per = [](const EncodeArgs& e) { return (e.rows / 16 * ((e.K + 63) / 64) + 3) / 4; };
+  if (!encode_table(list, count, per, eb)) {
+    for (int i = 0; i < count; ++i) {
+      const hipError_t e = launch_encode_operand(list + i, 1, sign_mask, rotate, adaptive46, slot, st);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
+  if (count == 1)
+    hipLaunchKernelGGL(k_encode_operand<false>, dim3(eb.per[0], (uint32_t)list[0].batch), dim3(256), 0, st, eb,
+                       sign_mask, (int)rotate, (int)adaptive46, slot);
+  else
+    hipLaunchKernelGGL(k_encode_operand<true>, dim3(eb.end[count - 1]), dim3(256), 0, st, eb, sign_mask, (int)rotate,
+                       (int)adaptive46, slot);
   return hipGetLastError();
 }
 
@@ -970,9 +1022,14 @@ hipError_t launch_encode_operand(const float* x, int64_t batch, int64_t rows, in
 // Eight waves per SIMD (64 VGPRs and 24 bytes of scratch per lane) rather than the
 // six its 73 registers would allow: the extra waves cover part of its LDS and
 // memory waits (about 2.5 % less time per launch).
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k_encode_x2(const float* x, int64_t m, int64_t n, int64_t x_bstride,
-                                                   uint32_t mask, int rotate, int adaptive, MatScalars* sc,
-                                                   int slot_n, int slot_m, OperandOut qx, OperandOut qxt, uint32_t reset_mask) {
+template <bool MULTI>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k_encode_x2(EncodeBatch eb, uint32_t mask, int rotate, int adaptive,
+                                                   int slot_n, int slot_m, uint32_t reset_mask) {
+  const EncodeSlot es = encode_slot<MULTI>(eb);
+  const EncodeArgs& ea = eb.p[es.problem];
+  const int64_t m = ea.rows, n = ea.K, b = es.mat;
+  MatScalars* const sc = ea.sc;
+  const OperandOut &qx = ea.q, &qxt = ea.qt;
   // rows padded to 68 floats: 16-byte row slices for the row blocks.  gfx950 serves
   // a 128-bit LDS read 16 lanes per cycle over 64 banks and a 128-bit write 8 lanes
   // per cycle over 32 banks: the 16 lanes of one read (4 rows x 4 slices) and 64
@@ -980,13 +1037,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k
   // one write (2 rows x 4 slices) because lanes with bit 1 of q set store their
   // four slices in the order k ^ 2
   __shared__ __align__(16) float tile[kT][kT + 4];
-  const int64_t b = blockIdx.y;
   const uint32_t tn = (uint32_t)cdiv(n, kT);   // tiles per row of tiles (grid.x < 2^32)
-  const int64_t r0 = (int64_t)(blockIdx.x / tn) * kT, c0 = (int64_t)(blockIdx.x % tn) * kT;
-  const float* X = x + b * x_bstride;
+  const int64_t r0 = (int64_t)(es.wg / tn) * kT, c0 = (int64_t)(es.wg % tn) * kT;
+  const float* X = ea.x + b * ea.bstride;
   const float sgn = tensor_scale_from_amax(amax_read(sc[b], slot_n));
   const float sgm = tensor_scale_from_amax(amax_read(sc[b], slot_m));
-  if (blockIdx.x == 0) {
+  if (es.wg == 0) {
     if (threadIdx.x == 0) {
       sc[b].sg[slot_n] = sgn;
       sc[b].sg[slot_m] = sgm;
@@ -1197,14 +1253,26 @@ hipError_t launch_untile_nvfp4(const uint8_t* codes, const uint8_t* scales, int6
   return hipGetLastError();
 }
 
-hipError_t launch_encode_x2(const float* x, int64_t batch, int64_t m, int64_t n, int64_t x_bstride,
-                            uint32_t sign_mask, bool rotate, bool adaptive46, MatScalars* sc,
-                            int slot_n, int slot_m, const OperandOut& qx, const OperandOut& qxt, hipStream_t st,
-                            uint32_t reset_mask) {
+hipError_t launch_encode_x2(const EncodeArgs* list, int count, uint32_t sign_mask, bool rotate, bool adaptive46,
+                            int slot_n, int slot_m, hipStream_t st, uint32_t reset_mask) {
+  if (count < 1 || count > kMaxEncode) return hipErrorInvalidValue;
   if (reset_mask & ((1u << slot_n) | (1u << slot_m))) return hipErrorInvalidValue;
-  const dim3 grid((uint32_t)(cdiv(m, kT) * cdiv(n, kT)), (uint32_t)batch);
-  hipLaunchKernelGGL(k_encode_x2, grid, dim3(256), 0, st, x, m, n, x_bstride, sign_mask, (int)rotate,
-                     (int)adaptive46, sc, slot_n, slot_m, qx, qxt, reset_mask);
+  EncodeBatch eb;
+  auto per = [](const EncodeArgs& e) { return cdiv(e.rows, kT) * cdiv(e.K, kT); };
+  if (!encode_table(list, count, per, eb)) {
+    for (int i = 0; i < count; ++i) {
+      const hipError_t e =
+          launch_encode_x2(list + i, 1, sign_mask, rotate, adaptive46, slot_n, slot_m, st, reset_mask);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
+  if (count == 1)
+    hipLaunchKernelGGL(k_encode_x2<false>, dim3(eb.per[0], (uint32_t)list[0].batch), dim3(256), 0, st, eb, sign_mask,
+                       (int)rotate, (int)adaptive46, slot_n, slot_m, reset_mask);
+  else
+    hipLaunchKernelGGL(k_encode_x2<true>, dim3(eb.end[count - 1]), dim3(256), 0, st, eb, sign_mask, (int)rotate,
+                       (int)adaptive46, slot_n, slot_m, reset_mask);
   return hipGetLastError();
 }
 
