@@ -80,6 +80,16 @@ hipError_t launch_bf16_update_blaslt(const uint16_t* b16, const uint16_t* xb, fl
                                      int64_t n, int64_t x_bstride, float a, void* ws, size_t ws_bytes,
                                      hipStream_t st) {
   if (batch == 0) return hipSuccess;
+  // No strided batch of odd length: one of 3 (3072 x 8192) gave a wrong first matrix and, in
+  // another call, a memory fault.  The cause is not known (its plan, layouts and buffers
+  // check out), so such a batch is not handed to the library: an even one, then a single.
+  if (batch > 1 && (batch & 1)) {
+    const int64_t k = batch - 1;
+    const hipError_t e = launch_bf16_update_blaslt(b16, xb, x, k, m, n, x_bstride, a, ws, ws_bytes, st);
+    if (e != hipSuccess) return e;
+    return launch_bf16_update_blaslt(b16 + k * m * m, xb + k * m * n, x + k * x_bstride, 1, m, n, x_bstride, a, ws,
+                                     ws_bytes, st);
+  }
   const Plan* p = plan_for(batch, m, n, x_bstride, ws_bytes);
   if (!p) return hipErrorNotSupported;
   hipblasLtHandle_t h;
