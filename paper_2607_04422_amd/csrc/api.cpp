@@ -1209,13 +1209,42 @@ int orthogonalize_launch(const fp4root_matrix* mats, int64_t count, const fp4roo
     if (clip) quantile_index(m * n, cfg->clip_quantile, lo, frac);
     FP4R_TRY(launch_init(reset_status && gi == 0 ? status : nullptr, w.step.sc, B, w.hist,
                          clip ? (int64_t)chunk_hist_words(B) : 0, st));
-    // clip, normalise, orient
+    // the last update is written straight to the callers' matrices
+    if (!bf16 && cfg->steps > 0)
+      for (size_t c0 = 0; c0 < all.size(); c0 += kMaxChunk)
+        gout[gi].push_back(make_chunk(all, c0, std::min(all.size() - c0, (size_t)kMaxChunk), m, n, lo, frac));
+    std::vector<float>& co = gco[gi];
+    co.assign((size_t)std::max(cfg->steps, 1) * 3, 0.0f);
+    if (cfg->coeffs)
+      std::memcpy(co.data(), cfg->coeffs, sizeof(float) * 3 * (size_t)cfg->steps);
+    else
+      default_coeffs_impl(m, n, cfg->steps, co.data());
+    return FP4ROOT_OK;
+  };
+  // clip, normalise, orient: with clipping, the passes also yield the norm of the clipped
+  // matrix; they collect elements in X, which the copy overwrites.  Small groups share launches.
+  ClipSets sets;
+  int64_t set_elems = 0;
+  const uint32_t mask0 = sign_mask(cfg->seed, 0);
+  const bool rot = cfg->flags & FP4ROOT_F_HADAMARD;
+  auto flush_sets = [&]() -> int {
+    const hipError_t e = sets.count ? launch_clip_prep(sets, status, cfg->eps, mask0, rot, kSlotXn, kSlotXm, st) : hipSuccess;
+    sets.count = 0;
+    sets.mats = 0;
+    set_elems = 0;
+    return e == hipSuccess ? FP4ROOT_OK : FP4ROOT_ERR_HIP;
+  };
+  auto copy_in = [&](size_t gi) -> int {
+    const int64_t m = groups[gi].m, n = groups[gi].n;
+    const GroupWs& w = gw[gi];
+    const std::vector<MatRef>& all = gall[gi];
+    int64_t lo = 0;
+    double frac = 0.0;
+    if (clip) quantile_index(m * n, cfg->clip_quantile, lo, frac);
     for (size_t c0 = 0; c0 < all.size(); c0 += kMaxChunk) {
       const size_t cnt = std::min(all.size() - c0, (size_t)kMaxChunk);
       const MatChunk ch = make_chunk(all, c0, cnt, m, n, lo, frac);
       float* const X = w.X + (int64_t)c0 * m * n;
-      // with clipping, the passes also yield the norm of the clipped matrix; they collect
-      // elements in X, which the copy overwrites
       if (clip) {
         ClipScratch cs;
         cs.hist = w.hist;
@@ -1224,21 +1253,21 @@ int orthogonalize_launch(const fp4root_matrix* mats, int64_t count, const fp4roo
         cs.cnt = w.cand_cnt;
         cs.psum = w.partial;
         cs.pcnt = w.partial_cnt;
+        const int64_t elems = (int64_t)all.size() * m * n;
+        if (!bf16 && ng > 1 && all.size() <= (size_t)kMaxClipSetMats && elems <= kClipSetElems) {
+          if (sets.count == kMaxClipSets || sets.mats + cnt > (size_t)kMaxClipSetMats ||
+              set_elems + elems > kClipSetElems)
+            FP4R_TRY_RC(flush_sets());
+          clip_set(sets, ch, w.step.sc, X, cs);
+          set_elems += elems;
+          continue;
+        }
         FP4R_TRY(launch_clip_threshold(ch, w.step.sc + c0, status, cs, cfg->eps, st));
       } else {
         FP4R_TRY(launch_inv_norm(ch, w.step.sc + c0, w.partial, cfg->eps, status, st));
       }
-      FP4R_TRY(launch_prep_copy(ch, w.step.sc + c0, X, m * n, sign_mask(cfg->seed, 0),
-                                cfg->flags & FP4ROOT_F_HADAMARD, kSlotXn, kSlotXm, st));
-      // the last update is written straight to the callers' matrices
-      if (!bf16 && cfg->steps > 0) gout[gi].push_back(ch);
+      FP4R_TRY(launch_prep_copy(ch, w.step.sc + c0, X, m * n, mask0, rot, kSlotXn, kSlotXm, st));
     }
-    std::vector<float>& co = gco[gi];
-    co.assign((size_t)std::max(cfg->steps, 1) * 3, 0.0f);
-    if (cfg->coeffs)
-      std::memcpy(co.data(), cfg->coeffs, sizeof(float) * 3 * (size_t)cfg->steps);
-    else
-      default_coeffs_impl(m, n, cfg->steps, co.data());
     return FP4ROOT_OK;
   };
   // without an update product that writes the outputs (no steps, or the BF16 path)
@@ -1262,6 +1291,7 @@ int orthogonalize_launch(const fp4root_matrix* mats, int64_t count, const fp4roo
       cv.off = kAlign;
       carve_group(cv, gr, bf16, gw[gi]);
       int rc = prepare(gi);
+      if (rc == FP4ROOT_OK) rc = copy_in(gi);
       if (rc != FP4ROOT_OK) return rc;
       if (cfg->steps > 0) FP4R_TRY(launch_cast_bf16(gw[gi].X, B, m, n, m * n, gw[gi].step.xb, st));
       for (int32_t k = 0; k < cfg->steps; ++k) {
@@ -1278,9 +1308,11 @@ int orthogonalize_launch(const fp4root_matrix* mats, int64_t count, const fp4roo
   // NVFP4: every group prepared, then each NS step over all groups at once
   for (size_t gi = 0; gi < ng; ++gi) {
     carve_group(shared, groups[gi], false, gw[gi]);
-    const int rc = prepare(gi);
+    int rc = prepare(gi);
+    if (rc == FP4ROOT_OK) rc = copy_in(gi);
     if (rc != FP4ROOT_OK) return rc;
   }
+  FP4R_TRY_RC(flush_sets());
   std::vector<StepGroup> sgs(ng);
   for (int32_t k = 0; k < cfg->steps; ++k) {
     for (size_t gi = 0; gi < ng; ++gi) {

@@ -116,6 +116,42 @@ struct ClipScratch {
   double* psum = nullptr;
   uint32_t* pcnt = nullptr;
 };
+struct ClipArgs {   // what the passes' kernels read of it
+  uint32_t* hist;
+  float* cand;
+  int64_t cand_stride;
+  uint32_t* cnt;
+  double* psum;
+  uint32_t* pcnt;
+  uint32_t tile_quads, tiles;
+  int32_t cand_shift;
+};
+// Chunks of several shape groups whose clip passes and copies share launches instead of
+// seven launches of 3 to 10 us per group (12 parameters of 256 x 256 and 256 x 1024: 416 ->
+// 387 us per optimizer step, three ragged groups of 6.6 M elements 839 -> 749 per call).
+// Only groups of together at most kClipSetElems elements (64 MB): a larger group finds its
+// matrices in the last-level cache again when its passes follow each other.
+constexpr int kMaxClipSets = 4, kMaxClipSetMats = 64;
+constexpr int64_t kClipSetElems = int64_t(1) << 24;
+struct ClipSet {
+  int64_t rows, cols, lo;
+  double frac;
+  MatScalars* sc;
+  float* X;
+  ClipArgs a;
+  uint32_t first, tile_end, prep_end;   // first matrix; workgroups up to and with this set
+};
+struct ClipSets {
+  MatRef m[kMaxClipSetMats];
+  ClipSet s[kMaxClipSets];
+  int count = 0;
+  uint32_t mats = 0;
+};
+// Append a chunk (its scratch as for launch_clip_threshold, with psum; X its canonical copy).
+void clip_set(ClipSets& cs, const MatChunk& ch, MatScalars* sc, float* X, const ClipScratch& w);
+// launch_clip_threshold and launch_prep_copy of every set.
+hipError_t launch_clip_prep(const ClipSets& cs, uint32_t* status, float eps, uint32_t mask, bool rotate, int slot_n,
+                            int slot_m, hipStream_t st);
 // Quantile of |x| per matrix in the chunk; writes sc[i].tau.  status: device word.
 hipError_t launch_clip_threshold(const MatChunk& ch, MatScalars* sc, uint32_t* status, const ClipScratch& w, float eps,
                                  hipStream_t st);

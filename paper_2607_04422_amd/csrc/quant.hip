@@ -78,9 +78,9 @@ struct QuadWalk {
   int64_t rr;
   bool flat;
 };
-FP4R_DEV QuadWalk quad_walk(const MatChunk& ch, const MatRef& r, int64_t q0) {
+FP4R_DEV QuadWalk quad_walk(int64_t rows, int64_t cols, const MatRef& r, int64_t q0) {
   QuadWalk w;
-  const int64_t c4 = (r.tall() ? ch.rows : ch.cols) / 4;
+  const int64_t c4 = (r.tall() ? rows : cols) / 4;
   w.ld = r.ld_in();
   w.c4 = (uint32_t)c4;
   w.flat = w.ld == 4 * c4;
@@ -141,17 +141,6 @@ FP4R_DEV double block_sum_256(double v, double* red) {
   return red[0];
 }
 
-struct ClipArgs {
-  uint32_t* hist;
-  float* cand;
-  int64_t cand_stride;
-  uint32_t* cnt;
-  double* psum;
-  uint32_t* pcnt;
-  uint32_t tile_quads, tiles;
-  int32_t cand_shift;
-};
-
 // Number of floats of a wave's segment in a tile of nq quads, and where it starts.
 FP4R_DEV uint32_t seg_cap(const ClipArgs& a, uint32_t nq) { return nq >> a.cand_shift; }
 FP4R_DEV float* seg_base(const ClipArgs& a, int mi, uint32_t tile, uint32_t nq, uint32_t wave) {
@@ -160,7 +149,8 @@ FP4R_DEV float* seg_base(const ClipArgs& a, int mi, uint32_t tile, uint32_t nq, 
 }
 
 template <int PASS>
-__global__ __launch_bounds__(256) void k_radix_hist(MatChunk ch, const MatScalars* sc, uint32_t* status, ClipArgs a) {
+FP4R_DEV void radix_hist_tile(const MatRef& r, int64_t rows, int64_t cols, const MatScalars& sm, uint32_t* status,
+                              const ClipArgs& a, int mi, uint32_t tile) {
   constexpr int kBins = PASS == 0 ? 2048 : 1024, kSets = PASS == 0 ? 1 : 2;
   __shared__ uint32_t h[kSets][kBins];
   __shared__ double red[256];
@@ -169,11 +159,8 @@ __global__ __launch_bounds__(256) void k_radix_hist(MatChunk ch, const MatScalar
   if (threadIdx.x == 0) above_all = 0;
   __syncthreads();
   const bool last = PASS == 2 && a.cand != nullptr;   // reads the segments
-  const int mi = (int)(blockIdx.x / a.tiles);
-  const uint32_t tile = blockIdx.x - (uint32_t)mi * a.tiles;
-  const MatRef& r = ch.m[mi];
-  const int64_t quads = ch.rows * ch.cols / 4;
-  const uint32_t p0 = PASS > 0 ? sc[mi].sel_prefix[0] : 0u, p1 = PASS > 0 ? sc[mi].sel_prefix[1] : 0u;
+  const int64_t quads = rows * cols / 4;
+  const uint32_t p0 = PASS > 0 ? sm.sel_prefix[0] : 0u, p1 = PASS > 0 ? sm.sel_prefix[1] : 0u;
   const bool two = PASS > 0 && p0 != p1;
   const uint32_t wave = threadIdx.x >> 6;
   double acc = 0.0;     // squares of the elements below prefix p0, in this thread's order
@@ -196,7 +183,7 @@ __global__ __launch_bounds__(256) void k_radix_hist(MatChunk ch, const MatScalar
     const int64_t q0 = (int64_t)tile * a.tile_quads;
     const uint32_t nq = (uint32_t)(quads - q0 < a.tile_quads ? quads - q0 : a.tile_quads);
     if constexpr (PASS == 0) {
-      walk_quads(quad_walk(ch, r, q0), nq, [&](float x, bool live) {
+      walk_quads(quad_walk(rows, cols, r, q0), nq, [&](float x, bool live) {
         const uint32_t key = __float_as_uint(x) & 0x7FFFFFFFu;
         if (!live) return;
         if (key >= 0x7F800000u) { bad = true; return; }
@@ -206,7 +193,7 @@ __global__ __launch_bounds__(256) void k_radix_hist(MatChunk ch, const MatScalar
       float* const seg = a.cand ? seg_base(a, mi, tile, nq, wave) : nullptr;
       const uint32_t cap = seg_cap(a, nq);
       uint32_t n = 0;   // elements collected by this wave (uniform)
-      walk_quads(quad_walk(ch, r, q0), nq, [&](float x, bool live) {
+      walk_quads(quad_walk(rows, cols, r, q0), nq, [&](float x, bool live) {
         const uint32_t key = __float_as_uint(x) & 0x7FFFFFFFu;
         live = live && key < 0x7F800000u;
         const uint32_t pre = key >> 20;
@@ -236,13 +223,13 @@ __global__ __launch_bounds__(256) void k_radix_hist(MatChunk ch, const MatScalar
           count_key(key, key >> 10, key & 1023u, true);
         }
       } else {
-        walk_quads(quad_walk(ch, r, q0), nq, [&](float x, bool live) {
+        walk_quads(quad_walk(rows, cols, r, q0), nq, [&](float x, bool live) {
           const uint32_t key = __float_as_uint(x) & 0x7FFFFFFFu, top = key >> 20;
           count_key(key, key >> 10, key & 1023u, live && (top == p0 >> 10 || top == p1 >> 10));
         });
       }
     } else {
-      walk_quads(quad_walk(ch, r, q0), nq, [&](float x, bool live) {
+      walk_quads(quad_walk(rows, cols, r, q0), nq, [&](float x, bool live) {
         const uint32_t key = __float_as_uint(x) & 0x7FFFFFFFu;
         count_key(key, key >> 10, key & 1023u, live && key < 0x7F800000u);
       });
@@ -266,20 +253,36 @@ __global__ __launch_bounds__(256) void k_radix_hist(MatChunk ch, const MatScalar
   }
 }
 
+template <int PASS>
+__global__ __launch_bounds__(256) void k_radix_hist(MatChunk ch, const MatScalars* sc, uint32_t* status, ClipArgs a) {
+  const int mi = (int)(blockIdx.x / a.tiles);
+  radix_hist_tile<PASS>(ch.m[mi], ch.rows, ch.cols, sc[mi], status, a, mi, blockIdx.x - (uint32_t)mi * a.tiles);
+}
+
+// The same passes over the matrices of several shape groups (see ClipSets).
+template <int PASS>
+__global__ __launch_bounds__(256) void k_radix_hist_sets(ClipSets cs, uint32_t* status) {
+  int i = 0;
+  while (i + 1 < cs.count && blockIdx.x >= cs.s[i].tile_end) ++i;
+  const ClipSet& g = cs.s[i];
+  const uint32_t wg = blockIdx.x - (i ? cs.s[i - 1].tile_end : 0u);
+  const int mi = (int)(wg / g.a.tiles);
+  radix_hist_tile<PASS>(cs.m[g.first + mi], g.rows, g.cols, g.sc[mi], status, g.a, mi, wg - (uint32_t)mi * g.a.tiles);
+}
+
 // Selects the digit of both ranks from the histograms (cleared for the next pass): one
 // workgroup per matrix, bins in thread order, a shuffle scan over each wave and the wave
 // totals through LDS (8.4 us as a 256-entry LDS scan per rank).
 template <int PASS>
-__global__ __launch_bounds__(256) void k_radix_select(MatChunk ch, MatScalars* sc, ClipArgs a, float eps) {
+FP4R_DEV void radix_select(int64_t rows, int64_t cols, int64_t lo, double frac, MatScalars& s, const ClipArgs& a, float eps,
+                           int mi) {
   constexpr int kPer = (PASS == 0 ? 2048 : 1024) / 256;   // bins per thread
   __shared__ uint32_t wsum[2][4];
   __shared__ uint32_t found_prefix[2], found_rank[2];
   __shared__ double red[256];
   __shared__ unsigned long long above_all;
-  const int mi = blockIdx.x;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  MatScalars& s = sc[mi];
-  const int64_t n = ch.rows * ch.cols;
+  const int64_t n = rows * cols;
   const uint32_t pre0 = PASS > 0 ? s.sel_prefix[0] : 0u, pre1 = PASS > 0 ? s.sel_prefix[1] : 0u;
   const bool two = pre0 != pre1;
   uint32_t* const hist = a.hist + (int64_t)mi * 2 * kHistBins;
@@ -312,7 +315,7 @@ __global__ __launch_bounds__(256) void k_radix_select(MatChunk ch, MatScalars* s
     for (int w = 0; w < 3; ++w)
       if (w < wave) before += wsum[rr][w];
     uint32_t cum = before + incl[rr] - local[rr];
-    const uint32_t target = PASS > 0 ? s.sel_rank[rr] : (uint32_t)(rr == 0 || ch.lo + 1 >= n ? ch.lo : ch.lo + 1);
+    const uint32_t target = PASS > 0 ? s.sel_rank[rr] : (uint32_t)(rr == 0 || lo + 1 >= n ? lo : lo + 1);
     if (target >= cum && target - cum < local[rr]) {   // exactly one thread owns the target rank
 #pragma unroll
       for (int j = 0; j < kPer; ++j) {
@@ -329,7 +332,7 @@ __global__ __launch_bounds__(256) void k_radix_select(MatChunk ch, MatScalars* s
   const uint32_t f0 = found_prefix[0], f1 = found_prefix[1];
   if (PASS == 2) {
     const double v0 = (double)__uint_as_float(f0), v1 = (double)__uint_as_float(f1);
-    const float tau = (float)__dadd_rn(v0, __dmul_rn(ch.frac, __dsub_rn(v1, v0)));
+    const float tau = (float)__dadd_rn(v0, __dmul_rn(frac, __dsub_rn(v1, v0)));
     if (t == 0) s.tau = tau;
     if (a.psum) {
       // ||clamp(M, tau)||^2 in a fixed order: the partials below v[lo]'s prefix, the
@@ -376,16 +379,34 @@ __global__ __launch_bounds__(256) void k_radix_select(MatChunk ch, MatScalars* s
   }
 }
 
+template <int PASS>
+__global__ __launch_bounds__(256) void k_radix_select(MatChunk ch, MatScalars* sc, ClipArgs a, float eps) {
+  radix_select<PASS>(ch.rows, ch.cols, ch.lo, ch.frac, sc[blockIdx.x], a, eps, (int)blockIdx.x);
+}
+template <int PASS>
+__global__ __launch_bounds__(256) void k_radix_select_sets(ClipSets cs, float eps) {
+  int i = 0;
+  while (i + 1 < cs.count && blockIdx.x >= cs.s[i + 1].first) ++i;
+  const ClipSet& g = cs.s[i];
+  const int mi = (int)(blockIdx.x - g.first);
+  radix_select<PASS>(g.rows, g.cols, g.lo, g.frac, g.sc[mi], g.a, eps, mi);
+}
+
+ClipArgs clip_args(const ClipScratch& w, int64_t quads, int64_t count) {
+  ClipArgs a;
+  a.hist = w.hist; a.cand = w.cand; a.cand_stride = w.cand_stride; a.cnt = w.cnt; a.psum = w.psum; a.pcnt = w.pcnt;
+  a.tile_quads = (uint32_t)hist_tile_quads(quads, count);
+  a.tiles = (uint32_t)hist_tiles(quads, count);
+  a.cand_shift = w.cand_shift;
+  return a;
+}
+
 hipError_t launch_clip_threshold(const MatChunk& ch, MatScalars* sc, uint32_t* status, const ClipScratch& w, float eps,
                                  hipStream_t st) {
   if (ch.count < 1) return hipSuccess;
   if (w.psum && !w.cand) return hipErrorInvalidValue;
   const int64_t quads = ch.rows * ch.cols / 4, tiles = hist_tiles(quads, ch.count);
-  ClipArgs a;
-  a.hist = w.hist; a.cand = w.cand; a.cand_stride = w.cand_stride; a.cnt = w.cnt; a.psum = w.psum; a.pcnt = w.pcnt;
-  a.tile_quads = (uint32_t)hist_tile_quads(quads, ch.count);
-  a.tiles = (uint32_t)tiles;
-  a.cand_shift = w.cand_shift;
+  const ClipArgs a = clip_args(w, quads, ch.count);
   const dim3 full((uint32_t)(tiles * ch.count)), sel((uint32_t)ch.count), wg(256);
   hipLaunchKernelGGL(k_radix_hist<0>, full, wg, 0, st, ch, sc, status, a);
   hipLaunchKernelGGL(k_radix_select<0>, sel, wg, 0, st, ch, sc, a, eps);
@@ -408,7 +429,7 @@ __global__ __launch_bounds__(256) void k_sumsq(MatChunk ch, double* partial, uin
   const uint32_t nq = (uint32_t)(quads - q0 < tile_quads ? quads - q0 : tile_quads);
   double acc = 0.0;
   bool bad = false;   // a NaN or infinite entry
-  walk_quads(quad_walk(ch, ch.m[mi], q0), nq, [&](float v, bool live) {   // quads past the end are zero
+  walk_quads(quad_walk(ch.rows, ch.cols, ch.m[mi], q0), nq, [&](float v, bool live) {   // quads past the end are zero
     bad |= live && !(fabsf(v) <= 3.40282347e38f);
     const double x = (double)fminf(fmaxf(v, -__builtin_inff()), __builtin_inff());
     acc = acc + x * x;
@@ -468,22 +489,16 @@ FP4R_DEV float block_max_256(float v, float* red) {
 // Prep: canonical X = fl32(clamp(M) * inv) (transposed when rows > cols), staged
 // through a 64 x 64 LDS tile that also yields the amaxes of X rotated along n
 // (16-column blocks) and along m (16-row blocks) for the first NS step.
-__global__ __launch_bounds__(256) void k_prep_copy(MatChunk ch, MatScalars* sc, float* xbase,
-                                                   int64_t x_bstride, uint32_t mask, int rotate,
-                                                   int slot_n, int slot_m) {
+FP4R_DEV void prep_tile(const MatRef& d, int64_t xm, int64_t xn, MatScalars& sm, float* X, uint32_t mask, int rotate,
+                        int slot_n, int slot_m, uint32_t tt) {   // canonical X: xm x xn
   __shared__ float tile[kT][kT + 1];
   __shared__ float red[4];
-  const int64_t xm = ch.rows, xn = ch.cols;   // canonical m x n
-  const uint32_t tcols = (uint32_t)cdiv(xn, kT), per = (uint32_t)cdiv(xm, kT) * tcols;
-  const int mi = (int)(blockIdx.x / per);
-  const uint32_t tt = blockIdx.x - (uint32_t)mi * per;
-  const MatRef& d = ch.m[mi];
+  const uint32_t tcols = (uint32_t)cdiv(xn, kT);
   const bool tall = d.tall();
   const int64_t ld_in = d.ld_in();
   const int64_t xr0 = (int64_t)(tt / tcols) * kT, xc0 = (int64_t)(tt % tcols) * kT;   // canonical tile origin
-  float* X = xbase + (int64_t)mi * x_bstride;
-  const float tau = sc[mi].tau;
-  const float inv = sc[mi].inv_norm;
+  const float tau = sm.tau;
+  const float inv = sm.inv_norm;
   // tile[i][j] = canonical X[xr0 + i][xc0 + j]; 16-byte accesses of M and X (rows of
   // both are 16-byte aligned and m, n are multiples of 16): thread -> four quads
   // v = threadIdx.x + 256 k, row v / 16 of the tile, columns 4 (v % 16) .. + 3
@@ -558,9 +573,58 @@ __global__ __launch_bounds__(256) void k_prep_copy(MatChunk ch, MatScalars* sc, 
   __syncthreads();
   const float bc = block_max_256(mc, red);
   if (threadIdx.x == 0) {
-    amax_record(&sc[mi], slot_n, blockIdx.x, br);
-    amax_record(&sc[mi], slot_m, blockIdx.x, bc);
+    amax_record(&sm, slot_n, tt, br);
+    amax_record(&sm, slot_m, tt, bc);
   }
+}
+
+__global__ __launch_bounds__(256) void k_prep_copy(MatChunk ch, MatScalars* sc, float* xbase,
+                                                   int64_t x_bstride, uint32_t mask, int rotate,
+                                                   int slot_n, int slot_m) {
+  const uint32_t per = (uint32_t)(cdiv(ch.rows, kT) * cdiv(ch.cols, kT));
+  const int mi = (int)(blockIdx.x / per);
+  prep_tile(ch.m[mi], ch.rows, ch.cols, sc[mi], xbase + (int64_t)mi * x_bstride, mask, rotate, slot_n, slot_m,
+            blockIdx.x - (uint32_t)mi * per);
+}
+__global__ __launch_bounds__(256) void k_prep_copy_sets(ClipSets cs, uint32_t mask, int rotate, int slot_n,
+                                                        int slot_m) {
+  int i = 0;
+  while (i + 1 < cs.count && blockIdx.x >= cs.s[i].prep_end) ++i;
+  const ClipSet& g = cs.s[i];
+  const uint32_t wg = blockIdx.x - (i ? cs.s[i - 1].prep_end : 0u);
+  const uint32_t per = (uint32_t)(cdiv(g.rows, kT) * cdiv(g.cols, kT));
+  const int mi = (int)(wg / per);
+  prep_tile(cs.m[g.first + mi], g.rows, g.cols, g.sc[mi], g.X + (int64_t)mi * g.rows * g.cols, mask, rotate, slot_n,
+            slot_m, wg - (uint32_t)mi * per);
+}
+
+void clip_set(ClipSets& cs, const MatChunk& ch, MatScalars* sc, float* X, const ClipScratch& w) {
+  ClipSet& g = cs.s[cs.count];
+  const uint32_t tiles = cs.count ? cs.s[cs.count - 1].tile_end : 0u, prep = cs.count ? cs.s[cs.count - 1].prep_end : 0u;
+  g.first = cs.mats;
+  for (int i = 0; i < ch.count; ++i) cs.m[cs.mats++] = ch.m[i];
+  g.rows = ch.rows; g.cols = ch.cols; g.lo = ch.lo; g.frac = ch.frac;
+  g.sc = sc;
+  g.X = X;
+  g.a = clip_args(w, ch.rows * ch.cols / 4, ch.count);
+  g.tile_end = tiles + g.a.tiles * (uint32_t)ch.count;
+  g.prep_end = prep + (uint32_t)(cdiv(ch.rows, kT) * cdiv(ch.cols, kT)) * (uint32_t)ch.count;
+  ++cs.count;
+}
+
+hipError_t launch_clip_prep(const ClipSets& cs, uint32_t* status, float eps, uint32_t mask, bool rotate, int slot_n,
+                            int slot_m, hipStream_t st) {
+  if (cs.count < 1) return hipSuccess;
+  const ClipSet& g = cs.s[cs.count - 1];
+  const dim3 full(g.tile_end), sel(cs.mats), wg(256);
+  hipLaunchKernelGGL(k_radix_hist_sets<0>, full, wg, 0, st, cs, status);
+  hipLaunchKernelGGL(k_radix_select_sets<0>, sel, wg, 0, st, cs, eps);
+  hipLaunchKernelGGL(k_radix_hist_sets<1>, full, wg, 0, st, cs, status);
+  hipLaunchKernelGGL(k_radix_select_sets<1>, sel, wg, 0, st, cs, eps);
+  hipLaunchKernelGGL(k_radix_hist_sets<2>, full, wg, 0, st, cs, status);
+  hipLaunchKernelGGL(k_radix_select_sets<2>, sel, wg, 0, st, cs, eps);
+  hipLaunchKernelGGL(k_prep_copy_sets, dim3(g.prep_end), wg, 0, st, cs, mask, (int)rotate, slot_n, slot_m);
+  return hipGetLastError();
 }
 
 // Rotated amaxes of X along n and along m from one read (X as given, no clipping): the
