@@ -137,7 +137,9 @@ double gemm_flop(int64_t batch, int64_t m, int64_t n, int64_t k) { return 2.0 * 
 
 // ---------------------------------------------------------------------------
 // Workspace of one batched NS step over `batch` m x n matrices.
-constexpr size_t kBlasltWsBytes = size_t(32) << 20;
+// Scratch of the library GEMM of the BF16 path: the needs it reports reach 72 MiB (1500 sizes
+// from 16 x 16 to 8192 x 32768 and batches up to 300).
+constexpr size_t kBlasltWsBytes = size_t(128) << 20;
 
 struct StepWs {
   MatScalars* sc = nullptr;

@@ -55,23 +55,33 @@ const Plan* plan_for(int64_t batch, int64_t m, int64_t n, int64_t x_bstride, siz
   Plan p;
   if (hipblasLtMatmulDescCreate(&p.desc, HIPBLAS_COMPUTE_32F, HIP_R_32F) != HIPBLAS_STATUS_SUCCESS) return nullptr;
   const hipblasOperation_t op = HIPBLAS_OP_N;
-  hipblasLtMatmulDescSetAttribute(p.desc, HIPBLASLT_MATMUL_DESC_TRANSA, &op, sizeof(op));
-  hipblasLtMatmulDescSetAttribute(p.desc, HIPBLASLT_MATMUL_DESC_TRANSB, &op, sizeof(op));
+  if (hipblasLtMatmulDescSetAttribute(p.desc, HIPBLASLT_MATMUL_DESC_TRANSA, &op, sizeof(op)) != HIPBLAS_STATUS_SUCCESS ||
+      hipblasLtMatmulDescSetAttribute(p.desc, HIPBLASLT_MATMUL_DESC_TRANSB, &op, sizeof(op)) != HIPBLAS_STATUS_SUCCESS)
+    return nullptr;
   const int32_t b32 = (int32_t)batch;
   if (!layout(&p.la, HIP_R_16BF, n, m, n, b32, m * n) || !layout(&p.lb, HIP_R_16BF, m, m, m, b32, m * m) ||
       !layout(&p.lc, HIP_R_32F, n, m, n, b32, x_bstride))
     return nullptr;
+  // Asked with a limit that no candidate reaches, the library reports what each one writes to
+  // its scratch.  With a limit below that it names the same algorithm and reports 0, but the
+  // algorithm (a split of the contraction with partial tiles in scratch) still writes them:
+  // 3 x 3072 x 8192 and 8 x 3072 x 3072 take 64 MiB.
   hipblasLtMatmulPreference_t pref = nullptr;
   if (hipblasLtMatmulPreferenceCreate(&pref) != HIPBLAS_STATUS_SUCCESS) return nullptr;
-  const uint64_t wsb = ws_bytes;
-  hipblasLtMatmulPreferenceSetAttribute(pref, HIPBLASLT_MATMUL_PREF_MAX_WORKSPACE_BYTES, &wsb, sizeof(wsb));
-  hipblasLtMatmulHeuristicResult_t res{};
+  const uint64_t limit = uint64_t(1) << 30;
+  constexpr int kCandidates = 8;
+  hipblasLtMatmulHeuristicResult_t res[kCandidates] = {};
   int found = 0;
-  const hipblasStatus_t hs =
-      hipblasLtMatmulAlgoGetHeuristic(h, p.desc, p.la, p.lb, p.lc, p.lc, pref, 1, &res, &found);
+  hipblasStatus_t hs =
+      hipblasLtMatmulPreferenceSetAttribute(pref, HIPBLASLT_MATMUL_PREF_MAX_WORKSPACE_BYTES, &limit, sizeof(limit));
+  if (hs == HIPBLAS_STATUS_SUCCESS)
+    hs = hipblasLtMatmulAlgoGetHeuristic(h, p.desc, p.la, p.lb, p.lc, p.lc, pref, kCandidates, res, &found);
   hipblasLtMatmulPreferenceDestroy(pref);
-  if (hs != HIPBLAS_STATUS_SUCCESS || found < 1) return nullptr;
-  p.algo = res.algo;
+  if (hs != HIPBLAS_STATUS_SUCCESS) return nullptr;
+  int pick = 0;
+  while (pick < found && res[pick].workspaceSize > ws_bytes) ++pick;
+  if (pick >= found) return nullptr;
+  p.algo = res[pick].algo;
   return &g_plans.emplace(key, p).first->second;
 }
 }  // namespace
@@ -80,16 +90,6 @@ hipError_t launch_bf16_update_blaslt(const uint16_t* b16, const uint16_t* xb, fl
                                      int64_t n, int64_t x_bstride, float a, void* ws, size_t ws_bytes,
                                      hipStream_t st) {
   if (batch == 0) return hipSuccess;
-  // No strided batch of odd length: one of 3 (3072 x 8192) gave a wrong first matrix and, in
-  // another call, a memory fault.  The cause is not known (its plan, layouts and buffers
-  // check out), so such a batch is not handed to the library: an even one, then a single.
-  if (batch > 1 && (batch & 1)) {
-    const int64_t k = batch - 1;
-    const hipError_t e = launch_bf16_update_blaslt(b16, xb, x, k, m, n, x_bstride, a, ws, ws_bytes, st);
-    if (e != hipSuccess) return e;
-    return launch_bf16_update_blaslt(b16 + k * m * m, xb + k * m * n, x + k * x_bstride, 1, m, n, x_bstride, a, ws,
-                                     ws_bytes, st);
-  }
   const Plan* p = plan_for(batch, m, n, x_bstride, ws_bytes);
   if (!p) return hipErrorNotSupported;
   hipblasLtHandle_t h;
