@@ -735,9 +735,10 @@ int fp4root_device_status(const void* ws, void* stream) {
 }
 
 namespace {
-// Count words of the clip passes' segments (4 per tile of the largest chunk).
+// Count words of the clip passes' segments (4 per tile of the largest chunk); none for a
+// shape that the call refuses.
 int64_t quantize_cand_counts(int64_t batch, int64_t rows, int64_t cols) {
-  if (batch <= 0 || rows <= 0 || cols <= 0) return 0;
+  if (batch <= 0 || !dims_ok(rows, cols)) return 0;
   const int64_t quads = rows * cols / 4, full = std::min<int64_t>(batch, kMaxChunk), last = batch % kMaxChunk;
   const int64_t t = hist_tiles(quads, full) * full;
   return 4 * (last ? std::max(t, hist_tiles(quads, last) * last) : t);

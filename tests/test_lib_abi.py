@@ -61,6 +61,17 @@ def test_workspace_queries():
     assert lib.fp4root_orthogonalize_workspace(mats, 2, ctypes.byref(both)) == 0
 
 
+@pytest.mark.timeout(20, method="thread")
+@pytest.mark.parametrize("rows,cols", [(1 << 31, 1 << 31), (1 << 31, 1 << 32), (1 << 40, 1 << 40), (17, 16), (-16, 16),
+                                       ((1 << 21) + 16, 16)])
+def test_workspace_query_of_a_refused_shape(rows, cols):
+    """Sides whose product leaves 64 bits, and others that the call refuses: the query
+    returns, and asks for no more than the scratch that does not depend on the shape."""
+    lib = _lib()
+    for batch in (1, 7, 300):
+        assert lib.fp4root_quantize_workspace(batch, rows, cols, 7) <= lib.fp4root_quantize_workspace(batch, 16, 16, 7)
+
+
 def test_product_tiling_switch():
     """Host-side setting: returns the previous mode, rejects modes outside 0..2."""
     lib = _lib()
