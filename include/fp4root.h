@@ -146,8 +146,8 @@ int fp4root_quantize(const float* x, int64_t batch, int64_t rows, int64_t cols, 
  * memory (code under HIP graph capture, tight serving loops, harnesses that forbid
  * allocation).  The same arguments and results as fp4root_quantize; its scratch is
  * a fixed array in the library (about 0.7 MB per GPU, kept until the process ends)
- * that covers up to 256 matrices per call.  A larger batch returns
- * FP4ROOT_ERR_WORKSPACE before any work.
+ * that covers up to 256 matrices per call with clipping and 1166 without.  A larger
+ * batch returns FP4ROOT_ERR_WORKSPACE before any work.
  *   status: optional device int32 that receives 0, or FP4ROOT_ERR_NONFINITE when a
  *           NaN or Inf was seen (the workspace query fp4root_device_status has no
  *           workspace to read here), or NULL.

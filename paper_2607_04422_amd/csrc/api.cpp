@@ -628,13 +628,16 @@ size_t orthogonalize_ws_size(const fp4root_matrix* mats, int64_t count, const fp
 // ---------------------------------------------------------------------------
 // Fixed scratch of fp4root_quantize_noalloc: a file-scope device array, one copy
 // per GPU, shared by every call on that GPU (overlapping calls on one GPU race).
-// Its largest use is kNoAllocMaxBatch matrices with clipping (the status word, the
-// per-matrix scalars and the radix histograms of one chunk of matrices).
+// It holds kNoAllocMaxBatch matrices with clipping (the status word, the per-matrix scalars
+// and the radix histograms of one chunk of matrices), and without clipping as many scalars as
+// fit in the same bytes.
 constexpr int64_t kNoAllocMaxBatch = 256;
 constexpr int kNoAllocChunk = 32;
 constexpr size_t kNoAllocScratchBytes =
     kAlign + (kNoAllocMaxBatch * sizeof(MatScalars) + kAlign - 1) / kAlign * kAlign +
     (size_t)kNoAllocChunk * 2 * kHistBins * sizeof(uint32_t);
+constexpr int64_t kNoAllocMaxPlain = (kNoAllocScratchBytes - kAlign) / sizeof(MatScalars);
+static_assert(kNoAllocMaxPlain == 1166, "stated in fp4root.h");
 static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes];
 
 namespace {
@@ -1154,7 +1157,7 @@ int fp4root_quantize_noalloc(const float* x, int64_t batch, int64_t rows, int64_
   const int rc = check_quantize(x, batch, rows, cols, ld, batch_stride, axis, flags, clip_quantile, codes, scales,
                                 tensor_scale);
   if (rc != FP4ROOT_OK) return rc;
-  if (batch > kNoAllocMaxBatch) return FP4ROOT_ERR_WORKSPACE;
+  if (batch > ((flags & FP4ROOT_F_CLIP) ? kNoAllocMaxBatch : kNoAllocMaxPlain)) return FP4ROOT_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)stream;
   void* ws = nullptr;
   const int rs = scratch_address(&ws);

@@ -245,7 +245,7 @@ def fp4root_quantize(x: torch.Tensor, axis: int = 1, flags: int = F_HADAMARD | F
 def fp4root_quantize_noalloc(x: torch.Tensor, out, axis: int = 1, flags: int = F_HADAMARD | F_ADAPTIVE46,
                              clip_quantile: float = 0.99, seed: int = 0, step: int = 0, stream=None):
     """fp4root_quantize into caller-owned outputs without a workspace (the library's
-    fixed scratch; at most 256 matrices).  out = (codes, scales, tensor_scale,
+    fixed scratch; at most 256 matrices with clipping, 1166 without).  out = (codes, scales, tensor_scale,
     clip_threshold or None, status or None), shaped as fp4root_quantize returns them
     (batch first); status is an int32 device tensor of one element."""
     _need_gpu_f32(x, "x")

@@ -102,3 +102,18 @@ def test_noalloc_status_and_limits():
     assert rc == 0
     torch.cuda.synchronize()
     assert int(status[0]) == 0 and float(sg.abs().max()) == 0.0
+
+
+@pytest.mark.parametrize("batch", [257, 1166])
+def test_more_matrices_without_clipping(batch):
+    """Without clipping the scratch holds scalars only: 1166 matrices, and one more is refused."""
+    lib = F.load()
+    x = torch.randn((batch, 16, 32), generator=torch.Generator(device="cuda").manual_seed(batch), device="cuda")
+    got, want = _noalloc(lib, x, 1, 6, 5, 2), _with_workspace(lib, x, 1, 6, 5, 2)
+    for g, w in zip(got[:3], want[:3]):
+        assert torch.equal(g, w)
+    assert got[4] == 0
+    big = torch.zeros((1167, 16, 16), device="cuda")
+    codes, scales, sg, tau, status = _outputs(1167, 16, 16, 1)
+    assert lib.fp4root_quantize_noalloc(_p(big), 1167, 16, 16, 16, 256, 1, 6, 0.99, 0, 0, _p(codes), _p(scales),
+                                        _p(sg), _p(tau), _p(status), None) == -3
