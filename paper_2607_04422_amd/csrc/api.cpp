@@ -559,17 +559,10 @@ void carve_group(Carver& cv, const Group& gr, bool bf16, GroupWs& w) {
   carve_step(cv, B, gr.m, gr.n, bf16, w.step);
   w.X = cv.take<float>((size_t)(B * gr.m * gr.n));
   w.hist = cv.take<uint32_t>(chunk_hist_words(B));
-  // tiles of the largest chunk (a smaller one may cut its matrices finer)
-  const int64_t quads = gr.m * gr.n / 4, last = B % kMaxChunk;
-  int64_t tiles = 0;
-  for (int64_t c : {std::min<int64_t>(B, kMaxChunk), last}) {
-    if (c == 0) continue;
-    const int64_t t = hist_tiles(quads, c);
-    tiles = std::max(tiles, t * c);
-  }
-  w.partial = cv.take<double>((size_t)tiles * 2);
-  w.partial_cnt = cv.take<uint32_t>((size_t)tiles * 2);
-  w.cand_cnt = cv.take<uint32_t>((size_t)tiles * 4);
+  const size_t parts = (size_t)(std::min<int64_t>(B, kMaxChunk) * hist_parts(gr.m * gr.n / 4));
+  w.partial = cv.take<double>(parts * 2);
+  w.partial_cnt = cv.take<uint32_t>(parts * 2);
+  w.cand_cnt = cv.take<uint32_t>(parts * 4);
 }
 
 int validate_matrices(const fp4root_matrix* mats, int64_t count) {
@@ -738,13 +731,11 @@ int fp4root_device_status(const void* ws, void* stream) {
 }
 
 namespace {
-// Count words of the clip passes' segments (4 per tile of the largest chunk); none for a
+// Count words of the clip passes' segments (4 per part of a chunk's matrices); none for a
 // shape that the call refuses.
 int64_t quantize_cand_counts(int64_t batch, int64_t rows, int64_t cols) {
   if (batch <= 0 || !dims_ok(rows, cols)) return 0;
-  const int64_t quads = rows * cols / 4, full = std::min<int64_t>(batch, kMaxChunk), last = batch % kMaxChunk;
-  const int64_t t = hist_tiles(quads, full) * full;
-  return 4 * (last ? std::max(t, hist_tiles(quads, last) * last) : t);
+  return 4 * std::min<int64_t>(batch, kMaxChunk) * hist_parts(rows * cols / 4);
 }
 }  // namespace
 

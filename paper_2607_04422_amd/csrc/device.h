@@ -507,6 +507,28 @@ FP4R_DEV uint32_t dpp_u(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xF, 0xF, true);
 }
 
+// The same move of a binary64 value.
+template <int CTRL>
+FP4R_DEV double dpp_d(double v) {
+  const uint64_t b = (uint64_t)__double_as_longlong(v);
+  const uint32_t lo = dpp_u<CTRL>((uint32_t)b), hi = dpp_u<CTRL>((uint32_t)(b >> 32));
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+FP4R_DEV double readlane_d(double v, int lane) {
+  const uint64_t b = (uint64_t)__double_as_longlong(v);
+  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)b, lane), hi = __builtin_amdgcn_readlane((uint32_t)(b >> 32), lane);
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+// Sum over the wave in a fixed order: pairs, quads, eights and sixteens of lanes, then the
+// four rows.  All lanes of the wave must be active, and every lane gets the result.
+FP4R_DEV double wave_sum_d(double v) {
+  v = v + dpp_d<0xB1>(v);
+  v = v + dpp_d<0x4E>(v);
+  v = v + dpp_d<0x141>(v);
+  v = v + dpp_d<0x140>(v);
+  return (readlane_d(v, 0) + readlane_d(v, 16)) + (readlane_d(v, 32) + readlane_d(v, 48));
+}
+
 // The stage word of the row whose four blocks sit in lanes 4i .. 4i + 3 (every lane of
 // the quad gets it).  All lanes of the wave must be active.
 FP4R_DEV uint32_t quad_row_word(uint32_t n2, uint32_t scale) {

@@ -33,19 +33,29 @@ struct MatChunk {
   int count;
 };
 
-// The clip passes cut a matrix into tiles of this many 16-byte quads (a power of two): at
-// most 1024 workgroups per matrix, since each ends with atomic adds to the same few
-// histogram bins (first pass on one 4096 x 4096: 28 us with 1024, 82 with 4096), and at
-// most 4096 in all (the second pass, which issues the most instructions per element, on 12
-// matrices of 25 M elements: 364, 212, 140 and 127 us per launch with 512 .. 4096).
-inline int64_t hist_tile_quads(int64_t quads, int64_t count) {
-  int64_t q = 512;
-  while (quads > q * 1024 || quads * count > q * 4096) q *= 2;
+// The clip passes and the norm cut a matrix into parts of this many 16-byte quads (a power
+// of two), at most 1024 of them.  Each part yields one partial sum of squares, and the parts
+// depend on the matrix alone, so the norm does not change with the matrices beside it.
+inline int64_t hist_part_quads(int64_t quads) {
+  int64_t q = 1024;
+  while (quads > q * 1024) q *= 2;
   return q;
 }
-inline int64_t hist_tiles(int64_t quads, int64_t count) {
-  const int64_t q = hist_tile_quads(quads, count);
+inline int64_t hist_parts(int64_t quads) {
+  const int64_t q = hist_part_quads(quads);
   return (quads + q - 1) / q;
+}
+// A workgroup takes a tile of one or more consecutive parts (a power of two): at most 1024
+// workgroups per matrix, since each ends with atomic adds to the same few histogram bins
+// (first pass on one 4096 x 4096: 28 us with 1024, 82 with 4096), and at most 4096 in all
+// (the second pass, which issues the most instructions per element, on 12 matrices of 25 M
+// elements: 364, 212, 140 and 127 us per launch with 512 .. 4096).
+constexpr int kMaxTileParts = kMaxChunk * 1024 / 4096;
+inline int64_t hist_tile_parts(int64_t quads, int64_t count) {
+  const int64_t q = hist_part_quads(quads);
+  int64_t p = 1;
+  while (quads * count > q * p * 4096) p *= 2;
+  return p;
 }
 
 // Per-matrix scalars kept in the workspace (one struct per matrix).
@@ -104,8 +114,8 @@ hipError_t launch_init(uint32_t* status, MatScalars* sc, int64_t n, uint32_t* hi
 // Scratch of the clip threshold beside the histograms (which must be zero on entry and
 // are zero again afterwards): with `cand` (per matrix cand_stride floats, 2^-cand_shift
 // of its elements at least) the second pass collects the elements that may still hold
-// the order statistics and the last pass reads only those; cnt: 4 words per tile.  With
-// psum / pcnt (2 tiles doubles / words per matrix; cand needed) it also
+// the order statistics and the last pass reads only those; cnt: 4 words per part.  With
+// psum / pcnt (2 doubles / words per part; cand needed) it also
 // writes inv_norm = fl32(1/(||clamp(M, tau)|| + eps)), as launch_inv_norm does.
 struct ClipScratch {
   uint32_t* hist = nullptr;   // count * 2 * kHistBins words
@@ -123,7 +133,8 @@ struct ClipArgs {   // what the passes' kernels read of it
   uint32_t* cnt;
   double* psum;
   uint32_t* pcnt;
-  uint32_t tile_quads, tiles;
+  uint32_t part_quads, parts;   // quads per part, parts per matrix
+  uint32_t tile_parts, tiles;   // parts per workgroup, workgroups per matrix
   int32_t cand_shift;
 };
 // Chunks of several shape groups whose clip passes and copies share launches instead of
@@ -160,7 +171,7 @@ hipError_t launch_clip_threshold(const MatChunk& ch, MatScalars* sc, uint32_t* s
 hipError_t launch_status_out(const uint32_t* status, int32_t* out, hipStream_t st);
 
 // Frobenius norm of the clipped matrices: sc[i].inv_norm = fl32(1/(||.|| + eps)).
-// partial: hist_tiles doubles per matrix of scratch.  A NaN or infinite entry sets
+// partial: hist_parts doubles per matrix of scratch.  A NaN or infinite entry sets
 // kStatusNonFinite in *status.
 hipError_t launch_inv_norm(const MatChunk& ch, MatScalars* sc, double* partial, float eps,
                            uint32_t* status, hipStream_t st);

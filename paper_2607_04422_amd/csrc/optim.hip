@@ -69,13 +69,6 @@ hipError_t launch_apply_update(uint16_t* w, const float* o, int64_t count, float
 // row, each partner sum formed identically in both lanes); the BF16 tile mean,
 // the residual, the rotation and the BF16-scale quantiser; then the AdamW update
 // of the BF16 weights from this step's binary32 m_t and v_t.
-template <int CTRL>
-FP4R_DEV double dpp_d(double v) {
-  const uint64_t b = (uint64_t)__double_as_longlong(v);
-  const uint32_t lo = dpp_u<CTRL>((uint32_t)b), hi = dpp_u<CTRL>((uint32_t)(b >> 32));
-  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
-}
-
 // The square roots and quotients of the AdamW step are the correctly rounded binary32 ones,
 // without the scaling and special cases of the general sequences; blocks with operands
 // outside the range use the general operations.  The pass over 25 M elements is bound by

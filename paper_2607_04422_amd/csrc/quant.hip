@@ -63,14 +63,15 @@ hipError_t launch_init(uint32_t* status, MatScalars* sc, int64_t n, uint32_t* hi
 //
 // The Frobenius norm of clamp(M, tau) comes out of the same passes: tau lies between
 // v[lo] and v[lo+1], and no element lies strictly between them, so an element whose
-// known prefix is below that of v[lo] is not clipped (its square goes into a binary64
-// partial of the block) and one above that of v[lo+1] is clipped to tau (it is only
+// known prefix is below that of v[lo] is not clipped (its square goes into the binary64
+// partial of its part of the matrix) and one above that of v[lo+1] is clipped to tau (it is only
 // counted); the elements of the two full prefixes are exactly the last histograms (a key
 // is the bit pattern of |x|), which the select step sums in bin order once tau is known.
 // Partials are formed and added in a fixed order.
 
-// A workgroup's part of a matrix: quads t, t + 256, ... of quads [q0, q0 + nq), four
-// loads issued before any is used; f(element value) in order.
+// Walks a range of a matrix's quads from q0 on: thread t takes quads t, t + 256, ..., four
+// loads issued before any is used; f(element value) in order.  A range whose length is a
+// multiple of 256 may be followed by the next one on the same walk.
 struct QuadWalk {
   const float* base;
   int64_t ld;
@@ -113,7 +114,7 @@ FP4R_DEV float4 walk_load(QuadWalk& w) {   // the next quad of this thread
   return v;
 }
 template <class F>
-FP4R_DEV void walk_quads(QuadWalk w, uint32_t nq, F f) {
+FP4R_DEV void walk_quads(QuadWalk& w, uint32_t nq, F f) {
   for (uint32_t q0 = threadIdx.x; q0 < nq; q0 += 1024u) {
     float4 v[4];
 #pragma unroll
@@ -141,10 +142,10 @@ FP4R_DEV double block_sum_256(double v, double* red) {
   return red[0];
 }
 
-// Number of floats of a wave's segment in a tile of nq quads, and where it starts.
+// Number of floats of a wave's segment in a part of nq quads, and where it starts.
 FP4R_DEV uint32_t seg_cap(const ClipArgs& a, uint32_t nq) { return nq >> a.cand_shift; }
-FP4R_DEV float* seg_base(const ClipArgs& a, int mi, uint32_t tile, uint32_t nq, uint32_t wave) {
-  return a.cand + (int64_t)mi * a.cand_stride + (((int64_t)tile * a.tile_quads * 4) >> a.cand_shift) +
+FP4R_DEV float* seg_base(const ClipArgs& a, int mi, uint32_t part, uint32_t nq, uint32_t wave) {
+  return a.cand + (int64_t)mi * a.cand_stride + (((int64_t)part * a.part_quads * 4) >> a.cand_shift) +
          (int64_t)wave * seg_cap(a, nq);
 }
 
@@ -153,7 +154,7 @@ FP4R_DEV void radix_hist_tile(const MatRef& r, int64_t rows, int64_t cols, const
                               const ClipArgs& a, int mi, uint32_t tile) {
   constexpr int kBins = PASS == 0 ? 2048 : 1024, kSets = PASS == 0 ? 1 : 2;
   __shared__ uint32_t h[kSets][kBins];
-  __shared__ double red[256];
+  __shared__ double part_sum[kMaxTileParts][4];   // per part and wave
   __shared__ uint32_t above_all;
   for (int i = threadIdx.x; i < kSets * kBins; i += 256) (&h[0][0])[i] = 0;
   if (threadIdx.x == 0) above_all = 0;
@@ -162,8 +163,8 @@ FP4R_DEV void radix_hist_tile(const MatRef& r, int64_t rows, int64_t cols, const
   const int64_t quads = rows * cols / 4;
   const uint32_t p0 = PASS > 0 ? sm.sel_prefix[0] : 0u, p1 = PASS > 0 ? sm.sel_prefix[1] : 0u;
   const bool two = PASS > 0 && p0 != p1;
-  const uint32_t wave = threadIdx.x >> 6;
-  double acc = 0.0;     // squares of the elements below prefix p0, in this thread's order
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  double acc = 0.0;     // squares of the part's elements below prefix p0, in this thread's order
   uint32_t above = 0;   // elements above prefix p1
   bool bad = false;
   // one element of the digit's candidates and the norm (pre: the prefix known so far)
@@ -179,21 +180,27 @@ FP4R_DEV void radix_hist_tile(const MatRef& r, int64_t rows, int64_t cols, const
       }
     }
   };
-  {
-    const int64_t q0 = (int64_t)tile * a.tile_quads;
-    const uint32_t nq = (uint32_t)(quads - q0 < a.tile_quads ? quads - q0 : a.tile_quads);
+  const uint32_t first = tile * a.tile_parts, end = min(first + a.tile_parts, a.parts);
+  QuadWalk walk = quad_walk(rows, cols, r, (int64_t)first * a.part_quads);
+  const uint32_t lane = threadIdx.x & 63;
+  uint32_t seg_n = 0;   // lane i: the elements in this wave's segment of part first + i
+  if (last && lane < end - first) seg_n = a.cnt[((int64_t)mi * a.parts + first + lane) * 4 + wave];
+  for (uint32_t part = first; part < end; ++part) {
+    const int64_t q0 = (int64_t)part * a.part_quads;
+    const uint32_t nq = (uint32_t)(quads - q0 < a.part_quads ? quads - q0 : a.part_quads);
+    acc = 0.0;
     if constexpr (PASS == 0) {
-      walk_quads(quad_walk(rows, cols, r, q0), nq, [&](float x, bool live) {
+      walk_quads(walk, nq, [&](float x, bool live) {
         const uint32_t key = __float_as_uint(x) & 0x7FFFFFFFu;
         if (!live) return;
         if (key >= 0x7F800000u) { bad = true; return; }
         atomicAdd(&h[0][key >> 20], 1u);
       });
     } else if constexpr (PASS == 1) {
-      float* const seg = a.cand ? seg_base(a, mi, tile, nq, wave) : nullptr;
+      float* const seg = a.cand ? seg_base(a, mi, part, nq, wave) : nullptr;
       const uint32_t cap = seg_cap(a, nq);
       uint32_t n = 0;   // elements collected by this wave (uniform)
-      walk_quads(quad_walk(rows, cols, r, q0), nq, [&](float x, bool live) {
+      walk_quads(walk, nq, [&](float x, bool live) {
         const uint32_t key = __float_as_uint(x) & 0x7FFFFFFFu;
         live = live && key < 0x7F800000u;
         const uint32_t pre = key >> 20;
@@ -209,44 +216,47 @@ FP4R_DEV void radix_hist_tile(const MatRef& r, int64_t rows, int64_t cols, const
           }
         }
       });
-      // lanes leave the walk together or not at all, except past the end of the tile: the
+      // lanes leave the walk together or not at all, except past the end of the part: the
       // count of the lane that stayed longest (lane 0) is the wave's
       n = __builtin_amdgcn_readfirstlane(n);
-      if (a.cand && (threadIdx.x & 63) == 0) a.cnt[((int64_t)mi * a.tiles + tile) * 4 + wave] = n;
+      if (a.cand && lane == 0) a.cnt[((int64_t)mi * a.parts + part) * 4 + wave] = n;
     } else if (last) {
       const uint32_t cap = seg_cap(a, nq);
-      const uint32_t n = a.cnt[((int64_t)mi * a.tiles + tile) * 4 + wave];
+      const uint32_t n = __builtin_amdgcn_readlane(seg_n, (int)(part - first));
       if (n <= cap) {
-        const float* const seg = seg_base(a, mi, tile, nq, wave);
-        for (uint32_t i = threadIdx.x & 63; i < n; i += 64) {
+        const float* const seg = seg_base(a, mi, part, nq, wave);
+        for (uint32_t i = lane; i < n; i += 64) {
           const uint32_t key = __float_as_uint(seg[i]) & 0x7FFFFFFFu;
           count_key(key, key >> 10, key & 1023u, true);
         }
       } else {
-        walk_quads(quad_walk(rows, cols, r, q0), nq, [&](float x, bool live) {
+        QuadWalk w = quad_walk(rows, cols, r, q0);
+        walk_quads(w, nq, [&](float x, bool live) {
           const uint32_t key = __float_as_uint(x) & 0x7FFFFFFFu, top = key >> 20;
           count_key(key, key >> 10, key & 1023u, live && (top == p0 >> 10 || top == p1 >> 10));
         });
       }
     } else {
-      walk_quads(quad_walk(rows, cols, r, q0), nq, [&](float x, bool live) {
+      walk_quads(walk, nq, [&](float x, bool live) {
         const uint32_t key = __float_as_uint(x) & 0x7FFFFFFFu;
         count_key(key, key >> 10, key & 1023u, live && key < 0x7F800000u);
       });
     }
-  }
-  if (PASS == 0 && bad) atomicOr(status, kStatusNonFinite);
-  if (PASS > 0 && a.psum) {
-    // partials: one per tile from the second pass, then one per tile from the last
-    if (above) atomicAdd(&above_all, above);
-    const double sum = block_sum_256(acc, red);
-    if (threadIdx.x == 0) {
-      const int64_t at = (int64_t)mi * 2 * a.tiles + (PASS == 2 ? a.tiles : 0u) + tile;
-      a.psum[at] = sum;
-      a.pcnt[at] = above_all;
+    if (PASS > 0 && a.psum) {
+      const double sum = wave_sum_d(acc);
+      if (lane == 0) part_sum[part - first][wave] = sum;
     }
   }
+  if (PASS == 0 && bad) atomicOr(status, kStatusNonFinite);
+  if (PASS > 0 && a.psum && above) atomicAdd(&above_all, above);
   __syncthreads();
+  if (PASS > 0 && a.psum && threadIdx.x < end - first) {
+    // partials: one per part from the second pass, then one per part from the last
+    const double* const w = part_sum[threadIdx.x];
+    const int64_t at = (int64_t)mi * 2 * a.parts + (PASS == 2 ? a.parts : 0u) + first + threadIdx.x;
+    a.psum[at] = (w[0] + w[1]) + (w[2] + w[3]);
+    a.pcnt[at] = threadIdx.x == 0 ? above_all : 0u;
+  }
   for (int b = threadIdx.x; b < kBins; b += 256) {
     if (h[0][b]) atomicAdd(&a.hist[(mi * 2 + 0) * kHistBins + b], h[0][b]);
     if (kSets > 1 && two && h[kSets - 1][b]) atomicAdd(&a.hist[(mi * 2 + 1) * kHistBins + b], h[kSets - 1][b]);
@@ -338,7 +348,7 @@ FP4R_DEV void radix_select(int64_t rows, int64_t cols, int64_t lo, double frac, 
       // ||clamp(M, tau)||^2 in a fixed order: the partials below v[lo]'s prefix, the
       // elements of the two prefixes from the histograms (bin order), the elements above
       // at tau^2 each
-      const int64_t np = (int64_t)2 * a.tiles;
+      const int64_t np = (int64_t)2 * a.parts;
       double below = 0.0;
       unsigned long long above = 0;
       for (int64_t i = t; i < np; i += 256) {
@@ -395,8 +405,10 @@ __global__ __launch_bounds__(256) void k_radix_select_sets(ClipSets cs, float ep
 ClipArgs clip_args(const ClipScratch& w, int64_t quads, int64_t count) {
   ClipArgs a;
   a.hist = w.hist; a.cand = w.cand; a.cand_stride = w.cand_stride; a.cnt = w.cnt; a.psum = w.psum; a.pcnt = w.pcnt;
-  a.tile_quads = (uint32_t)hist_tile_quads(quads, count);
-  a.tiles = (uint32_t)hist_tiles(quads, count);
+  a.part_quads = (uint32_t)hist_part_quads(quads);
+  a.parts = (uint32_t)hist_parts(quads);
+  a.tile_parts = (uint32_t)hist_tile_parts(quads, count);
+  a.tiles = (a.parts + a.tile_parts - 1) / a.tile_parts;
   a.cand_shift = w.cand_shift;
   return a;
 }
@@ -405,9 +417,8 @@ hipError_t launch_clip_threshold(const MatChunk& ch, MatScalars* sc, uint32_t* s
                                  hipStream_t st) {
   if (ch.count < 1) return hipSuccess;
   if (w.psum && !w.cand) return hipErrorInvalidValue;
-  const int64_t quads = ch.rows * ch.cols / 4, tiles = hist_tiles(quads, ch.count);
-  const ClipArgs a = clip_args(w, quads, ch.count);
-  const dim3 full((uint32_t)(tiles * ch.count)), sel((uint32_t)ch.count), wg(256);
+  const ClipArgs a = clip_args(w, ch.rows * ch.cols / 4, ch.count);
+  const dim3 full(a.tiles * (uint32_t)ch.count), sel((uint32_t)ch.count), wg(256);
   hipLaunchKernelGGL(k_radix_hist<0>, full, wg, 0, st, ch, sc, status, a);
   hipLaunchKernelGGL(k_radix_select<0>, sel, wg, 0, st, ch, sc, a, eps);
   hipLaunchKernelGGL(k_radix_hist<1>, full, wg, 0, st, ch, sc, status, a);
@@ -418,32 +429,41 @@ hipError_t launch_clip_threshold(const MatChunk& ch, MatScalars* sc, uint32_t* s
 }
 
 // ---------------------------------------------------------------------------
-// Frobenius norm of the matrices without clipping: per-tile binary64 partials in a
+// Frobenius norm of the matrices without clipping: per-part binary64 partials in a
 // fixed order, then one fixed-order sum per matrix (deterministic).
 
-__global__ __launch_bounds__(256) void k_sumsq(MatChunk ch, double* partial, uint32_t* status, uint32_t tile_quads,
-                                               uint32_t tiles) {
-  __shared__ double red[256];
+__global__ __launch_bounds__(256) void k_sumsq(MatChunk ch, double* partial, uint32_t* status, uint32_t part_quads,
+                                               uint32_t parts, uint32_t tile_parts, uint32_t tiles) {
+  __shared__ double part_sum[kMaxTileParts][4];
   const int mi = (int)(blockIdx.x / tiles);
-  const int64_t q0 = (int64_t)(blockIdx.x - (uint32_t)mi * tiles) * tile_quads, quads = ch.rows * ch.cols / 4;
-  const uint32_t nq = (uint32_t)(quads - q0 < tile_quads ? quads - q0 : tile_quads);
-  double acc = 0.0;
+  const uint32_t first = (blockIdx.x - (uint32_t)mi * tiles) * tile_parts, end = min(first + tile_parts, parts);
+  const int64_t quads = ch.rows * ch.cols / 4;
+  QuadWalk walk = quad_walk(ch.rows, ch.cols, ch.m[mi], (int64_t)first * part_quads);
   bool bad = false;   // a NaN or infinite entry
-  walk_quads(quad_walk(ch.rows, ch.cols, ch.m[mi], q0), nq, [&](float v, bool live) {   // quads past the end are zero
-    bad |= live && !(fabsf(v) <= 3.40282347e38f);
-    const double x = (double)fminf(fmaxf(v, -__builtin_inff()), __builtin_inff());
-    acc = acc + x * x;
-  });
+  for (uint32_t part = first; part < end; ++part) {
+    const int64_t left = quads - (int64_t)part * part_quads;
+    double acc = 0.0;
+    walk_quads(walk, (uint32_t)(left < part_quads ? left : part_quads), [&](float v, bool live) {   // quads past the end are zero
+      bad |= live && !(fabsf(v) <= 3.40282347e38f);
+      const double x = (double)fminf(fmaxf(v, -__builtin_inff()), __builtin_inff());
+      acc = acc + x * x;
+    });
+    const double sum = wave_sum_d(acc);
+    if ((threadIdx.x & 63) == 0) part_sum[part - first][threadIdx.x >> 6] = sum;
+  }
   if (__builtin_amdgcn_ballot_w64(bad) != 0 && (threadIdx.x & 63) == 0) atomicOr(status, kStatusNonFinite);
-  const double sum = block_sum_256(acc, red);
-  if (threadIdx.x == 0) partial[blockIdx.x] = sum;
+  __syncthreads();
+  if (threadIdx.x < end - first) {
+    const double* const w = part_sum[threadIdx.x];
+    partial[(int64_t)mi * parts + first + threadIdx.x] = (w[0] + w[1]) + (w[2] + w[3]);
+  }
 }
 
-__global__ __launch_bounds__(256) void k_norm_final(MatScalars* sc, const double* partial, float eps, uint32_t tiles) {
+__global__ __launch_bounds__(256) void k_norm_final(MatScalars* sc, const double* partial, float eps, uint32_t parts) {
   __shared__ double red[256];
   const int mi = blockIdx.x;
   double acc = 0.0;
-  for (uint32_t i = threadIdx.x; i < tiles; i += 256) acc = acc + partial[(int64_t)mi * tiles + i];
+  for (uint32_t i = threadIdx.x; i < parts; i += 256) acc = acc + partial[(int64_t)mi * parts + i];
   const double total = block_sum_256(acc, red);
   if (threadIdx.x == 0) {
     const double nu = __dsqrt_rn(total);
@@ -464,10 +484,10 @@ hipError_t launch_status_out(const uint32_t* status, int32_t* out, hipStream_t s
 
 hipError_t launch_inv_norm(const MatChunk& ch, MatScalars* sc, double* partial, float eps,
                            uint32_t* status, hipStream_t st) {
-  const int64_t quads = ch.rows * ch.cols / 4, tiles = hist_tiles(quads, ch.count);
-  hipLaunchKernelGGL(k_sumsq, dim3((uint32_t)(tiles * ch.count)), dim3(256), 0, st, ch, partial, status,
-                     (uint32_t)hist_tile_quads(quads, ch.count), (uint32_t)tiles);
-  hipLaunchKernelGGL(k_norm_final, dim3(ch.count), dim3(256), 0, st, sc, (const double*)partial, eps, (uint32_t)tiles);
+  const ClipArgs a = clip_args(ClipScratch{}, ch.rows * ch.cols / 4, ch.count);
+  hipLaunchKernelGGL(k_sumsq, dim3(a.tiles * (uint32_t)ch.count), dim3(256), 0, st, ch, partial, status, a.part_quads,
+                     a.parts, a.tile_parts, a.tiles);
+  hipLaunchKernelGGL(k_norm_final, dim3(ch.count), dim3(256), 0, st, sc, (const double*)partial, eps, a.parts);
   return hipGetLastError();
 }
 
