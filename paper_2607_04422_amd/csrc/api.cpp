@@ -536,7 +536,9 @@ MatChunk make_chunk(const std::vector<MatRef>& all, size_t first, size_t count, 
   for (size_t i = 0; i < count; ++i) ch.m[i] = all[first + i];
   return ch;
 }
-size_t chunk_hist_words(int64_t batch) { return (size_t)std::min<int64_t>(batch, kMaxChunk) * 2 * kHistBins; }
+size_t chunk_hist_words(int64_t batch, int64_t elems) {
+  return (size_t)(std::min<int64_t>(batch, kMaxChunk) * hist_words(elems));
+}
 
 void quantile_index(int64_t n, float q, int64_t& lo, double& frac) {
   const double h = (double)q * (double)(n - 1);
@@ -558,7 +560,7 @@ void carve_group(Carver& cv, const Group& gr, bool bf16, GroupWs& w) {
   const int64_t B = (int64_t)gr.members.size();
   carve_step(cv, B, gr.m, gr.n, bf16, w.step);
   w.X = cv.take<float>((size_t)(B * gr.m * gr.n));
-  w.hist = cv.take<uint32_t>(chunk_hist_words(B));
+  w.hist = cv.take<uint32_t>(chunk_hist_words(B, gr.m * gr.n));
   const size_t parts = (size_t)(std::min<int64_t>(B, kMaxChunk) * hist_parts(gr.m * gr.n / 4));
   w.partial = cv.take<double>(parts * 2);
   w.partial_cnt = cv.take<uint32_t>(parts * 2);
@@ -745,7 +747,7 @@ size_t fp4root_quantize_workspace(int64_t batch, int64_t rows, int64_t cols, uin
   cv.off = kAlign;
   cv.take<MatScalars>((size_t)batch);
   if (flags & FP4ROOT_F_CLIP) {
-    cv.take<uint32_t>(chunk_hist_words(batch));
+    cv.take<uint32_t>(chunk_hist_words(batch, dims_ok(rows, cols) ? rows * cols : 0));
     cv.take<uint32_t>((size_t)quantize_cand_counts(batch, rows, cols));
   }
   return cv.off;
@@ -777,14 +779,15 @@ int quantize_launch(const float* x, int64_t batch, int64_t rows, int64_t cols, i
                     uint8_t* scales, float* tensor_scale, float* clip_threshold, void* ws, bool collect,
                     hipStream_t st) {
   const bool clip = flags & FP4ROOT_F_CLIP;
-  const size_t chunk = collect ? kMaxChunk : kNoAllocChunk;
-  const size_t hist_words = std::min((size_t)batch, chunk) * 2 * kHistBins;
+  // half as many matrices of 64-bit counts fit in the fixed scratch
+  const size_t chunk = collect ? kMaxChunk : wide_counts(rows * cols) ? kNoAllocChunk / 2 : kNoAllocChunk;
+  const size_t hist_n = std::min((size_t)batch, chunk) * (size_t)hist_words(rows * cols);
   Carver cv(ws);
   uint32_t* status = cv.take<uint32_t>(1);
   MatScalars* sc = cv.take<MatScalars>((size_t)batch);
-  uint32_t* hist = clip ? cv.take<uint32_t>(hist_words) : nullptr;
+  uint32_t* hist = clip ? cv.take<uint32_t>(hist_n) : nullptr;
   uint32_t* cnt = clip && collect ? cv.take<uint32_t>((size_t)quantize_cand_counts(batch, rows, cols)) : nullptr;
-  FP4R_TRY(launch_init(status, sc, batch, hist, clip ? (int64_t)hist_words : 0, st));
+  FP4R_TRY(launch_init(status, sc, batch, hist, clip ? (int64_t)hist_n : 0, st));
   if (clip) {
     int64_t lo;
     double frac;
@@ -1205,7 +1208,7 @@ int orthogonalize_launch(const fp4root_matrix* mats, int64_t count, const fp4roo
     double frac = 0.0;
     if (clip) quantile_index(m * n, cfg->clip_quantile, lo, frac);
     FP4R_TRY(launch_init(reset_status && gi == 0 ? status : nullptr, w.step.sc, B, w.hist,
-                         clip ? (int64_t)chunk_hist_words(B) : 0, st));
+                         clip ? (int64_t)chunk_hist_words(B, m * n) : 0, st));
     // the last update is written straight to the callers' matrices
     if (!bf16 && cfg->steps > 0)
       for (size_t c0 = 0; c0 < all.size(); c0 += kMaxChunk)

@@ -74,7 +74,7 @@ struct MatScalars {
   float tau;             // clip threshold (+inf without clipping)
   float inv_norm;        // 1 / (||X'||_F + eps)
   uint32_t sel_prefix[2];  // radix select state for ranks lo and lo + 1
-  uint32_t sel_rank[2];
+  uint64_t sel_rank[2];
 };
 
 // Record a non-negative maximum in amax slot `slot` (line chosen by `spread`),
@@ -98,8 +98,11 @@ constexpr int kSlotXn = 0, kSlotXm = 1, kSlotA = 4, kSlotB = 5;
 constexpr int kSlotPrevState = 1;
 constexpr int kNumSlots = 6;
 
-// Radix select histogram: [2 ranks][2048 bins] per matrix.
+// Radix select histogram: [2 ranks][2048 bins] per matrix, of 64-bit counts for a matrix
+// whose ranks and counts may not fit in 32 bits.
 constexpr int kHistBins = 2048;
+inline bool wide_counts(int64_t elems) { return elems >> 32 != 0; }
+inline int64_t hist_words(int64_t elems) { return (int64_t)2 * kHistBins * (wide_counts(elems) ? 2 : 1); }
 
 // ---------------------------------------------------------------------------
 // Launchers (all asynchronous on `st`; return hipSuccess or the launch error).
@@ -118,7 +121,7 @@ hipError_t launch_init(uint32_t* status, MatScalars* sc, int64_t n, uint32_t* hi
 // psum / pcnt (2 doubles / words per part; cand needed) it also
 // writes inv_norm = fl32(1/(||clamp(M, tau)|| + eps)), as launch_inv_norm does.
 struct ClipScratch {
-  uint32_t* hist = nullptr;   // count * 2 * kHistBins words
+  uint32_t* hist = nullptr;   // count * hist_words
   float* cand = nullptr;
   int64_t cand_stride = 0;
   int cand_shift = 0;

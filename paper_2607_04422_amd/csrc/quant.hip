@@ -7,6 +7,8 @@
 #include "device.h"
 #include "internal.h"
 
+#include <type_traits>
+
 namespace fp4r {
 
 // ---------------------------------------------------------------------------
@@ -149,7 +151,8 @@ FP4R_DEV float* seg_base(const ClipArgs& a, int mi, uint32_t part, uint32_t nq, 
          (int64_t)wave * seg_cap(a, nq);
 }
 
-template <int PASS>
+// WIDE: the global counts have 64 bits (a tile's own, at most 2^31, always fit in 32).
+template <int PASS, bool WIDE>
 FP4R_DEV void radix_hist_tile(const MatRef& r, int64_t rows, int64_t cols, const MatScalars& sm, uint32_t* status,
                               const ClipArgs& a, int mi, uint32_t tile) {
   constexpr int kBins = PASS == 0 ? 2048 : 1024, kSets = PASS == 0 ? 1 : 2;
@@ -257,16 +260,18 @@ FP4R_DEV void radix_hist_tile(const MatRef& r, int64_t rows, int64_t cols, const
     a.psum[at] = (w[0] + w[1]) + (w[2] + w[3]);
     a.pcnt[at] = threadIdx.x == 0 ? above_all : 0u;
   }
+  using Count = std::conditional_t<WIDE, unsigned long long, uint32_t>;
+  Count* const hist = reinterpret_cast<Count*>(a.hist) + mi * 2 * kHistBins;
   for (int b = threadIdx.x; b < kBins; b += 256) {
-    if (h[0][b]) atomicAdd(&a.hist[(mi * 2 + 0) * kHistBins + b], h[0][b]);
-    if (kSets > 1 && two && h[kSets - 1][b]) atomicAdd(&a.hist[(mi * 2 + 1) * kHistBins + b], h[kSets - 1][b]);
+    if (h[0][b]) atomicAdd(&hist[b], (Count)h[0][b]);
+    if (kSets > 1 && two && h[kSets - 1][b]) atomicAdd(&hist[kHistBins + b], (Count)h[kSets - 1][b]);
   }
 }
 
-template <int PASS>
+template <int PASS, bool WIDE>
 __global__ __launch_bounds__(256) void k_radix_hist(MatChunk ch, const MatScalars* sc, uint32_t* status, ClipArgs a) {
   const int mi = (int)(blockIdx.x / a.tiles);
-  radix_hist_tile<PASS>(ch.m[mi], ch.rows, ch.cols, sc[mi], status, a, mi, blockIdx.x - (uint32_t)mi * a.tiles);
+  radix_hist_tile<PASS, WIDE>(ch.m[mi], ch.rows, ch.cols, sc[mi], status, a, mi, blockIdx.x - (uint32_t)mi * a.tiles);
 }
 
 // The same passes over the matrices of several shape groups (see ClipSets).
@@ -277,40 +282,44 @@ __global__ __launch_bounds__(256) void k_radix_hist_sets(ClipSets cs, uint32_t* 
   const ClipSet& g = cs.s[i];
   const uint32_t wg = blockIdx.x - (i ? cs.s[i - 1].tile_end : 0u);
   const int mi = (int)(wg / g.a.tiles);
-  radix_hist_tile<PASS>(cs.m[g.first + mi], g.rows, g.cols, g.sc[mi], status, g.a, mi, wg - (uint32_t)mi * g.a.tiles);
+  radix_hist_tile<PASS, false>(cs.m[g.first + mi], g.rows, g.cols, g.sc[mi], status, g.a, mi,
+                               wg - (uint32_t)mi * g.a.tiles);
 }
 
 // Selects the digit of both ranks from the histograms (cleared for the next pass): one
 // workgroup per matrix, bins in thread order, a shuffle scan over each wave and the wave
 // totals through LDS (8.4 us as a 256-entry LDS scan per rank).
-template <int PASS>
+template <int PASS, bool WIDE>
 FP4R_DEV void radix_select(int64_t rows, int64_t cols, int64_t lo, double frac, MatScalars& s, const ClipArgs& a, float eps,
                            int mi) {
   constexpr int kPer = (PASS == 0 ? 2048 : 1024) / 256;   // bins per thread
-  __shared__ uint32_t wsum[2][4];
-  __shared__ uint32_t found_prefix[2], found_rank[2];
+  using Count = std::conditional_t<WIDE, unsigned long long, uint32_t>;
+  typedef Count Count4 __attribute__((ext_vector_type(4)));
+  __shared__ Count wsum[2][4];
+  __shared__ uint32_t found_prefix[2];
+  __shared__ Count found_rank[2];
   __shared__ double red[256];
   __shared__ unsigned long long above_all;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int64_t n = rows * cols;
   const uint32_t pre0 = PASS > 0 ? s.sel_prefix[0] : 0u, pre1 = PASS > 0 ? s.sel_prefix[1] : 0u;
   const bool two = pre0 != pre1;
-  uint32_t* const hist = a.hist + (int64_t)mi * 2 * kHistBins;
-  uint32_t c[2][kPer], local[2], incl[2];
+  Count* const hist = reinterpret_cast<Count*>(a.hist) + (int64_t)mi * 2 * kHistBins;
+  Count c[2][kPer], local[2], incl[2];
 #pragma unroll
   for (int rr = 0; rr < 2; ++rr) {
-    const uint4* hh = reinterpret_cast<const uint4*>(hist + (two ? rr : 0) * kHistBins + t * kPer);
+    const Count4* hh = reinterpret_cast<const Count4*>(hist + (two ? rr : 0) * kHistBins + t * kPer);
     local[rr] = 0;
 #pragma unroll
     for (int j = 0; j < kPer / 4; ++j) {
-      const uint4 v = hh[j];
+      const Count4 v = hh[j];
       c[rr][4 * j] = v.x; c[rr][4 * j + 1] = v.y; c[rr][4 * j + 2] = v.z; c[rr][4 * j + 3] = v.w;
       local[rr] += v.x + v.y + v.z + v.w;
     }
     incl[rr] = local[rr];
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
-      const uint32_t up = (uint32_t)__shfl_up((int)incl[rr], off, 64);
+      const Count up = __shfl_up(incl[rr], off, 64);
       if (lane >= off) incl[rr] += up;
     }
     if (lane == 63) wsum[rr][wave] = incl[rr];
@@ -320,12 +329,12 @@ FP4R_DEV void radix_select(int64_t rows, int64_t cols, int64_t lo, double frac, 
   __syncthreads();
 #pragma unroll
   for (int rr = 0; rr < 2; ++rr) {
-    uint32_t before = 0;
+    Count before = 0;
 #pragma unroll
     for (int w = 0; w < 3; ++w)
       if (w < wave) before += wsum[rr][w];
-    uint32_t cum = before + incl[rr] - local[rr];
-    const uint32_t target = PASS > 0 ? s.sel_rank[rr] : (uint32_t)(rr == 0 || lo + 1 >= n ? lo : lo + 1);
+    Count cum = before + incl[rr] - local[rr];
+    const Count target = PASS > 0 ? (Count)s.sel_rank[rr] : (Count)(rr == 0 || lo + 1 >= n ? lo : lo + 1);
     if (target >= cum && target - cum < local[rr]) {   // exactly one thread owns the target rank
 #pragma unroll
       for (int j = 0; j < kPer; ++j) {
@@ -380,7 +389,8 @@ FP4R_DEV void radix_select(int64_t rows, int64_t cols, int64_t lo, double frac, 
       }
     }
   }
-  for (int b = t; b < 2 * kHistBins / 4; b += 256) reinterpret_cast<uint4*>(hist)[b] = make_uint4(0u, 0u, 0u, 0u);
+  for (int b = t; b < 2 * kHistBins * (int)sizeof(Count) / 16; b += 256)
+    reinterpret_cast<uint4*>(hist)[b] = make_uint4(0u, 0u, 0u, 0u);
   if (t == 0) {
     s.sel_prefix[0] = f0;
     s.sel_prefix[1] = f1;
@@ -389,9 +399,9 @@ FP4R_DEV void radix_select(int64_t rows, int64_t cols, int64_t lo, double frac, 
   }
 }
 
-template <int PASS>
+template <int PASS, bool WIDE>
 __global__ __launch_bounds__(256) void k_radix_select(MatChunk ch, MatScalars* sc, ClipArgs a, float eps) {
-  radix_select<PASS>(ch.rows, ch.cols, ch.lo, ch.frac, sc[blockIdx.x], a, eps, (int)blockIdx.x);
+  radix_select<PASS, WIDE>(ch.rows, ch.cols, ch.lo, ch.frac, sc[blockIdx.x], a, eps, (int)blockIdx.x);
 }
 template <int PASS>
 __global__ __launch_bounds__(256) void k_radix_select_sets(ClipSets cs, float eps) {
@@ -399,7 +409,7 @@ __global__ __launch_bounds__(256) void k_radix_select_sets(ClipSets cs, float ep
   while (i + 1 < cs.count && blockIdx.x >= cs.s[i + 1].first) ++i;
   const ClipSet& g = cs.s[i];
   const int mi = (int)(blockIdx.x - g.first);
-  radix_select<PASS>(g.rows, g.cols, g.lo, g.frac, g.sc[mi], g.a, eps, mi);
+  radix_select<PASS, false>(g.rows, g.cols, g.lo, g.frac, g.sc[mi], g.a, eps, mi);
 }
 
 ClipArgs clip_args(const ClipScratch& w, int64_t quads, int64_t count) {
@@ -413,18 +423,25 @@ ClipArgs clip_args(const ClipScratch& w, int64_t quads, int64_t count) {
   return a;
 }
 
+template <bool WIDE>
+void launch_radix(const MatChunk& ch, MatScalars* sc, uint32_t* status, const ClipArgs& a, float eps, hipStream_t st) {
+  const dim3 full(a.tiles * (uint32_t)ch.count), sel((uint32_t)ch.count), wg(256);
+  hipLaunchKernelGGL((k_radix_hist<0, WIDE>), full, wg, 0, st, ch, sc, status, a);
+  hipLaunchKernelGGL((k_radix_select<0, WIDE>), sel, wg, 0, st, ch, sc, a, eps);
+  hipLaunchKernelGGL((k_radix_hist<1, WIDE>), full, wg, 0, st, ch, sc, status, a);
+  hipLaunchKernelGGL((k_radix_select<1, WIDE>), sel, wg, 0, st, ch, sc, a, eps);
+  hipLaunchKernelGGL((k_radix_hist<2, WIDE>), full, wg, 0, st, ch, sc, status, a);
+  hipLaunchKernelGGL((k_radix_select<2, WIDE>), sel, wg, 0, st, ch, sc, a, eps);
+}
+
 hipError_t launch_clip_threshold(const MatChunk& ch, MatScalars* sc, uint32_t* status, const ClipScratch& w, float eps,
                                  hipStream_t st) {
   if (ch.count < 1) return hipSuccess;
   if (w.psum && !w.cand) return hipErrorInvalidValue;
   const ClipArgs a = clip_args(w, ch.rows * ch.cols / 4, ch.count);
-  const dim3 full(a.tiles * (uint32_t)ch.count), sel((uint32_t)ch.count), wg(256);
-  hipLaunchKernelGGL(k_radix_hist<0>, full, wg, 0, st, ch, sc, status, a);
-  hipLaunchKernelGGL(k_radix_select<0>, sel, wg, 0, st, ch, sc, a, eps);
-  hipLaunchKernelGGL(k_radix_hist<1>, full, wg, 0, st, ch, sc, status, a);
-  hipLaunchKernelGGL(k_radix_select<1>, sel, wg, 0, st, ch, sc, a, eps);
-  hipLaunchKernelGGL(k_radix_hist<2>, full, wg, 0, st, ch, sc, status, a);
-  hipLaunchKernelGGL(k_radix_select<2>, sel, wg, 0, st, ch, sc, a, eps);
+  // 64-bit counts from 2^32 elements on, where a rank or a bin may need them
+  if (wide_counts(ch.rows * ch.cols)) launch_radix<true>(ch, sc, status, a, eps, st);
+  else launch_radix<false>(ch, sc, status, a, eps, st);
   return hipGetLastError();
 }
 
