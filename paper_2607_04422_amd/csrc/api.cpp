@@ -68,7 +68,8 @@ bool aligned(const void* p, size_t a) { return ((uintptr_t)p % a) == 0; }
 // bytes, are then addressed with 32-bit offsets too.
 constexpr int64_t kMaxDim = int64_t(1) << 21;
 constexpr int64_t kMaxElems = int64_t(1) << 36;
-// Row strides: 16 rows of 2^33 - 4 floats are 512 GiB, more than the device holds.
+// Row strides of the matrix lists (MatRef keeps them in 31 bits of 16-byte units): 16 rows of
+// 2^33 - 4 floats are 512 GiB, more than the device holds.
 constexpr int64_t kMaxLd = (int64_t(1) << 33) - 4;
 bool dims_ok(int64_t r, int64_t c) {
   return r > 0 && c > 0 && r % 16 == 0 && c % 16 == 0 && r <= kMaxDim && c <= kMaxDim && r * c <= kMaxElems;
@@ -765,6 +766,7 @@ int check_quantize(const float* x, int64_t batch, int64_t rows, int64_t cols, in
   if (!dims_ok(rows, cols)) return FP4ROOT_ERR_SHAPE;
   if (ld < cols || ld % 4 || (batch > 1 && batch_stride < rows * ld) || batch_stride % 4)
     return FP4ROOT_ERR_SHAPE;
+  if ((flags & FP4ROOT_F_CLIP) && ld > kMaxLd) return FP4ROOT_ERR_SHAPE;
   if (!aligned(x, 16) || !aligned(codes, 8)) return FP4ROOT_ERR_INVALID_ARG;
   if ((flags & FP4ROOT_F_CLIP) && !(clip_quantile >= 0.0f && clip_quantile <= 1.0f)) return FP4ROOT_ERR_INVALID_ARG;
   return FP4ROOT_OK;

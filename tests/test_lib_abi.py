@@ -126,6 +126,19 @@ def test_argument_errors_are_synchronous():
     assert lib.fp4root_orthogonalize(m1, 1, None, ws, 1 << 30, None) == -1
 
 
+def test_row_strides_beyond_the_matrix_lists():
+    """Strides that the clip passes and the orthogonalisation do not hold are refused, not cut."""
+    lib = _lib()
+    fake, ws = ctypes.c_void_p(0x100000), ctypes.c_void_p(0x200000)
+    for ld in ((1 << 33), (1 << 34) + 16, (1 << 40)):
+        args = (1, 16, 16, ld, 16 * ld, 1, 1, 0.99, 0, 0, fake, fake, fake, None)
+        assert lib.fp4root_quantize(fake, *args, ws, 1 << 30, None) == -2
+        assert lib.fp4root_quantize_noalloc(fake, *args, None, None) == -2
+        cfg = F.NsConfig(5, None, 7, 0.99, 1e-7, 0)
+        mats = (F.Matrix * 1)(F.Matrix(0x100000, 0x300000, 16, 16, ld, 16))
+        assert lib.fp4root_orthogonalize(mats, 1, ctypes.byref(cfg), ws, 1 << 30, None) == -2
+
+
 def test_binding_refuses_cpu_tensors():
     import torch
     _lib()
