@@ -1042,7 +1042,7 @@ void root_chunk(const fp4root_param* params, int64_t count, int64_t first, const
   for (int64_t i = first; i < count && ch.count < kMaxRootChunk; ++i) {
     const fp4root_param& p = params[i];
     const int64_t nblk = p.rows * p.cols / 16, wgs = (nblk + 255) / 256;
-    bool fits = end + wgs <= kMaxRootBlocks;
+    bool fits = end + wgs <= kMaxSharedBlocks;
     for (int64_t k = first; k < i && fits; ++k) fits = !depend(params[k], p);
     if (ch.count > 0 && !fits) break;
     const uint64_t seed = rc.momentum_seed + (uint64_t)i;

@@ -107,6 +107,11 @@ inline int64_t hist_words(int64_t elems) { return (int64_t)2 * kHistBins * (wide
 // ---------------------------------------------------------------------------
 // Launchers (all asynchronous on `st`; return hipSuccess or the launch error).
 
+// Workgroups (of 256 threads) of a launch that takes several problems: a grid's threads have to
+// stay below 2^32.  What does not fit runs in launches of its own.
+constexpr int64_t kMaxSharedBlocks = int64_t(1) << 23;
+static_assert(kMaxSharedBlocks * 256 < int64_t(1) << 32, "threads of a grid");
+
 hipError_t launch_fill_u32(uint32_t* p, uint32_t value, int64_t n, hipStream_t st);
 
 // Start of a call: zero the status word (may be null), reset n scalar records (amaxes and
@@ -312,7 +317,6 @@ hipError_t launch_apply_update(uint16_t* w, const float* o, int64_t count, float
 // Parameters of an optimizer step, for the launches that take several at a time (the
 // workgroups of parameter i are [end[i - 1], end[i]) of the grid).
 constexpr int kMaxRootChunk = 32;
-constexpr int64_t kMaxRootBlocks = int64_t(1) << 28;   // per launch, when it takes more than one parameter
 struct RootRef {
   const float* g;
   float* m;

@@ -1029,7 +1029,7 @@ FP4R_DEV EncodeSlot encode_slot(const EncodeBatch& eb) {
 }
 
 // The table of a launch over list[0 .. count) with per(i) workgroups per matrix; false when
-// the problems must go one by one (a grid too long for 32 bits).
+// the problems must go one by one.
 template <class F>
 bool encode_table(const EncodeArgs* list, int count, F per, EncodeBatch& eb) {
   eb.count = count;
@@ -1038,7 +1038,7 @@ bool encode_table(const EncodeArgs* list, int count, F per, EncodeBatch& eb) {
     eb.p[i] = list[i];
     const int64_t n = per(list[i]);
     end += n * list[i].batch;
-    if (count > 1 && end > int64_t(1) << 30) return false;
+    if (count > 1 && end > kMaxSharedBlocks) return false;
     eb.per[i] = (uint32_t)n;
     eb.end[i] = (uint32_t)end;
   }
