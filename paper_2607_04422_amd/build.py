@@ -9,6 +9,8 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfp4root.so")
+# sweeps of the device helpers over their ranges, loaded by tests only
+SWEEPS = os.path.join(HERE, "libfp4root_sweeps.so")
 SOURCES = ["quant.hip", "gemm_fp4.hip", "gemm_bf16.hip", "gemm_blaslt.cpp", "optim.hip", "api.cpp"]
 # the update product of the BF16 comparison path is a hipBLASLt GEMM
 LINK_LIBS = ["-L/opt/rocm/lib", "-lhipblaslt", "-Wl,-rpath,/opt/rocm/lib"]
@@ -62,6 +64,17 @@ def build(verbose: bool = False, jobs: int = 3, extra_flags=(), out: str = LIB) 
     return out
 
 
+def build_sweeps() -> str:
+    """Compile probes/exact_math.hip (device helpers against the general operations)."""
+    cmd = [hipcc(), *HIPCC_FLAGS, "-shared", "-x", "hip", os.path.join(HERE, "probes", "exact_math.hip"),
+           "-o", SWEEPS + ".tmp"]
+    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("hipcc failed on probes/exact_math.hip:\n" + res.stdout)
+    os.replace(SWEEPS + ".tmp", SWEEPS)
+    return SWEEPS
+
+
 def _wait(item):
     src, p = item
     out, _ = p.communicate()
@@ -75,3 +88,4 @@ def _wait(item):
 
 if __name__ == "__main__":
     print(build(verbose="-v" in sys.argv))
+    print(build_sweeps())

@@ -110,6 +110,15 @@ FP4R_DEV uint16_t bf16_rne(float f) {
   return (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
 }
 
+// The BF16 bit patterns of two values in one instruction (v_cvt_pk_bf16_f32): those of
+// bf16_rne for every value but NaN (tests/test_gpu_exact_math.py).
+FP4R_DEV uint32_t bf16_pair(float lo, float hi) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  const f32x2 t = {lo, hi};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(t, bf16x2));
+}
+
 // Binary32 value of an E4M3FN code (bit 7 ignored): (8 + m) 2^(e - 10), or m 2^-9
 // for the subnormal codes.
 FP4R_DEV float e4m3_value(uint32_t code) {
@@ -442,6 +451,35 @@ FP4R_DEV void quant_block_bf16(const float (&u)[16], bool adaptive, uint32_t& sc
   }
   scale = bf16_rne(c6.s);
   codes = c6.codes;
+}
+
+// The square roots and quotients of the AdamW step are the correctly rounded binary32 ones,
+// without the scaling and special cases of the general sequences; blocks with operands
+// outside the range use the general operations.  The pass over 25 M elements is bound by
+// issue: 77 us with these, 92 without (75 with the weights' pairwise BF16 conversion).
+constexpr float kFastLo = 0x1p-100f, kFastHi = 0x1p+40f;
+
+// sqrt(v): g = v rsq(v) within a few ulp, corrected by its residual (exact in one fma).
+// Whether the last rounding is right for every significand depends on the rsq table, so
+// it is compared with the general square root over every binary32 value of [2^-100, 2^100] on
+// gfx950 (tests/test_gpu_exact_math.py, which also samples the quotients): none differs.
+FP4R_DEV float fast_sqrt(float v) {
+  const float r = __builtin_amdgcn_rsqf(fmaxf(v, kFastLo));
+  const float g = v * r, d = fmaf(-g, g, v);
+  return fmaf(d, 0.5f * r, g);
+}
+
+// fl32(a / b) with rb = fl64(1 / b), for a quotient in the normal range (or a = 0): a / b
+// lies at least 2^-49 (relative) from every binary32 midpoint m, since a - m b is a
+// multiple of the last place of the 49-bit product and not 0 (m is odd with 25 bits, a has
+// 24), and a rb in binary64 is within 2^-52 of it.
+FP4R_DEV float fast_div(float a, double rb) { return (float)((double)a * rb); }
+
+// 1 / b in binary64, within 2^-52: the residual e of rcp(b) is below 2^-22, so
+// x (1 + e + e^2) leaves 2^-66 and two roundings.
+FP4R_DEV double recip64(float b) {
+  const double x = (double)__builtin_amdgcn_rcpf(b), e = __builtin_fma(-(double)b, x, 1.0);
+  return __builtin_fma(x, __builtin_fma(e, e, e), x);
 }
 
 // The first-moment update of one 16-element block at flat offset e0: decode of the

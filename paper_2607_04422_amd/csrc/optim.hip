@@ -69,35 +69,6 @@ hipError_t launch_apply_update(uint16_t* w, const float* o, int64_t count, float
 // row, each partner sum formed identically in both lanes); the BF16 tile mean,
 // the residual, the rotation and the BF16-scale quantiser; then the AdamW update
 // of the BF16 weights from this step's binary32 m_t and v_t.
-// The square roots and quotients of the AdamW step are the correctly rounded binary32 ones,
-// without the scaling and special cases of the general sequences; blocks with operands
-// outside the range use the general operations.  The pass over 25 M elements is bound by
-// issue: 77 us with these, 92 without (75 with the weights' pairwise BF16 conversion).
-constexpr float kFastLo = 0x1p-100f, kFastHi = 0x1p+40f;
-
-// sqrt(v): g = v rsq(v) within a few ulp, corrected by its residual (exact in one fma).
-// Whether the last rounding is right for every significand depends on the rsq table, so
-// it was compared with the general square root over every binary32 value of
-// [2^-100, 2^100] on gfx950: none differs.
-FP4R_DEV float fast_sqrt(float v) {
-  const float r = __builtin_amdgcn_rsqf(fmaxf(v, kFastLo));
-  const float g = v * r, d = fmaf(-g, g, v);
-  return fmaf(d, 0.5f * r, g);
-}
-
-// fl32(a / b) with rb = fl64(1 / b), for a quotient in the normal range (or a = 0): a / b
-// lies at least 2^-49 (relative) from every binary32 midpoint m, since a - m b is a
-// multiple of the last place of the 49-bit product and not 0 (m is odd with 25 bits, a has
-// 24), and a rb in binary64 is within 2^-52 of it.
-FP4R_DEV float fast_div(float a, double rb) { return (float)((double)a * rb); }
-
-// 1 / b in binary64, within 2^-52: the residual e of rcp(b) is below 2^-22, so
-// x (1 + e + e^2) leaves 2^-66 and two roundings.
-FP4R_DEV double recip64(float b) {
-  const double x = (double)__builtin_amdgcn_rcpf(b), e = __builtin_fma(-(double)b, x, 1.0);
-  return __builtin_fma(x, __builtin_fma(e, e, e), x);
-}
-
 struct QAdamWArgs {
   uint16_t* w;
   const float* g;
@@ -249,11 +220,8 @@ __global__ __launch_bounds__(256) void k_qadamw(QAdamWArgs a) {
   }
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
-    typedef float f32x2 __attribute__((ext_vector_type(2)));
-    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
     const float w0 = __uint_as_float(ww[k] << 16) * a.c1w, w1 = __uint_as_float(ww[k] & 0xFFFF0000u) * a.c1w;
-    const f32x2 t = {w0 - a.lr * upd16[2 * k], w1 - a.lr * upd16[2 * k + 1]};
-    out[k] = __builtin_bit_cast(uint32_t, __builtin_convertvector(t, bf16x2));   // v_cvt_pk_bf16_f32: bf16_rne
+    out[k] = bf16_pair(w0 - a.lr * upd16[2 * k], w1 - a.lr * upd16[2 * k + 1]);
   }
   if (live) {
     uint4* wo = reinterpret_cast<uint4*>(a.w + e0);
