@@ -14,6 +14,9 @@ import math
 import numpy as np
 import pytest
 
+from oracle import rht
+from oracle.quantize import quantize
+
 K2 = np.array([0, 1, 2, 3, 4, 6, 8, 12])
 LIM = 2.0 ** 48 * (1 - 2.0 ** -16)
 
@@ -40,6 +43,44 @@ def run_bound(words):
         t = [np.float32(t[i] + t[i + 1]) for i in range(0, len(t), 2)]
     rho = float(t[0]) * 4.0 ** -min(w & 15 for w in words)
     return float(np.float32(np.float32(rho) * np.float32(1 + 2.0 ** -20)))
+
+
+def mixed_matrix(m, n):
+    """A matrix whose runs of four stages take turns: all of one magnitude, two magnitudes by
+    halves of the run, by stages, by blocks of a stage."""
+    k = np.arange(n // 16)
+    run, stage, block = k // 16 % 4, k // 4 % 4, k % 4
+    e = -5 * np.where(run == 1, stage // 2, np.where(run == 2, stage % 2, np.where(run == 3, block % 2, 0)))
+    x = np.random.default_rng(m + n).standard_normal((m, n)).astype(np.float32)
+    x *= np.exp2(e.repeat(16)).astype(np.float32)
+    return (x / np.linalg.norm(x.astype(np.float64))).astype(np.float32)
+
+
+def operand_levels(q):
+    """The chain levels of an NVFP4 record (rows of the product's operand): per 32 rows, the
+    largest bound over runs of one, two and four stages."""
+    rows, K = q.codes.shape
+    nst = -(-K // 64)
+    k2 = np.zeros((rows, nst * 64), np.int64)
+    k2[:, :K] = K2[q.codes & 7] * np.where(q.codes & 8, -1, 1)
+    sc = np.zeros((rows, nst * 4), np.int64)
+    sc[:, :K // 16] = q.scales
+    words = [[row_word(k2[r, 64 * s:64 * s + 64].reshape(4, 16), [int(c) for c in sc[r, 4 * s:4 * s + 4]])
+              for s in range(nst)] for r in range(rows)]
+    return [np.array([[max(run_bound([words[r][s] if s < nst else 15 for s in range(g * j, g * j + g)])
+                           for r in range(u, min(u + 32, rows))) for j in range(-(-nst // g))]
+                      for u in range(0, rows, 32)]) for g in (1, 2, 4)]
+
+
+def outcomes(levels):
+    """{(stage chains, its run of two holds, its run of four holds): stages of unit pairs}."""
+    one, two, four = levels
+    count = {}
+    for s in range(one.shape[1]):
+        held = [np.outer(lv[:, s // g], lv[:, s // g]) < LIM for lv, g in ((one, 1), (two, 2), (four, 4))]
+        for key in zip(*(h.reshape(-1).tolist() for h in held)):
+            count[key] = count.get(key, 0) + 1
+    return count
 
 
 def make_row(rng, stages, lo, hi, kind):
@@ -92,3 +133,13 @@ def test_rounding_up():
                     for b, c in enumerate(codes[0]))
         t = float(np.uint32(row_word(k2[0], [int(c) for c in codes[0]]) & ~15).view(np.float32))
         assert exact <= t <= exact + 47 * 2.0 ** (math.frexp(float(exact))[1] - 23)
+
+
+@pytest.mark.parametrize("shape", [(272, 1104), (112, 2000), (48, 4240), (16, 32848)])
+def test_mixed_matrix_has_every_outcome(shape):
+    """The GPU test's matrices reach every kind of stage: none of its bounds holds, its own
+    only, its run of two, its run of four (each a twentieth of all stages at least)."""
+    q = quantize(mixed_matrix(*shape), 1, rht.step_signs(7, 2), True)
+    count = outcomes(operand_levels(q))
+    assert set(count) == {(False, False, False), (True, False, False), (True, True, False), (True, True, True)}
+    assert min(count.values()) >= sum(count.values()) / 20

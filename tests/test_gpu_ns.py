@@ -145,8 +145,8 @@ def test_orthogonalize_default_coeffs_and_zero_steps():
 
 
 def test_orthogonalize_large_group_copy_out():
-    """More than 32 matrices of one shape are written back by the copy-out kernel
-    (tall ones transposed back): exact at zero steps, the oracle's NS after five."""
+    """Groups of many matrices, tall ones among them: at zero steps they are written back by
+    the copy-out kernel (exact), after five by the last update product (the oracle's NS)."""
     mats = [workloads.matrix(96, 32, seed=50 + i) for i in range(40)]
     mats += [workloads.matrix(32, 64, seed=90 + i) for i in range(36)]
     ins = [torch.from_numpy(m).cuda() for m in mats]

@@ -1,13 +1,12 @@
 """The NVFP4 products' two tile forms give the same bits.
 
-The products cover each 128 x 128 output tile either with four waves of 64 x 64
-outputs or with eight waves of 32 x 64, chosen per launch by how many rounds of
-resident workgroups the launch fills.  Every product is exact (the binary32
-rounding of its exact value), so the two forms must agree bit for bit; the other
-GPU tests hold the per-launch choice to the oracle, and since the small shapes
-they use run the narrow form, these cases force each form on ragged shapes:
-sides that are not multiples of 128 (tail tiles), of 64 (no chain records: every
-block folds) or both, wide and tall inputs, and a partial last 64-element stage.
+The products run with workgroup tiles of 128 x 128 outputs (64 x 64 per wave) or 64 x 64
+(32 x 32 per wave), chosen per launch by the number of tiles.  Every product is exact (the
+binary32 rounding of its exact value), so the two forms must agree bit for bit; the other
+GPU tests hold the per-launch choice to the oracle, and since the small shapes they use
+run the narrow form, these cases force each form on ragged shapes: sides that are not
+multiples of 128 (tail tiles), of 64 (a partial last stage, which chains like the others)
+or both, wide and tall inputs.
 """
 import numpy as np
 import pytest
