@@ -344,8 +344,8 @@ int fp4root_version(void);
  * The NVFP4 products run with workgroup tiles of 128 x 128 outputs, 64 x 64 per wave
  * ("wide"), or 64 x 64 outputs, 32 x 32 per wave ("narrow").  By default (mode 0) a
  * launch takes the wide form when it has at least one round of wide workgroups (two
- * per CU), the narrow form otherwise.  Mode 1 forces the narrow form everywhere, mode
- * 2 the wide form.  Every product is exact, so outputs are bit for bit the same in
+ * per CU), with the tiles of a nearly empty last round cut into narrow ones, and the
+ * narrow form otherwise.  Mode 1 forces the narrow form everywhere, mode 2 the wide form.  Every product is exact, so outputs are bit for bit the same in
  * every mode; only the time changes.  The setting is process-wide and applies to
  * launches issued after the call (calls on other threads race with it).
  * Returns the previous mode, or FP4ROOT_ERR_INVALID_ARG for a mode outside 0..2. */

@@ -64,8 +64,7 @@ bool aligned(const void* p, size_t a) { return ((uintptr_t)p % a) == 0; }
 
 // Each side at most 2^21: the products address one 128-row tile of an operand or
 // of the output with 32-bit byte offsets (128 * 2^21 * 4 bytes = 2^30).  At most
-// 2^36 elements (256 GiB of FP32): the chain records of a matrix, K rows / 256
-// bytes, are then addressed with 32-bit offsets too.
+// 2^36 elements: 256 GiB of FP32, about what the device holds.
 constexpr int64_t kMaxDim = int64_t(1) << 21;
 constexpr int64_t kMaxElems = int64_t(1) << 36;
 // Row strides of the matrix lists (MatRef keeps them in 31 bits of 16-byte units): 16 rows of
@@ -157,8 +156,11 @@ struct StepWs {
   char* blaslt_ws = nullptr;   // scratch of the library GEMM (update product)
 };
 
-// Chain bounds over runs of up to four stages take one more launch per encoder; with
-// few stages the encoders' own one-stage records do.
+// Chain bounds over runs of up to four stages take one more launch per encoder (about 5 us);
+// with few stages the encoders' own one-stage records do.  Bounds from 512 elements on
+// instead of 1024: 256 matrices of 512 x 512 3759 -> 3831 us per call, one of 256 x 512 244 -> 258.
+// From 2048 on: 12 parameters of 256 x 256 and 256 x 1024 384 -> 370, three ragged groups of 1040
+// to 4112 773 -> 764, one 4096 x 4096 and a step of a 3B-shaped block the same within 0.1 %.
 constexpr int64_t kLevelsMinK = 1024;
 bool use_levels(int64_t K) { return K >= kLevelsMinK; }
 int64_t words_stride(int64_t rows, int64_t K) { return (K + 63) / 64 * rows; }
@@ -316,7 +318,9 @@ int launch_products(GemmMode mode, int timer_kernel, const StepGroup* gs, int co
   return FP4ROOT_OK;
 }
 
-constexpr int64_t kShareTiles = 512;   // a round of wide tiles
+// A round of wide tiles.  Shared update products run narrow below it; exactly that many, and
+// launches forced to the wide form, run wide.
+constexpr int64_t kShareTiles = 512;
 
 // One NVFP4 NS step on `count` shape groups at once: each kernel of the step runs
 // for every group before the next kernel, and the two Gram products of all groups
@@ -774,7 +778,7 @@ int check_quantize(const float* x, int64_t batch, int64_t rows, int64_t cols, in
 
 // The launches of fp4root_quantize (arguments checked, batch > 0) on the scratch
 // memory at ws: with `collect` fp4root_quantize_workspace bytes, otherwise
-// noalloc_scratch_bytes (the clip passes then read the matrix three times, in chunks of
+// kNoAllocScratchBytes (the clip passes then read the matrix three times, in chunks of
 // kNoAllocChunk).  Every part that must start at zero is cleared by a kernel first.
 int quantize_launch(const float* x, int64_t batch, int64_t rows, int64_t cols, int64_t ld, int64_t batch_stride,
                     int axis, uint32_t flags, float clip_quantile, uint64_t seed, int32_t step, uint8_t* codes,

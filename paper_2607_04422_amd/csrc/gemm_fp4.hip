@@ -107,7 +107,7 @@ FP4R_DEV void tile_coords(int64_t t, int tiles_m, int tiles_n, bool sym, int& tm
 // NVFP4 operand staging.  A lane of a 32x32x16 MFMA holds eight consecutive
 // contraction elements of one row: half h = lane / 32 of a 16-element block.  The
 // operands are stage-major with the code words of a row's four blocks ordered by
-// half (see QOut::tiled), so the 16 bytes at half h are the lane's codes of a whole
+// half (see OperandOut), so the 16 bytes at half h are the lane's codes of a whole
 // stage, one word per block.  Each wave copies the rows it multiplies into a ring of
 // its own in LDS, straight from memory (global_load_lds, no registers), and decodes
 // the words in registers just before their MFMAs: no data passes between waves, so
@@ -480,17 +480,13 @@ FP4R_DEV void gemm_fp4_tile(const GemmFp4Args& g, int64_t mat, int tm, int tn, c
     __builtin_amdgcn_sched_barrier(0);
     // the MFMAs of block kb and the decode of the next block, in a fixed order: one
     // MFMA, then the vector instructions that fit its time on the matrix core
-    auto block = [&](auto kb_tag, auto fresh_tag) __attribute__((always_inline)) {
+    auto block = [&](auto kb_tag) __attribute__((always_inline)) {
       constexpr int kb = decltype(kb_tag)::value;
-      constexpr bool fresh = decltype(fresh_tag)::value;
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          if (fresh) fold(i, j);
-          p[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(op[kb & 1][i], op[kb & 1][TM + j],
-                                                           fresh ? zero : p[i][j], 0, 0, 0);
-        }
+        for (int j = 0; j < TN; ++j)
+          p[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(op[kb & 1][i], op[kb & 1][TM + j], p[i][j], 0, 0, 0);
 #pragma unroll
       for (int t = 0; t < kOps; ++t) {
         decode((kb + 1) & 3, t);
@@ -498,7 +494,6 @@ FP4R_DEV void gemm_fp4_tile(const GemmFp4Args& g, int64_t mat, int tm, int tn, c
       }
 #pragma unroll
       for (int t = 0; t < TM * TN; ++t) {
-        if (fresh) __builtin_amdgcn_sched_group_barrier(kSchedValu, 32, 0);
         __builtin_amdgcn_sched_group_barrier(kSchedMfma, 1, 0);
         __builtin_amdgcn_sched_group_barrier(kSchedValu, (8 * kOps + TM * TN - 1) / (TM * TN) + 1, 0);
       }
@@ -525,16 +520,16 @@ FP4R_DEV void gemm_fp4_tile(const GemmFp4Args& g, int64_t mat, int tm, int tn, c
           p[i][j] = zero16();
         }
     }
-    block(block_t<0>(), std::false_type());
+    block(block_t<0>());
     split();
-    block(block_t<1>(), std::false_type());
+    block(block_t<1>());
     split();
-    block(block_t<2>(), std::false_type());
+    block(block_t<2>());
     split();
     wait_loads<kLoads>();
     read_raw(s + 1);
     __builtin_amdgcn_sched_barrier(0);
-    block(block_t<3>(), std::false_type());
+    block(block_t<3>());
   }
   wait_loads<0>();
   if constexpr (!ACC32) {

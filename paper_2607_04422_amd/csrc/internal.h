@@ -147,7 +147,7 @@ struct ClipArgs {   // what the passes' kernels read of it
 };
 // Chunks of several shape groups whose clip passes and copies share launches instead of
 // seven launches of 3 to 10 us per group (12 parameters of 256 x 256 and 256 x 1024: 416 ->
-// 387 us per optimizer step, three ragged groups of 6.6 M elements 839 -> 749 per call).
+// 387 us per optimizer step, three ragged groups of 6.6 M elements 839 -> 773 per call).
 // Only groups of together at most kClipSetElems elements (64 MB): a larger group finds its
 // matrices in the last-level cache again when its passes follow each other.
 constexpr int kMaxClipSets = 4, kMaxClipSetMats = 64;
