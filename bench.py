@@ -39,9 +39,7 @@ COPY_PROBE_BYTES = 256 << 20
 METRIC = "NS-orthogonalised matrices/s + effective TFLOP/s (% MFMA peak), 3B-shaped set"
 BF16_MFMA_PEAK_TFLOPS = 2516.6
 # The exact NVFP4 products run on the f16 MFMA (32x32x16, decoded operands), whose dense
-# peak is the bf16/fp16 one: 2.5 PFLOP/s.  With whole 4-block stages chained into one
-# binary32 accumulator, the binary64 folds (2 VALU ops per output per 64-element stage)
-# match that rate too: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz / 2 x 128 FLOP = 2516 TFLOP/s.
+# peak is the bf16/fp16 one: 2.5 PFLOP/s.
 F16_MFMA_PEAK_TFLOPS = BF16_MFMA_PEAK_TFLOPS
 HBM_PEAK_GBS = 8000.0   # MI355X HBM3E
 TRAFFIC_RECORD = os.path.join(ROOT, "profiles", "k_gemm_fp4_update_block3b_x4_traffic.md")
