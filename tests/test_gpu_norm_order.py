@@ -4,7 +4,7 @@ The first element is L and the others are small enough that a binary64 sum with 
 each one's square, so how many of them are added to L^2 one by one, and how many are summed
 apart first, shows in the last place of the sum; eps puts the inverse norm next to a
 binary32 rounding boundary, so that one last place of the sum decides the result.  (The pairs
-separate sums over 2048 quads of the matrix from sums over 8192 quads.)
+separate sums over 512 16-byte quads of the matrix from sums over 2048.)
 """
 import numpy as np
 import pytest
